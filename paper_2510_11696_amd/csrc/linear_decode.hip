@@ -466,6 +466,46 @@ __global__ __launch_bounds__(256) void prepack_kernel(const uint8_t* __restrict_
   }
 }
 
+// The same order where the canonical rows can be read in whole 16-weight blocks (codes on an 8-byte boundary; a row
+// of them is a multiple of 8 bytes long as it is).  Bound by memory: 18944 x 3584 takes 16 us
+// (4.8 TB/s) against 26 us when each dword is assembled from bytes by prepack_kernel.  A wave owns one tile, lane (p, row) the 64 weights of plane p: it reads 32 consecutive bytes
+// and writes the 16-byte pieces of lanes row and row + 32, so that a wave writes 512 consecutive bytes per
+// instruction; the four waves of a workgroup take four neighbours along K, which share cache lines of every row.
+__global__ __launch_bounds__(256) void prepack_blocks_kernel(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, int64_t N,
+                                                             int64_t K, int64_t k_tiles, int64_t k_quads, bool scale_dwords,
+                                                             uint8_t* __restrict__ out) {
+  const int64_t nt = blockIdx.x / k_quads;
+  const int64_t kt = (blockIdx.x - nt * k_quads) * 4 + (threadIdx.x >> 6);
+  if (kt >= k_tiles) return;
+  const int r32 = threadIdx.x & 31, p = (threadIdx.x >> 5) & 1;
+  const int64_t row = nt * 32 + r32;
+  uint8_t* dst = out + (nt * k_tiles + kt) * kPackTileBytes;
+  const int64_t blk = kt * 8 + 4 * p, blks = K / kBlock;   // this lane's four 16-weight blocks
+  u32x4 lo = {0u, 0u, 0u, 0u}, hi = lo;                    // weights 0..7 and 8..15 of each block
+  uint32_t sc = 0;
+  if (row < N) {
+    const uint8_t* src = codes + row * (K / 2) + blk * 8;
+    const uint8_t* ss = scales + row * blks + blk;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      if (blk + b < blks) {
+        const u32x2 v = *reinterpret_cast<const u32x2*>(src + b * 8);
+        lo[b] = v[0];
+        hi[b] = v[1];
+      }
+    if (scale_dwords) {                                    // K a multiple of 64, scales on a 4-byte boundary
+      if (blk < blks) sc = *reinterpret_cast<const uint32_t*>(ss);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if (blk + b < blks) sc |= (uint32_t)ss[b] << (8 * b);
+    }
+  }
+  *reinterpret_cast<u32x4*>(dst + p * 1024 + r32 * 16) = lo;
+  *reinterpret_cast<u32x4*>(dst + p * 1024 + 512 + r32 * 16) = hi;
+  *reinterpret_cast<uint32_t*>(dst + 2048 + (r32 * 2 + p) * 4) = sc;
+}
+
 // ---- host ------------------------------------------------------------------------------------------
 
 static int g_force_kw = 0, g_force_t = 0;
@@ -520,6 +560,11 @@ int launch_decode(const DecodePlan& p, const DecodeArgs& a, hipStream_t st) {
 int launch_prepack(const uint8_t* codes, const uint8_t* scales, int64_t N, int64_t K, uint8_t* out,
                    hipStream_t st) {
   const int64_t n_tiles = ceil_div(N, kPackTileRows), k_tiles = ceil_div(K, kPackTileK);
+  if (aligned(codes, 8)) {
+    const int64_t k_quads = ceil_div(k_tiles, 4);
+    prepack_blocks_kernel<<<(unsigned)(n_tiles * k_quads), 256, 0, st>>>(codes, scales, N, K, k_tiles, k_quads, K % 64 == 0 && aligned(scales, 4), out);
+    return launch_status();
+  }
   prepack_kernel<<<(unsigned)(n_tiles * k_tiles), 256, 0, st>>>(codes, scales, N, K, n_tiles, k_tiles, out);
   return launch_status();
 }
