@@ -64,3 +64,50 @@ def test_quantize_is_deterministic():
     for _ in range(5):
         b = qerl.nvfp4_quantize(W)
         assert all(torch.equal(p, q) for p, q in zip(a, b))
+
+
+@pytest.mark.parametrize("amax", [1.0, 0.0546875, 3.0e4, 2.0e-20, 1.0e-30])
+def test_quantize_every_bf16_below_the_block_maximum(amax):
+    """Sixteenths of every binade a code can come from, around all rounding boundaries, under several block maxima:
+    the codes taken from w * (1 / d) equal those of the divisions, next to a boundary and away from it."""
+    top = torch.tensor([amax], dtype=torch.bfloat16).view(torch.int16).item()
+    rows = []
+    for bmax in (top, top - 1, top - 37, top - 128 * 3 - 5, top - 128 * 9 - 77):
+        mags = np.arange(max(bmax - 128 * 6, 0), bmax + 1, dtype=np.int64)
+        mags = np.concatenate([mags, np.zeros(-len(mags) % 15, dtype=np.int64)]).reshape(-1, 15)
+        blocks = np.concatenate([np.full((len(mags), 1), bmax), mags], axis=1)
+        blocks[:, 1::2] |= 0x8000
+        rows.append(blocks)
+    bits = np.concatenate(rows)
+    bits = np.concatenate([np.tile(np.int64(top), (1, 16)), bits])
+    W = (bits.astype(np.uint32) << 16).view(np.float32).reshape(1, -1)
+    gpu, ref = quantize_both(W)
+    _assert_same(gpu, ref, amax)
+
+
+@pytest.mark.parametrize("N,K,ldw", [(1, 16, 16), (255, 16 * 129, 16 * 129), (257, 16 * 129, 16 * 131), (1111, 16 * 480, 16 * 480),
+                                     (700, 16 * 800, 16 * 800 + 8)])
+def test_quantize_remainders_of_the_two_passes(N, K, ldw):
+    """Less than one load per thread, remainders of the unrolled maximum, several encode steps per thread; rows with
+    and without a gap behind them."""
+    W = cases.gaussian(N, K, seed=N)
+    big = torch.full((N, ldw), 9.0, dtype=torch.bfloat16, device="cuda")
+    big[:, :K] = to_gpu_bf16(W)
+    _assert_same(qerl.nvfp4_quantize(big[:, :K]), oracle.nvfp4_quantize(W), (N, K, ldw))
+
+
+@pytest.mark.parametrize("N,K", [(1, 16), (33, 272), (64, 640), (100, 1104), (32, 64 * 9)])
+def test_prepack_of_unaligned_codes_and_scales_is_the_same(N, K):
+    gen = torch.Generator().manual_seed(N * K)
+    codes = torch.randint(0, 256, (N, K // 2), generator=gen, dtype=torch.uint8).cuda()
+    scales = torch.randint(0, 127, (N, K // 16), generator=gen, dtype=torch.uint8).cuda()
+    ts = torch.ones(1, device="cuda")
+    want = qerl.nvfp4_prepack(codes, scales, ts).packed
+
+    def shifted(t, by):
+        flat = torch.empty(t.numel() + 16, dtype=torch.uint8, device="cuda")
+        flat[by:by + t.numel()] = t.flatten()
+        return flat[by:by + t.numel()].view(t.shape)
+
+    for cs, ss in ((0, 1), (8, 2), (4, 0), (1, 3)):
+        assert torch.equal(qerl.nvfp4_prepack(shifted(codes, cs), shifted(scales, ss), ts).packed, want), (cs, ss)
