@@ -61,179 +61,271 @@ __global__ __launch_bounds__(256) void prepack_t_kernel(const uint8_t* __restric
   }
 }
 
-// One launch before the products of a call: AT[c, j] = A[j, c] and BT[j, n] = B[n, j] (the adapters change with every
-// optimiser step, so both are transposed per call), and the arrival counters of the K-split down-projections set
-// to zero.  Blocks [0, blocks_a) transpose A, the next blocks_b transpose B, the last block clears the counters.
-__global__ __launch_bounds__(256) void backward_prepare_kernel(const uint16_t* __restrict__ A, int64_t r, int64_t K, uint16_t* __restrict__ AT,
-                                                               const uint16_t* __restrict__ B, int64_t N, uint16_t* __restrict__ BT,
-                                                               int blocks_a, int blocks_b, uint32_t* __restrict__ counters, int n_counters) {
-  int b = blockIdx.x;
-  if (b >= blocks_a + blocks_b) {
-    for (int i = threadIdx.x; i < n_counters; i += 256) counters[i] = 0u;
+// One launch before the products of a call: AT[c, j] = A[j, c] and BT[j, n] = B[n, j] of every member (the adapters
+// change with every optimiser step, so they are transposed per call), and the arrival counters of the K-split
+// down-projections set to zero by the last block.  64 x 64 tiles through LDS, whole rows of a tile on both sides.
+struct TransposeJob { const uint16_t* in; uint16_t* out; int64_t R, C; int block0; };   // in [R, C], out [C, R]
+struct PrepareArgs { TransposeJob job[2 * kMaxGroup]; int n; int n_blocks; uint32_t* counters; int n_counters; };
+__global__ __launch_bounds__(256) void backward_prepare_kernel(const PrepareArgs a) {
+  __shared__ uint16_t lds[64 * 66];    // 64 x 64 elements; the odd number of dwords per row spreads the banks
+  const int b = blockIdx.x;
+  if (b >= a.n_blocks) {
+    for (int i = threadIdx.x; i < a.n_counters; i += 256) a.counters[i] = 0u;
     return;
   }
-  const uint16_t* in = A;
-  uint16_t* out = AT;
-  int64_t R = r, C = K;           // in is [R, C], out [C, R]
-  int blocks = blocks_a;
-  if (b >= blocks_a) { b -= blocks_a; in = B; out = BT; R = N; C = r; blocks = blocks_b; }
-  const int64_t total = R * C;
-  for (int64_t i = (int64_t)b * 256 + threadIdx.x; i < total; i += (int64_t)blocks * 256) {
-    const int64_t c = i / R, rr = i - c * R;       // consecutive threads write consecutive elements of out
-    out[i] = in[rr * C + c];
+  int ji = 0;
+#pragma unroll
+  for (int i = 1; i < 2 * kMaxGroup; ++i) ji = i < a.n && b >= a.job[i].block0 ? i : ji;
+  const TransposeJob t = a.job[ji];
+  const int c_tiles = (int)ceil_div_dev(t.C, 64), tile = b - t.block0, rt = tile / c_tiles;
+  const int64_t r0 = (int64_t)rt * 64, c0 = (int64_t)(tile - rt * c_tiles) * 64;
+  const int i = threadIdx.x & 63, j0 = threadIdx.x >> 6;
+  uint16_t v[16];                      // all requested before the first is stored; rows and columns outside are redirected
+  const int64_t ci = c0 + i < t.C ? c0 + i : t.C - 1;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int64_t rj = r0 + j0 + 4 * k;
+    v[k] = t.in[(rj < t.R ? rj : t.R - 1) * t.C + ci];
   }
+#pragma unroll
+  for (int k = 0; k < 16; ++k) lds[(j0 + 4 * k) * 66 + i] = v[k];
+  __syncthreads();
+#pragma unroll
+  for (int j = j0; j < 64; j += 4)
+    if (c0 + j < t.C && r0 + i < t.R) t.out[(c0 + j) * t.R + r0 + i] = lds[i * 66 + j];
 }
 
-// ---- dA, dB: partial[chunk][c][j] = sum over the chunk's tokens of P[m, j] * Q[m, c] ------------------------
+// ---- dA, dB: sum over the tokens of P[m, j] * Q[m, c], all of a call's products in one launch --------------------
 // P [M, r] arrives as the three bf16 terms the LoRA down-projection kernel writes ([M, ts_ld]: hi | mid | lo,
-// their sum exact to 2^-24); Q is x or dY (bf16, row-major).  Both operands are contracted over their ROWS, so a
-// lane's eight consecutive contraction values lie in eight different rows: tiles of 32 tokens go through LDS
-// row by row (coalesced) and are read back column-wise, two bf16 values per dword.  A workgroup owns 128 columns
-// of Q (32 per wave), all ranks and one token chunk; three MFMAs per rank tile and 16 tokens (one per term).
+// their sum exact to 2^-24); Q is x (dA) or dY (dB), bf16, row-major.  Both operands are contracted over their ROWS, so a
+// lane's eight consecutive contraction values lie in eight different rows.  A thread therefore fetches two columns of
+// eight tokens (256 contiguous bytes per wave and row), turns them in registers and leaves two 16-byte MFMA operands in
+// LDS ([8-token group][column][8 tokens]), which the products read back with one ds_read_b128 each: seven reads for
+// six MFMAs, the two pipes about level.  With row-major tiles and sixteen-bit reads, 56 of them for the same six, the LDS
+// pipe was the bound, and each product was a launch of its own: the fourteen products of a 14B layer (2048 tokens, r = 64)
+// took 364 us and their sums 78 us in 28 launches, against 166 us and 29 us in eight.  Guarded 64-bit loads instead of buffer
+// loads (a branch and an argument fetch each) cost 404 us.
+// A workgroup owns 128 columns of one product (32 per wave), all ranks and one chunk of the tokens; three MFMAs per rank tile and
+// 16 tokens (one per term).  Chunks: as many as give a product 128 workgroups -- their partial sums, 4 r bytes per
+// column and chunk, are written and read once each, so no more than that.  The count depends on the product alone, not on
+// the group it comes in, so a member's gradients are the same bits in a group and by themselves.  The partial sums are added
+// in order by a second launch.
 constexpr int kGradRanks = 64;       // most ranks
-constexpr int kGradChunksMax = 8;    // token chunks (workgroups along M) whose partial sums are added in order
-constexpr int kGradTokens = 32;      // tokens per LDS tile
-constexpr int kGradQStride = 128 + 8, kGradPStride = 3 * kGradRanks + 8;   // u16 per LDS row: 16 bytes of padding shift the banks from row to row
-// RANK_MAJOR: the result is wanted as [r, C] (dA): the MFMA operands change places, so that a lane owns a column
-// and the partial sums leave as partial[chunk][j][c], rows of C contiguous like the final result.
+constexpr int kGradChunksMax = 8;    // token chunks (workgroups along M)
+constexpr int kGradTokens = 64;      // tokens per LDS tile
+constexpr int kGradGroups = kGradTokens / 8, kGradCols = 128, kGradPCols = 3 * kGradRanks;
+constexpr int64_t kGradWorkgroups = 128;
+constexpr int64_t kGradChunkTiles = 10;   // most tiles of a chunk (up to kGradChunksMax of them): the fp32 chains stay at or below 640 tokens
+struct GradSplit { int n_chunks; int64_t tokens_per_chunk; };
+static GradSplit grad_split(int64_t M, int64_t C) {
+  const int64_t tiles = ceil_div(M, kGradTokens);
+  int64_t chunks = ceil_div(kGradWorkgroups, ceil_div(C, kGradCols));
+  const int64_t by_tiles = ceil_div(tiles, kGradChunkTiles);
+  chunks = chunks < by_tiles ? by_tiles : chunks;
+  chunks = chunks > kGradChunksMax ? kGradChunksMax : chunks;
+  chunks = chunks > tiles ? tiles : chunks;
+  const int64_t tokens = ceil_div(tiles, chunks) * kGradTokens;
+  return GradSplit{(int)ceil_div(M, tokens), tokens};
+}
+struct GradJob {
+  const uint16_t* P; int64_t p_ld; const uint16_t* Q; int64_t q_ld; int64_t C; int r;
+  int rank_major;                    // result wanted as [r, C] (dA), else [C, r] (dB)
+  const float* mult; float* out;
+  int n_chunks; int64_t tokens_per_chunk;
+  int col_blocks, block0;            // the product's workgroups: [chunk][column block] from block0 on
+  float* partial;                    // [chunk][C r] in the order of the result
+  int64_t elem0;                     // first of the product's elements among those the second launch sums
+};
+struct GradArgs { GradJob job[2 * kMaxGroup]; int n; int n_blocks; int64_t M, elems; };
+
+// RANK_MAJOR: the MFMA operands change places, so that a lane owns a column and the results leave as rows of C.
 template <bool RANK_MAJOR>
-__global__ __launch_bounds__(256) void lora_grad_partial_kernel(const uint16_t* __restrict__ ts, int64_t ts_ld, int r,
-                                                                const uint16_t* __restrict__ Q, int64_t ldq, int64_t M, int64_t C,
-                                                                int64_t tokens_per_chunk, float* __restrict__ partial) {
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[kGradTokens * kGradQStride];
-  __shared__ __attribute__((aligned(16))) uint16_t sP[kGradTokens * kGradPStride];
+__device__ __forceinline__ void lora_grad_block(const GradJob& jb, int64_t c0, int64_t m_lo, int64_t m_hi, float mult, float* dst,
+                                                u32x4* sQ, u32x4* sP) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, kg = lane >> 5;
-  const int64_t c0 = (int64_t)blockIdx.x * 128;
-  const int64_t m_lo = (int64_t)blockIdx.y * tokens_per_chunk;
-  const int64_t m_hi = m_lo + tokens_per_chunk < M ? m_lo + tokens_per_chunk : M;
-  const int p_chunks = 3 * r / 8;      // 16-byte chunks of a row of the three terms
-  f32x16 acc[2];
+  const int r = jb.r;
+  const int64_t C = jb.C;
+  f32x16 hi[2], lo[2];   // the first term's sums apart from the smaller two's: a third of the roundings at full magnitude
 #pragma unroll
   for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[jt][i] = 0.f;
-  // the tile after the current one is requested before the current one is multiplied (registers), so that a
-  // workgroup pays the memory latency once, not once per tile
-  u32x4 qreg[2], preg[3];
+    for (int i = 0; i < 16; ++i) hi[jt][i] = lo[jt][i] = 0.f;
+  // The tile after the current one is requested before the current one is multiplied.  Buffer loads relative to the
+  // tile: tokens past the chunk's end lie behind the descriptor's range and read as zero, without a branch per load.
+  // Columns of Q past C read whatever follows inside the range (their sums are dropped), columns of P past 3 r are not fetched.
+  // Rows so far apart that 32 bits do not span a tile take guarded loads.
+  constexpr int kQTasks = kGradGroups * (kGradCols / 2) / 256, kPTasks = kGradGroups * (kGradPCols / 2) / 256;
+  uint32_t qreg[kQTasks][8], preg[kPTasks][8];
+  const uint16_t* const Q = jb.Q;
+  const uint16_t* const P = jb.P;
+  const int64_t q_ld = jb.q_ld, p_ld = jb.p_ld;
+  const bool far = q_ld >= (int64_t)1 << 24;
+  const uint32_t q_row = (uint32_t)q_ld * 2, p_row = (uint32_t)p_ld * 2;
+  const int p_pairs = 3 * r / 2;
+  uint32_t q_off[kQTasks], p_off[kPTasks];
+  int p_slot[kPTasks];
+#pragma unroll
+  for (int i = 0; i < kQTasks; ++i) {
+    const int idx = tid + 256 * i;
+    q_off[i] = (uint32_t)(idx >> 6) * 8 * q_row + (uint32_t)(idx & 63) * 4;
+  }
+#pragma unroll
+  for (int i = 0; i < kPTasks; ++i) {
+    const int idx = tid + 256 * i, g = idx / p_pairs, pair = idx - g * p_pairs;
+    p_off[i] = g < kGradGroups ? (uint32_t)g * 8 * p_row + (uint32_t)pair * 4 : 0x80000000u;   // past any range
+    p_slot[i] = g < kGradGroups ? g * kGradPCols + 2 * pair : -1;
+  }
   auto request = [&](int64_t m0) {
+    const int64_t left = m_hi - m0;
+    const uint32_t rows = left <= 0 ? 0u : (uint32_t)(left < kGradTokens ? left : kGradTokens);
+    const int64_t mb = rows ? m0 : m_lo;
+    if (far) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {      // Q tile: 32 rows x 16 chunks
-      const int idx = tid + 256 * i, row = idx >> 4, ch = idx & 15;
-      qreg[i] = u32x4{0u, 0u, 0u, 0u};
-      if (m0 + row < m_hi && c0 + ch * 8 < C) qreg[i] = *reinterpret_cast<const u32x4*>(Q + (m0 + row) * ldq + c0 + ch * 8);
-    }
+      for (int i = 0; i < kQTasks; ++i) {
+        const int idx = tid + 256 * i, g = 8 * (idx >> 6);
+        const int64_t c = c0 + 2 * (idx & 63);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {      // P tile: 32 rows x up to 24 chunks
-      const int idx = tid + 256 * i, row = idx / 24, ch = idx - row * 24;
-      preg[i] = u32x4{0u, 0u, 0u, 0u};
-      if (m0 + row < m_hi && ch < p_chunks) preg[i] = *reinterpret_cast<const u32x4*>(ts + (m0 + row) * ts_ld + ch * 8);
+        for (int e = 0; e < 8; ++e) {
+          qreg[i][e] = 0u;
+          if ((uint32_t)(g + e) < rows && c < C) qreg[i][e] = *reinterpret_cast<const uint32_t*>(Q + (mb + g + e) * q_ld + c);
+        }
+      }
+    } else {
+      const uint32_t bytes = rows ? (rows - 1) * q_row + (uint32_t)(C - c0 < kGradCols ? C - c0 : kGradCols) * 2 : 0u;
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Q + mb * q_ld + c0), 0, (int)bytes, 0x00027000);
+#pragma unroll
+      for (int i = 0; i < kQTasks; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qreg[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(q_off[i] + e * q_row), 0, 0);
     }
+    const uint32_t bytes = rows ? (rows - 1) * p_row + (uint32_t)r * 6 : 0u;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(P + mb * p_ld), 0, (int)bytes, 0x00027000);
+#pragma unroll
+    for (int i = 0; i < kPTasks; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) preg[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)(p_off[i] + e * p_row), 0, 0);
+  };
+  auto turn = [](const uint32_t (&v)[8], u32x4* to) {   // eight tokens of two columns -> two operands
+    u32x4 a, b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      a[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x05040100u);
+      b[e] = __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], 0x07060302u);
+    }
+    to[0] = a;
+    to[1] = b;
   };
   request(m_lo);
   for (int64_t m0 = m_lo; m0 < m_hi; m0 += kGradTokens) {
     __syncthreads();                   // the previous tile has been read
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int idx = tid + 256 * i, row = idx >> 4, ch = idx & 15;
-      *reinterpret_cast<u32x4*>(sQ + row * kGradQStride + ch * 8) = qreg[i];
-    }
+    for (int i = 0; i < kQTasks; ++i) turn(qreg[i], sQ + 2 * (tid + 256 * i));
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int idx = tid + 256 * i, row = idx / 24, ch = idx - row * 24;
-      *reinterpret_cast<u32x4*>(sP + row * kGradPStride + ch * 8) = preg[i];
-    }
+    for (int i = 0; i < kPTasks; ++i)
+      if (p_slot[i] >= 0) turn(preg[i], sP + p_slot[i]);
     __syncthreads();
     request(m0 + kGradTokens);         // past the chunk's end every guard fails: zeros, no access
 #pragma unroll
     for (int ks = 0; ks < kGradTokens / 16; ++ks) {
-      const int rb = ks * 16 + 8 * kg;   // this lane's eight tokens of the step
-      u32x4 af;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t lo = sQ[(rb + 2 * e) * kGradQStride + wave * 32 + n32], hi = sQ[(rb + 2 * e + 1) * kGradQStride + wave * 32 + n32];
-        af[e] = lo | (hi << 16);
-      }
+      const int g = 2 * ks + kg;       // this lane's eight tokens of the step
+      const bf16x8 af = __builtin_bit_cast(bf16x8, sQ[g * kGradCols + wave * 32 + n32]);
 #pragma unroll
       for (int jt = 0; jt < 2; ++jt) {
         const int j = jt * 32 + n32;
         if (jt * 32 < r) {             // uniform
 #pragma unroll
           for (int t = 0; t < 3; ++t) {
-            u32x4 bf = {0u, 0u, 0u, 0u};
-            if (j < r) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const uint32_t lo = sP[(rb + 2 * e) * kGradPStride + t * r + j], hi = sP[(rb + 2 * e + 1) * kGradPStride + t * r + j];
-                bf[e] = lo | (hi << 16);
-              }
-            }
-            if constexpr (RANK_MAJOR)
-              acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf), __builtin_bit_cast(bf16x8, af), acc[jt], 0, 0, 0);
-            else
-              acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af), __builtin_bit_cast(bf16x8, bf), acc[jt], 0, 0, 0);
+            u32x4 b = sP[g * kGradPCols + t * r + (j < r ? j : 0)];
+            if (j >= r) b = u32x4{0u, 0u, 0u, 0u};
+            const bf16x8 bf = __builtin_bit_cast(bf16x8, b);
+            f32x16& acc = t == 0 ? hi[jt] : lo[jt];
+            if constexpr (RANK_MAJOR) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf, af, acc, 0, 0, 0);
+            else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
           }
         }
       }
     }
   }
-  if constexpr (RANK_MAJOR) {
-    // acc[jt][q] = sum for rank 32 jt + 8 (q / 4) + 4 kg + q % 4 and column c0 + 32 wave + n32
-    const int64_t c = c0 + wave * 32 + n32;
 #pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
+  for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int j = jt * 32 + 8 * (q >> 2) + 4 * kg + (q & 3);
-        if (c < C && j < r) partial[((int64_t)blockIdx.y * kGradRanks + j) * C + c] = acc[jt][q];
-      }
-  } else {
-    // acc[jt][q] = sum for column c0 + 32 wave + 8 (q / 4) + 4 kg + q % 4 and rank 32 jt + n32
-#pragma unroll
-    for (int jt = 0; jt < 2; ++jt) {
-      const int j = jt * 32 + n32;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int64_t c = c0 + wave * 32 + 8 * (q >> 2) + 4 * kg + (q & 3);
-        if (c < C && j < r) partial[((int64_t)blockIdx.y * C + c) * kGradRanks + j] = acc[jt][q];
-      }
+    for (int q = 0; q < 16; ++q) {
+      const float v = (hi[jt][q] + lo[jt][q]) * mult;
+      const int inner = 8 * (q >> 2) + 4 * kg + (q & 3);     // MFMA result: row inner, column n32
+      const int j = jt * 32 + (RANK_MAJOR ? inner : n32);
+      const int64_t c = c0 + wave * 32 + (RANK_MAJOR ? n32 : inner);
+      if (c < C && j < r) dst[RANK_MAJOR ? j * C + c : c * r + j] = v;
     }
-  }
 }
 
-// out = mult * sum over chunks (in chunk order): [C, r] from partial[chunk][c][j], or (rank_major) [r, C] from
-// partial[chunk][j][c]; consecutive threads read and write consecutive elements either way
-__global__ __launch_bounds__(256) void lora_grad_reduce_kernel(const float* __restrict__ partial, int n_chunks, int64_t C, int r,
-                                                               const float* __restrict__ mult, int rank_major, float* __restrict__ out) {
-  const int64_t total = C * r;
-  const float s = *mult;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    int64_t first, stride;
-    if (rank_major) { first = i; stride = (int64_t)kGradRanks * C; }                       // i = j C + c
-    else { const int64_t c = i / r; first = c * kGradRanks + (i - c * r); stride = C * kGradRanks; }
-    float sum = 0.f;
-    for (int z = 0; z < n_chunks; ++z) sum += partial[first + z * stride];
-    out[i] = sum * s;
+__global__ __launch_bounds__(256) void lora_grad_kernel(const GradArgs a) {
+  __shared__ u32x4 sQ[kGradGroups * kGradCols];
+  __shared__ u32x4 sP[kGradGroups * kGradPCols];
+  int ji = 0;
+#pragma unroll
+  for (int i = 1; i < 2 * kMaxGroup; ++i) ji = i < a.n && (int)blockIdx.x >= a.job[i].block0 ? i : ji;
+  const GradJob jb = a.job[ji];
+  const int b = (int)blockIdx.x - jb.block0, chunk = b / jb.col_blocks;
+  const int64_t c0 = (int64_t)(b - chunk * jb.col_blocks) * kGradCols;
+  const int64_t m_lo = chunk * jb.tokens_per_chunk;
+  const int64_t m_hi = m_lo + jb.tokens_per_chunk < a.M ? m_lo + jb.tokens_per_chunk : a.M;
+  // the three-term values carry lora_scale / S32, the gradients want lora_scale: one multiplication by S32, here if there is
+  // one chunk, behind the sum of the chunks otherwise
+  const bool last = jb.n_chunks == 1;
+  float* dst = last ? jb.out : jb.partial + chunk * (jb.C * jb.r);
+  const float mult = last ? *jb.mult : 1.f;
+  if (jb.rank_major) lora_grad_block<true>(jb, c0, m_lo, m_hi, mult, dst, sQ, sP);
+  else lora_grad_block<false>(jb, c0, m_lo, m_hi, mult, dst, sQ, sP);
+}
+
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // the results are only known to lie on four bytes
+// out = S32 * sum over chunks (in chunk order) of every product with more than one
+__global__ __launch_bounds__(256) void lora_grad_reduce_kernel(const GradArgs a) {
+  // four consecutive elements per thread: C r is a multiple of eight
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < a.elems; i += 4 * (int64_t)gridDim.x * 256) {
+    int ji = 0;
+#pragma unroll
+    for (int k = 1; k < 2 * kMaxGroup; ++k) ji = k < a.n && i >= a.job[k].elem0 ? k : ji;
+    const GradJob& jb = a.job[ji];
+    const int64_t e = i - jb.elem0, stride = jb.C * jb.r;
+    const float* src = jb.partial + e;
+    f32x4 v[kGradChunksMax];
+#pragma unroll
+    for (int z = 0; z < kGradChunksMax; ++z) {
+      v[z] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (z < jb.n_chunks) v[z] = *reinterpret_cast<const f32x4*>(src + z * stride);
+    }
+    const float mult = *jb.mult;
+    f32x4_any out;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float sum = v[0][k];
+#pragma unroll
+      for (int z = 1; z < kGradChunksMax; ++z) sum += v[z][k];
+      out[k] = sum * mult;
+    }
+    *reinterpret_cast<f32x4_any*>(jb.out + e) = out;
   }
 }
 
 static size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
+static size_t grad_partial_bytes(int64_t M, int64_t C, int64_t r) {
+  const int n = grad_split(M > 0 ? M : 1, C).n_chunks;
+  return n > 1 ? al256((size_t)n * (size_t)(C * r) * sizeof(float)) : 0;
+}
 // Workspace of a backward call over n members that read the same x: the arrival counters of the K-split
 // down-projections, then per member A^T, B^T and the two three-term products, then one area that first holds the
-// down-projections' K-part sums and later the gradient products' partial sums.
+// down-projections' K-part sums and later the partial sums of all gradient products.
 struct BackwardMemberLayout { size_t at_off, bt_off, tsu_off, tst_off; int64_t ts_ld; int ext_stages; };
-struct BackwardLayout { size_t ctr_off, part_off, total; int n_chunks; int64_t tokens_per_chunk; BackwardMemberLayout mem[kMaxGroup]; };
+struct BackwardLayout { size_t ctr_off, part_off, total; BackwardMemberLayout mem[kMaxGroup]; };
 static BackwardLayout backward_layout(int64_t M, int64_t K, const int64_t* Ns, const int64_t* rs, int n) {
   BackwardLayout L{};
   const size_t m = (size_t)(M > 0 ? M : 1), k = (size_t)(K > 0 ? K : 1);
-  int64_t chunks = ceil_div((int64_t)m, 64);
-  chunks = chunks > kGradChunksMax ? kGradChunksMax : chunks;
-  L.n_chunks = (int)chunks;
-  L.tokens_per_chunk = ceil_div((int64_t)m, chunks);
   L.ctr_off = 0;                                   // zeroed by every call
   size_t off = al256(kDownMaxSlots * sizeof(uint32_t));
-  size_t widest = 0;
+  size_t part = 0;                                 // partial sums of the gradient products
   bool any = false;
   for (int i = 0; i < n; ++i) {
     const size_t nn = (size_t)(Ns[i] > 0 ? Ns[i] : 1), rr = (size_t)(rs[i] > 0 ? rs[i] : 0);
@@ -244,15 +336,13 @@ static BackwardLayout backward_layout(int64_t M, int64_t K, const int64_t* Ns, c
     b.bt_off = off;  off += al256(nn * rr * 2);
     b.tsu_off = off; off += al256(m * (size_t)b.ts_ld * 2);
     b.tst_off = off; off += al256(m * (size_t)b.ts_ld * 2);
-    if (rr) { any = true; widest = widest > nn ? widest : nn; }
+    if (rr) {
+      any = true;
+      part += grad_partial_bytes(M, (int64_t)k, (int64_t)rr) + grad_partial_bytes(M, (int64_t)nn, (int64_t)rr);
+    }
   }
   L.part_off = off;
-  size_t part = 0;
-  if (any) {
-    widest = widest > k ? widest : k;
-    part = al256((size_t)chunks * widest * kGradRanks * sizeof(float));
-    if (part < kDownExchangeBytes) part = kDownExchangeBytes;
-  }
+  if (any && part < kDownExchangeBytes) part = kDownExchangeBytes;
   L.total = L.part_off + part;
   return L;
 }
@@ -295,10 +385,9 @@ static int backward_validate(const void* x, int64_t M, int64_t K, int64_t ldx, c
   return QERL_OK;
 }
 
-// The members' launches: per member one that transposes its adapter, one down-projection of its own dY, and four
-// for its gradient products; shared by the group: the down-projections of x (one launch over all adapters) and dX,
-// ONE GEMM whose contraction runs over the members' rows one after the other, so that dX is summed in fp32 and
-// rounded once.
+// A call's launches: one that transposes all adapters, per member a down-projection of its own dY, the
+// down-projections of x (one launch over all adapters), dX -- ONE GEMM whose contraction runs over the members' rows one
+// after the other, so that dX is summed in fp32 and rounded once -- and one or two for the gradient products of all members.
 static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const BackwardMember* mem, int n, uint16_t* dx, int64_t lddx,
                         void* workspace, size_t workspace_bytes, hipStream_t st) {
   int64_t Ns[kMaxGroup], rs[kMaxGroup];
@@ -312,17 +401,43 @@ static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
   GemmArgs down{};   // t_i = x A_i^T of all adapters, one launch
   down.x = x; down.ldx = ldx; down.M = M; down.K = K; down.k_tiles = ceil_div(K, kPackTileK);
   down.tpart = (uint32_t*)part; down.counters = counters;
+  PrepareArgs prep{};
+  GradArgs grad{};
+  float* grad_part = part;   // the down-projections are done with the area when the gradient products start
+  auto add_grad = [&](const uint16_t* P, int64_t p_ld, const uint16_t* Q, int64_t q_ld, int64_t C, const BackwardMember& b, int rank_major, float* out) {
+    const GradSplit sp = grad_split(M, C);
+    const int cols = (int)ceil_div(C, kGradCols);
+    grad.job[grad.n++] = GradJob{P, p_ld, Q, q_ld, C, (int)b.r, rank_major, b.tensor_scale, out, sp.n_chunks, sp.tokens_per_chunk,
+                                 cols, grad.n_blocks, grad_part, grad.elems};
+    grad.n_blocks += cols * sp.n_chunks;
+    if (sp.n_chunks > 1) {
+      grad.elems += C * b.r;
+      grad_part += grad_partial_bytes(M, C, b.r) / sizeof(float);
+    }
+  };
+  for (int i = 0; i < n; ++i) {
+    const BackwardMember& b = mem[i];
+    if (b.r == 0) continue;
+    const BackwardMemberLayout& l = L.mem[i];
+    prep.job[prep.n++] = TransposeJob{b.A, (uint16_t*)(ws + l.at_off), b.r, K, prep.n_blocks};
+    prep.n_blocks += (int)(ceil_div(b.r, 64) * ceil_div(K, 64));
+    prep.job[prep.n++] = TransposeJob{b.B, (uint16_t*)(ws + l.bt_off), b.N, b.r, prep.n_blocks};
+    prep.n_blocks += (int)(ceil_div(b.N, 64) * ceil_div(b.r, 64));
+    add_grad((const uint16_t*)(ws + l.tsu_off), l.ts_ld, x, ldx, K, b, 1, b.dA);
+    add_grad((const uint16_t*)(ws + l.tst_off), l.ts_ld, b.dy, b.lddy, b.N, b, 0, b.dB);
+  }
+  if (prep.n > 0) {
+    prep.counters = counters;
+    prep.n_counters = kDownMaxSlots;
+    backward_prepare_kernel<<<dim3((unsigned)(prep.n_blocks + 1)), dim3(256), 0, st>>>(prep);
+    if ((rc = launch_status()) != QERL_OK) return rc;
+  }
   int tiles = 0;
   for (int i = 0; i < n; ++i) {
     const BackwardMember& b = mem[i];
     if (b.r == 0) continue;
     const BackwardMemberLayout& l = L.mem[i];
-    uint16_t* AT = (uint16_t*)(ws + l.at_off);
     uint16_t* BT = (uint16_t*)(ws + l.bt_off);
-    const int blocks_a = grid_for(b.r * K), blocks_b = grid_for(b.N * b.r);
-    backward_prepare_kernel<<<dim3((unsigned)(blocks_a + blocks_b + 1)), dim3(256), 0, st>>>(
-        b.A, b.r, K, AT, b.B, b.N, BT, blocks_a, blocks_b, counters, kDownMaxSlots);
-    if ((rc = launch_status()) != QERL_OK) return rc;
     // U_i = dY_i B_i as three bf16 terms of (lora_scale / S32) times the product
     GemmArgs d{};
     d.x = b.dy; d.ldx = b.lddy; d.M = M; d.K = b.N; d.k_tiles = ceil_div(b.N, kPackTileK);
@@ -360,19 +475,14 @@ static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
     g.x = g.seg[0].x; g.ldx = g.seg[0].ldx; g.K = rows; g.k_tiles = g.seg[0].k_tiles; g.packed = g.seg[0].packed; g.tensor_scale = g.seg[0].tensor_scale;
     if ((rc = launch_gemm(g, st)) != QERL_OK) return rc;
   }
-  for (int i = 0; i < n; ++i) {
-    const BackwardMember& b = mem[i];
-    if (b.r == 0) continue;
-    const BackwardMemberLayout& l = L.mem[i];
-    // the three-term values carry lora_scale / S32; the gradients want lora_scale: one multiplication by S32
-    const dim3 blk(256);
-    lora_grad_partial_kernel<true><<<dim3((unsigned)ceil_div(K, 128), (unsigned)L.n_chunks), blk, 0, st>>>(
-        (const uint16_t*)(ws + l.tsu_off), l.ts_ld, (int)b.r, x, ldx, M, K, L.tokens_per_chunk, part);
-    lora_grad_reduce_kernel<<<dim3((unsigned)grid_for(K * b.r)), blk, 0, st>>>(part, L.n_chunks, K, (int)b.r, b.tensor_scale, 1, b.dA);
-    lora_grad_partial_kernel<false><<<dim3((unsigned)ceil_div(b.N, 128), (unsigned)L.n_chunks), blk, 0, st>>>(
-        (const uint16_t*)(ws + l.tst_off), l.ts_ld, (int)b.r, b.dy, b.lddy, M, b.N, L.tokens_per_chunk, part);
-    lora_grad_reduce_kernel<<<dim3((unsigned)grid_for(b.N * b.r)), blk, 0, st>>>(part, L.n_chunks, b.N, (int)b.r, b.tensor_scale, 0, b.dB);
+  if (grad.n > 0) {
+    grad.M = M;
+    lora_grad_kernel<<<dim3((unsigned)grad.n_blocks), dim3(256), 0, st>>>(grad);
     if ((rc = launch_status()) != QERL_OK) return rc;
+    if (grad.elems > 0) {
+      lora_grad_reduce_kernel<<<dim3((unsigned)grid_for(ceil_div(grad.elems, 4))), dim3(256), 0, st>>>(grad);
+      rc = launch_status();
+    }
   }
   return rc;
 }

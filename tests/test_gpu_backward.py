@@ -165,3 +165,42 @@ def test_group_backward_equals_oracle(M, K, Ns, rs):
     if rs[i]:
         assert torch.equal(one[1][0][0], single[1]) and torch.equal(one[1][0][1], single[2])
         assert torch.equal(grads[i][0], single[1])
+
+
+@pytest.mark.parametrize("M,N,K,r", [
+    (64, 136, 144, 8),           # one token tile: gradients written without partial sums; column blocks of 8 and 16
+    (65, 264, 272, 40),          # two chunks, one of them of a single token; a rank tile of 8
+    (70, 16392, 64, 24),         # dB in one chunk of two tiles, dA in two chunks
+    (513, 128, 384, 56),         # nine tiles over eight chunks: chunks of two tiles, the last of a single token
+    (1345, 16392, 48, 64),       # as many chunks as the length of a chunk asks for
+])
+def test_gradient_products_at_the_edges_of_their_tiles(M, N, K, r):
+    """dA and dB of rows that lie apart in memory, against a float64 product of the oracle's operands."""
+    print("gradient products", M, N, K, r, flush=True)
+    W = cases.gaussian(N, K, 7100 + M)
+    pt = qerl.nvfp4_prepack_t(*(torch.as_tensor(t).cuda().reshape(-1) if np.ndim(t) == 0 else torch.from_numpy(t).cuda()
+                                for t in oracle.nvfp4_quantize(W)))
+    x = torch.zeros((M, K + 8), dtype=torch.bfloat16, device="cuda")
+    dy = torch.zeros((M, N + 16), dtype=torch.bfloat16, device="cuda")
+    x[:, :K], dy[:, :N] = qs.activations(M, K, 7200 + M).cuda(), qs.activations(M, N, 7300 + M, std=0.5).cuda()
+    x[:, K:], dy[:, N:] = float("nan"), float("nan")      # never read as part of the tensors
+    A, B = (t.cuda() for t in qs.lora_pair(N, K, r, 7400 + M, b_std=0.05))
+    _, dA, dB = qerl.nvfp4_lora_linear_backward(x[:, :K], dy[:, :N], pt, A, B, 2.0)
+    x64, dy64, A64, B64 = x[:, :K].double(), dy[:, :N].double(), A.double(), B.double()
+    _check_f32(dA, (2.0 * (dy64 @ B64).T @ x64).cpu().numpy(), "dA")
+    _check_f32(dB, (2.0 * dy64.T @ (x64 @ A64.T)).cpu().numpy(), "dB")
+
+
+def test_gradient_products_of_rows_far_apart():
+    """Rows of dY so far apart that a token tile does not fit a 32-bit buffer range: the guarded loads."""
+    M, N, K, r, ld = 66, 136, 64, 8, 1 << 24
+    flat = torch.empty(((M - 1) * ld + N,), dtype=torch.bfloat16, device="cuda")
+    far = flat.as_strided((M, N), (ld, 1))
+    far.copy_(qs.activations(M, N, 7500, std=0.5))
+    near = far.contiguous()
+    W = cases.gaussian(N, K, 7501)
+    pt = qerl.nvfp4_prepack_t(*qerl.nvfp4_quantize(torch.from_numpy(W).to(torch.bfloat16).cuda()))
+    x = qs.activations(M, K, 7502).cuda()
+    A, B = (t.cuda() for t in qs.lora_pair(N, K, r, 7503, b_std=0.05))
+    for got, want in zip(qerl.nvfp4_lora_linear_backward(x, far, pt, A, B, 2.0), qerl.nvfp4_lora_linear_backward(x, near, pt, A, B, 2.0)):
+        assert torch.equal(got, want)
