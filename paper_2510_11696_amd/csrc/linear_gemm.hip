@@ -910,11 +910,13 @@ static int launch_lora_down64(const GemmArgs& a0, hipStream_t st) {
   const int n_tiles = a.g_tile0[a.g_n];
   const int tpw = (n_tiles + 1) / 2;
   const int64_t tbs = ceil_div(a.M, 64);
-  // K-parts until the chip is full (twice over for a single adapter, whose parts exchange little): at most 32,
-  // at least 512 columns each, one arrival counter per token block, and the parts' sums must fit the exchange area
+  // K-parts until every CU has a workgroup: at most 32, at least 512 columns each, one arrival counter per token block,
+  // and the parts' sums must fit the exchange area.  A slab of 64 columns takes 0.41 us and every part adds about 0.7 us
+  // to the last workgroup's sums, so filling the chip twice over loses: one adapter of r = 64, 2048 tokens, K = 5120 / 13824 at
+  // 8 parts 13.7 / 21.6 us, at 10 / 16 parts 15.3 / 24.8; 4096 tokens, K = 5120 at 4 parts 17.4, at 8 parts 19.3.
   int64_t P = 1;
   if (a.tpart && a.counters && tbs <= kDownMaxSlots) {
-    P = (tpw == 1 ? 512 : 256) / tbs;
+    P = 256 / tbs;
     const int64_t p_max = ceil_div(a.K, 512);
     P = P < p_max ? P : p_max;
     P = P > kDownMaxPartsWide ? kDownMaxPartsWide : (P < 1 ? 1 : P);
