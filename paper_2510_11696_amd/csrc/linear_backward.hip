@@ -311,21 +311,21 @@ __global__ __launch_bounds__(256) void lora_grad_reduce_kernel(const GradArgs a)
 }
 
 static size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
-static size_t grad_partial_bytes(int64_t M, int64_t C, int64_t r) {
-  const int n = grad_split(M > 0 ? M : 1, C).n_chunks;
-  return n > 1 ? al256((size_t)n * (size_t)(C * r) * sizeof(float)) : 0;
-}
 // Workspace of a backward call over n members that read the same x: the arrival counters of the K-split
 // down-projections, then per member A^T, B^T and the two three-term products, then one area that first holds the
-// down-projections' K-part sums and later the partial sums of all gradient products.
+// down-projections' K-part sums and later the partial sums of the gradient products.  The area holds the widest product in
+// the most chunks there can be (grad_split never takes more than kGradChunksMax, nor more than one per 64 tokens), so that
+// every product fits and the size never falls when M, a width or a rank grows, which the chunk counts themselves do (8 at
+// 512 tokens, 5 at 513): a buffer sized for the largest call serves the smaller ones.  Products that do not fit
+// together take more than one launch.
 struct BackwardMemberLayout { size_t at_off, bt_off, tsu_off, tst_off; int64_t ts_ld; int ext_stages; };
-struct BackwardLayout { size_t ctr_off, part_off, total; BackwardMemberLayout mem[kMaxGroup]; };
+struct BackwardLayout { size_t ctr_off, part_off, part_bytes, total; BackwardMemberLayout mem[kMaxGroup]; };
 static BackwardLayout backward_layout(int64_t M, int64_t K, const int64_t* Ns, const int64_t* rs, int n) {
   BackwardLayout L{};
   const size_t m = (size_t)(M > 0 ? M : 1), k = (size_t)(K > 0 ? K : 1);
   L.ctr_off = 0;                                   // zeroed by every call
   size_t off = al256(kDownMaxSlots * sizeof(uint32_t));
-  size_t part = 0;                                 // partial sums of the gradient products
+  size_t widest = 0;
   bool any = false;
   for (int i = 0; i < n; ++i) {
     const size_t nn = (size_t)(Ns[i] > 0 ? Ns[i] : 1), rr = (size_t)(rs[i] > 0 ? rs[i] : 0);
@@ -336,14 +336,17 @@ static BackwardLayout backward_layout(int64_t M, int64_t K, const int64_t* Ns, c
     b.bt_off = off;  off += al256(nn * rr * 2);
     b.tsu_off = off; off += al256(m * (size_t)b.ts_ld * 2);
     b.tst_off = off; off += al256(m * (size_t)b.ts_ld * 2);
-    if (rr) {
-      any = true;
-      part += grad_partial_bytes(M, (int64_t)k, (int64_t)rr) + grad_partial_bytes(M, (int64_t)nn, (int64_t)rr);
-    }
+    if (rr) { any = true; widest = widest > nn ? widest : nn; }
   }
   L.part_off = off;
-  if (any && part < kDownExchangeBytes) part = kDownExchangeBytes;
-  L.total = L.part_off + part;
+  if (any) {
+    widest = widest > k ? widest : k;
+    size_t chunks = (m + kGradTokens - 1) / kGradTokens;
+    chunks = chunks < (size_t)kGradChunksMax ? chunks : (size_t)kGradChunksMax;
+    L.part_bytes = al256(chunks * widest * kGradRanks * sizeof(float));
+    if (L.part_bytes < kDownExchangeBytes) L.part_bytes = kDownExchangeBytes;
+  }
+  L.total = L.part_off + L.part_bytes;
   return L;
 }
 static int grid_for(int64_t items) {
@@ -387,7 +390,8 @@ static int backward_validate(const void* x, int64_t M, int64_t K, int64_t ldx, c
 
 // A call's launches: one that transposes all adapters, per member a down-projection of its own dY, the
 // down-projections of x (one launch over all adapters), dX -- ONE GEMM whose contraction runs over the members' rows one
-// after the other, so that dX is summed in fp32 and rounded once -- and one or two for the gradient products of all members.
+// after the other, so that dX is summed in fp32 and rounded once -- and one or two for the gradient products of all
+// members, or as often as their partial sums fill the area.
 static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const BackwardMember* mem, int n, uint16_t* dx, int64_t lddx,
                         void* workspace, size_t workspace_bytes, hipStream_t st) {
   int64_t Ns[kMaxGroup], rs[kMaxGroup];
@@ -402,19 +406,6 @@ static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
   down.x = x; down.ldx = ldx; down.M = M; down.K = K; down.k_tiles = ceil_div(K, kPackTileK);
   down.tpart = (uint32_t*)part; down.counters = counters;
   PrepareArgs prep{};
-  GradArgs grad{};
-  float* grad_part = part;   // the down-projections are done with the area when the gradient products start
-  auto add_grad = [&](const uint16_t* P, int64_t p_ld, const uint16_t* Q, int64_t q_ld, int64_t C, const BackwardMember& b, int rank_major, float* out) {
-    const GradSplit sp = grad_split(M, C);
-    const int cols = (int)ceil_div(C, kGradCols);
-    grad.job[grad.n++] = GradJob{P, p_ld, Q, q_ld, C, (int)b.r, rank_major, b.tensor_scale, out, sp.n_chunks, sp.tokens_per_chunk,
-                                 cols, grad.n_blocks, grad_part, grad.elems};
-    grad.n_blocks += cols * sp.n_chunks;
-    if (sp.n_chunks > 1) {
-      grad.elems += C * b.r;
-      grad_part += grad_partial_bytes(M, C, b.r) / sizeof(float);
-    }
-  };
   for (int i = 0; i < n; ++i) {
     const BackwardMember& b = mem[i];
     if (b.r == 0) continue;
@@ -423,8 +414,6 @@ static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
     prep.n_blocks += (int)(ceil_div(b.r, 64) * ceil_div(K, 64));
     prep.job[prep.n++] = TransposeJob{b.B, (uint16_t*)(ws + l.bt_off), b.N, b.r, prep.n_blocks};
     prep.n_blocks += (int)(ceil_div(b.N, 64) * ceil_div(b.r, 64));
-    add_grad((const uint16_t*)(ws + l.tsu_off), l.ts_ld, x, ldx, K, b, 1, b.dA);
-    add_grad((const uint16_t*)(ws + l.tst_off), l.ts_ld, b.dy, b.lddy, b.N, b, 0, b.dB);
   }
   if (prep.n > 0) {
     prep.counters = counters;
@@ -475,15 +464,39 @@ static int backward_run(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
     g.x = g.seg[0].x; g.ldx = g.seg[0].ldx; g.K = rows; g.k_tiles = g.seg[0].k_tiles; g.packed = g.seg[0].packed; g.tensor_scale = g.seg[0].tensor_scale;
     if ((rc = launch_gemm(g, st)) != QERL_OK) return rc;
   }
-  if (grad.n > 0) {
-    grad.M = M;
+  // The gradient products; the down-projections are done with the area, and a launch's sums with it before the next one writes.
+  GradArgs grad{};
+  grad.M = M;
+  size_t used = 0;
+  auto launch_grads = [&]() -> int {
     lora_grad_kernel<<<dim3((unsigned)grad.n_blocks), dim3(256), 0, st>>>(grad);
-    if ((rc = launch_status()) != QERL_OK) return rc;
-    if (grad.elems > 0) {
+    int status = launch_status();
+    if (status == QERL_OK && grad.elems > 0) {
       lora_grad_reduce_kernel<<<dim3((unsigned)grid_for(ceil_div(grad.elems, 4))), dim3(256), 0, st>>>(grad);
-      rc = launch_status();
+      status = launch_status();
     }
+    grad.n = grad.n_blocks = 0;
+    grad.elems = 0;
+    used = 0;
+    return status;
+  };
+  for (int i = 0; i < 2 * n; ++i) {
+    const BackwardMember& b = mem[i / 2];
+    if (b.r == 0) continue;
+    const BackwardMemberLayout& l = L.mem[i / 2];
+    const bool da = i % 2 == 0;        // dA = U^T x as [r, K], then dB = dY^T t as [N, r]
+    const int64_t C = da ? K : b.N;
+    const GradSplit sp = grad_split(M, C);
+    const size_t bytes = sp.n_chunks > 1 ? (size_t)sp.n_chunks * (size_t)(C * b.r) * sizeof(float) : 0;   // a multiple of 256
+    if (used + bytes > L.part_bytes && (rc = launch_grads()) != QERL_OK) return rc;
+    const int cols = (int)ceil_div(C, kGradCols);
+    grad.job[grad.n++] = GradJob{(const uint16_t*)(ws + (da ? l.tsu_off : l.tst_off)), l.ts_ld, da ? x : b.dy, da ? ldx : b.lddy, C, (int)b.r, da,
+                                 b.tensor_scale, da ? b.dA : b.dB, sp.n_chunks, sp.tokens_per_chunk, cols, grad.n_blocks, part + used / sizeof(float), grad.elems};
+    grad.n_blocks += cols * sp.n_chunks;
+    if (bytes > 0) grad.elems += C * b.r;
+    used += bytes;
   }
+  if (grad.n > 0) rc = launch_grads();
   return rc;
 }
 

@@ -147,6 +147,36 @@ def test_workspace_size_is_monotone_enough(lib):
     assert f(8, 3584, 18944, 32) < 64 << 20
 
 
+def _backward_group_bytes(lib, M, K, members):
+    from paper_2510_11696_amd.binding import _BackwardDesc
+    d = (_BackwardDesc * len(members))()
+    for i, (N, r) in enumerate(members):
+        d[i].N, d[i].r = N, r
+    return lib.nvfp4_lora_linear_backward_group_workspace_bytes(M, K, ctypes.cast(d, ctypes.c_void_p), len(members))
+
+
+def test_backward_workspace_of_a_larger_call_serves_every_smaller_one(lib):
+    """Neither size function of the backward pass falls when the token count (every one up to 1300, then around the
+    64-token tiles), a width or a rank grows: a buffer sized for the largest call is accepted by the smaller ones."""
+    tokens = sorted(set(range(1, 1300)) | {64 * t + d for t in range(20, 140) for d in (-1, 0, 1)})
+    groups = [(5120, [(5120, 64), (1024, 64), (1024, 64)]), (5120, [(13824, 64)] * 2), (3584, [(3584, 64), (512, 64), (512, 64)]),
+              (3584, [(18944, 32)] * 2), (13824, [(5120, 64)]), (2048, [(2048, 8), (256, 0)])]
+    for K, members in groups:
+        sizes = [_backward_group_bytes(lib, M, K, members) for M in tokens]
+        falls = [(tokens[i], tokens[i + 1]) for i in range(len(sizes) - 1) if sizes[i + 1] < sizes[i]]
+        assert not falls, (K, members, falls[:4])
+    single = lib.nvfp4_lora_linear_backward_workspace_bytes
+    for N, K, r in ((5120, 13824, 64), (18944, 3584, 32), (1024, 5120, 64)):
+        sizes = [single(M, N, K, r) for M in tokens]
+        assert sizes == sorted(sizes), (N, K, r)
+    for M in (1, 64, 65, 500, 640, 641, 2048, 4096):
+        for widths in (range(128, 20000, 128), range(8, 20000, 1000), (16376, 16384, 16392)):
+            assert (s := [single(M, N, 5120, 64) for N in widths]) == sorted(s), M
+            assert (s := [single(M, 5120, 2 * K, 64) for K in widths]) == sorted(s), M
+        assert (s := [single(M, 13824, 5120, r) for r in range(0, 65, 8)]) == sorted(s), M
+        assert (s := [_backward_group_bytes(lib, M, 5120, [(5120, 64), (1024, 64), (13824, 64)][:n]) for n in (1, 2, 3)]) == sorted(s), M
+
+
 def test_sigma_schedules_match_the_oracle():
     from oracle import nvfp4_oracle as oracle
     for kind in oracle.SCHEDULE_KINDS:

@@ -1,9 +1,12 @@
 """GPU parity of the backward pass (dX through the frozen NVFP4 weights, dA, dB) against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2510_11696_amd as qerl
+from paper_2510_11696_amd.binding import _BackwardDesc
 import qerl_synth as qs
 from oracle import nvfp4_oracle as oracle
 from tests import cases
@@ -204,3 +207,32 @@ def test_gradient_products_of_rows_far_apart():
     A, B = (t.cuda() for t in qs.lora_pair(N, K, r, 7503, b_std=0.05))
     for got, want in zip(qerl.nvfp4_lora_linear_backward(x, far, pt, A, B, 2.0), qerl.nvfp4_lora_linear_backward(x, near, pt, A, B, 2.0)):
         assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("M,K,Ns,rs", [
+    (512, 2048, (2048,) * 4, (64,) * 4),             # eight products of 4 MB of partial sums in an area of 16 MB
+    (1100, 4096, (4096, 264, 4096, 2048), (64, 8, 64, 64)),   # narrow products between wide ones; launches of unequal length
+])
+def test_gradient_products_that_do_not_fit_the_area_together(M, K, Ns, rs):
+    """The partial sums of a group's products fill the workspace area more than once: same gradients, nothing behind the
+    stated size written."""
+    print("gradient products in several launches", M, K, Ns, rs, flush=True)
+    x = qs.activations(M, K, 7600).cuda()
+    dys = [qs.activations(M, N, 7610 + i, std=0.5).cuda() for i, N in enumerate(Ns)]
+    weights = [qerl.nvfp4_prepack_t(*qerl.nvfp4_quantize(torch.from_numpy(cases.gaussian(N, K, 7620 + i)).to(torch.bfloat16).cuda()))
+               for i, N in enumerate(Ns)]
+    As, Bs = zip(*([t.cuda() for t in qs.lora_pair(N, K, r, 7630 + i, b_std=0.05)] for i, (N, r) in enumerate(zip(Ns, rs))))
+    descs = (_BackwardDesc * len(Ns))()
+    for d, N, r in zip(descs, Ns, rs):
+        d.N, d.r = N, r
+    need = qerl.load_library().nvfp4_lora_linear_backward_group_workspace_bytes(M, K, ctypes.cast(descs, ctypes.c_void_p), len(Ns))
+    ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    start = -ws.data_ptr() % 256
+    _, grads = qerl.nvfp4_lora_linear_backward_group(x, dys, weights, As, Bs, [2.0] * len(Ns), workspace=ws[start:start + need])
+    assert bool((ws[start + need:] == 0xA5).all())
+    for i in range(len(Ns)):
+        dy64, x64 = dys[i].double(), x.double()
+        _check_f32(grads[i][0], (2.0 * (dy64 @ Bs[i].double()).T @ x64).cpu().numpy(), ("dA", i))
+        _check_f32(grads[i][1], (2.0 * dy64.T @ (x64 @ As[i].double().T)).cpu().numpy(), ("dB", i))
+        alone = qerl.nvfp4_lora_linear_backward(x, dys[i], weights[i], As[i], Bs[i], 2.0)
+        assert torch.equal(grads[i][0], alone[1]), i
