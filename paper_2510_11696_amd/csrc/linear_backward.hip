@@ -115,12 +115,12 @@ constexpr int kGradChunksMax = 8;    // token chunks (workgroups along M)
 constexpr int kGradTokens = 64;      // tokens per LDS tile
 constexpr int kGradGroups = kGradTokens / 8, kGradCols = 128, kGradPCols = 3 * kGradRanks;
 constexpr int64_t kGradWorkgroups = 128;
-constexpr int64_t kGradChunkTiles = 10;   // most tiles of a chunk (up to kGradChunksMax of them): the fp32 chains stay at or below 640 tokens
+constexpr int64_t kGradOneChunkTiles = 8;   // a product of more tiles takes at least two chunks: its error then stays below that of eight chunks in plain chains
 struct GradSplit { int n_chunks; int64_t tokens_per_chunk; };
 static GradSplit grad_split(int64_t M, int64_t C) {
   const int64_t tiles = ceil_div(M, kGradTokens);
   int64_t chunks = ceil_div(kGradWorkgroups, ceil_div(C, kGradCols));
-  const int64_t by_tiles = ceil_div(tiles, kGradChunkTiles);
+  const int64_t by_tiles = tiles > kGradOneChunkTiles ? 2 : 1;
   chunks = chunks < by_tiles ? by_tiles : chunks;
   chunks = chunks > kGradChunksMax ? kGradChunksMax : chunks;
   chunks = chunks > tiles ? tiles : chunks;
@@ -147,11 +147,15 @@ __device__ __forceinline__ void lora_grad_block(const GradJob& jb, int64_t c0, i
   const int n32 = lane & 31, kg = lane >> 5;
   const int r = jb.r;
   const int64_t C = jb.C;
-  f32x16 hi[2], lo[2];   // the first term's sums apart from the smaller two's: a third of the roundings at full magnitude
+  // The leading term is summed tile by tile (four MFMAs) and the tiles' sums are added up; the small terms, at most a 256th
+  // of its size, run through.  That keeps the fp32 chains short where a chunk is long.  Relative error of a product against
+  // float64, eight chunks of one chain each / one chain for the leading term in the chunks of grad_split / these two
+  // levels: 640 tokens, C = 18944: 7.4e-8 / 1.41e-7 / 6.8e-8; 2048 tokens, C = 13824: 1.02e-7 / 1.31e-7 / 9.2e-8.
+  f32x16 sum[2], small[2];
 #pragma unroll
   for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) hi[jt][i] = lo[jt][i] = 0.f;
+    for (int i = 0; i < 16; ++i) sum[jt][i] = small[jt][i] = 0.f;
   // The tile after the current one is requested before the current one is multiplied.  Buffer loads relative to the
   // tile: tokens past the chunk's end lie behind the descriptor's range and read as zero, without a branch per load.
   // Columns of Q past C read whatever follows inside the range (their sums are dropped), columns of P past 3 r are not fetched.
@@ -227,6 +231,11 @@ __device__ __forceinline__ void lora_grad_block(const GradJob& jb, int64_t c0, i
       if (p_slot[i] >= 0) turn(preg[i], sP + p_slot[i]);
     __syncthreads();
     request(m0 + kGradTokens);         // past the chunk's end every guard fails: zeros, no access
+    f32x16 tile[2];
+#pragma unroll
+    for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) tile[jt][i] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < kGradTokens / 16; ++ks) {
       const int g = 2 * ks + kg;       // this lane's eight tokens of the step
@@ -240,19 +249,23 @@ __device__ __forceinline__ void lora_grad_block(const GradJob& jb, int64_t c0, i
             u32x4 b = sP[g * kGradPCols + t * r + (j < r ? j : 0)];
             if (j >= r) b = u32x4{0u, 0u, 0u, 0u};
             const bf16x8 bf = __builtin_bit_cast(bf16x8, b);
-            f32x16& acc = t == 0 ? hi[jt] : lo[jt];
+            f32x16& acc = t == 0 ? tile[jt] : small[jt];
             if constexpr (RANK_MAJOR) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf, af, acc, 0, 0, 0);
             else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
           }
         }
       }
     }
+#pragma unroll
+    for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum[jt][i] += tile[jt][i];
   }
 #pragma unroll
   for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const float v = (hi[jt][q] + lo[jt][q]) * mult;
+      const float v = (sum[jt][q] + small[jt][q]) * mult;
       const int inner = 8 * (q >> 2) + 4 * kg + (q & 3);     // MFMA result: row inner, column n32
       const int j = jt * 32 + (RANK_MAJOR ? inner : n32);
       const int64_t c = c0 + wave * 32 + (RANK_MAJOR ? n32 : inner);
@@ -260,7 +273,8 @@ __device__ __forceinline__ void lora_grad_block(const GradJob& jb, int64_t c0, i
     }
 }
 
-__global__ __launch_bounds__(256) void lora_grad_kernel(const GradArgs a) {
+// two workgroups per CU: without the bound the registers of lora_grad_block's sums leave one
+__global__ __launch_bounds__(256, 2) void lora_grad_kernel(const GradArgs a) {
   __shared__ u32x4 sQ[kGradGroups * kGradCols];
   __shared__ u32x4 sP[kGradGroups * kGradPCols];
   int ji = 0;

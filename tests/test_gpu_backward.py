@@ -236,3 +236,36 @@ def test_gradient_products_that_do_not_fit_the_area_together(M, K, Ns, rs):
         _check_f32(grads[i][1], (2.0 * dy64.T @ (x64 @ As[i].double().T)).cpu().numpy(), ("dB", i))
         alone = qerl.nvfp4_lora_linear_backward(x, dys[i], weights[i], As[i], Bs[i], 2.0)
         assert torch.equal(grads[i][0], alone[1]), i
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (384, 18944, 64), (640, 18944, 64), (640, 64, 18944),   # products so wide that few token chunks fill the chip
+    (777, 3584, 64), (1300, 64, 20480), (2048, 13824, 64), (2048, 64, 5120),
+])
+def test_gradient_products_are_as_exact_as_eight_short_chains(M, N, K):
+    """Adapters of unit rows make t and U exact, so the gradients' distance from float64 is that of their sums over
+    the tokens: no larger than that of at most eight chunks of one fp32 chain of 16-token steps each.  The matrix
+    instruction's own sum of sixteen products is not exact as the chain's here is: where both orders are the same (384 tokens) it
+    costs 8 % (6.5e-8 against 6.0e-8); 5 % more for the statistics of the roundings."""
+    print("gradient product sums", M, N, K, flush=True)
+    r, top = 64, 2688.0 * 2.0 ** -14                       # the weights' largest magnitude: a tensor scale of 2^-14
+    W = torch.from_numpy(cases.gaussian(N, K, 7700 + M)).clamp(-top, top)
+    W[0, 0] = top
+    pt = qerl.nvfp4_prepack_t(*qerl.nvfp4_quantize(W.to(torch.bfloat16).cuda()))
+    assert float(pt.tensor_scale) == 2.0 ** -14
+    x, dy = qs.activations(M, K, 7710).cuda(), qs.activations(M, N, 7711, std=0.5).cuda()
+    A, B = torch.eye(r, K, dtype=torch.bfloat16, device="cuda"), torch.eye(N, r, dtype=torch.bfloat16, device="cuda")
+    _, dA, dB = qerl.nvfp4_lora_linear_backward(x, dy, pt, A, B, 1.0)
+    chunks = min(-(-M // 64), 8)
+    tokens = -(-M // chunks)
+    for got, P, Q in ((dA.T, dy[:, :r].double(), x.double()), (dB, x[:, :r].double(), dy.double())):
+        total = torch.zeros((Q.shape[1], r), device="cuda")
+        for lo in range(0, M, tokens):
+            acc = torch.zeros_like(total)
+            for m in range(lo, min(lo + tokens, M), 16):
+                e = min(m + 16, lo + tokens, M)
+                acc = (acc.double() + Q[m:e].T.contiguous() @ P[m:e]).float()
+            total = total + acc
+        want = Q.T.contiguous() @ P
+        err, bound = (float((t.double() - want).norm() / want.norm()) for t in (got, total))
+        assert err <= 1.13 * bound, (M, N, K, err, bound)
