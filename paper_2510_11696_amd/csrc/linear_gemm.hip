@@ -467,12 +467,15 @@ __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, cons
       base[kXChunks + row * 8 + (lchunk ^ ((row >> 1) & 7))] = sl.w[i];
     }
   };
-  f32x16 acc[TPW];
+  // With one tile per wave the parts are up to twice as long (down64_parts): every second slab is summed in a chain of its own,
+  // so that the fp32 chains stay as short, at no cost (0.4 %; sums slab by slab, added up: 3 %).
+  constexpr int kChains = TPW == 1 ? 2 : 1;
+  f32x16 acc[TPW], odd[TPW];
 #pragma unroll
   for (int i = 0; i < TPW; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
-  auto compute = [&](int buf) {
+    for (int e = 0; e < 16; ++e) acc[i][e] = odd[i][e] = 0.f;
+  auto compute = [&](int buf, f32x16 (&sum)[TPW]) {
     const u32x4* base = lds64 + buf * (kXChunks + kAChunks);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, cons
       for (int i = 0; i < TPW; ++i) {
         const int arow = (t_first + 2 * i) * 32 + n32;
         const bf16x8 af = __builtin_bit_cast(bf16x8, base[kXChunks + arow * 8 + ((2 * j + kg) ^ ((arow >> 1) & 7))]);
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, af, acc[i], 0, 0, 0);
+        sum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf, af, sum[i], 0, 0, 0);
       }
     }
   };
@@ -502,8 +505,12 @@ __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, cons
         load(ring[u], s0 + u + D);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        compute(buf);
+        compute(buf, kChains == 2 && (u & 1) ? odd : acc);
       }
+    }
+    if constexpr (kChains == 2) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[0][e] += odd[0][e];
     }
   }
 
@@ -899,6 +906,28 @@ static int launch_down64_t(const GemmArgs& a, int n_tiles, int P, dim3 grid, hip
   return launch_status();
 }
 
+// K-parts of the 64-token kernel: at most 32, at least 512 columns each.  Two and more tiles per wave: until every CU has a
+// workgroup.  One tile per wave: the count that is estimated fastest among those whose parts are no longer than twice what
+// they are when the chip is filled twice over (the kernel's two chains then lose no more than one chain did there).  In
+// units of a 64-column slab (0.41 us of a workgroup that has its CU to itself): 1.6 slabs' time per slab where two share a CU,
+// 1.7 per part for the last workgroup's sums, 6 for the exchange as such.  Measured over K = 1024..27648, r = 16 and 64, the count
+// taken / the chip filled twice over / once, in us: K = 13824: 512 tokens 16.1 (14 parts) / 19.3 / 19.3, 2048 tokens 20.4 (8) / 24.4 /
+// 20.4; K = 18944, 640 tokens 19.3 (16) / 25.8 / 23.4, 4096 tokens 42.3 (8) / 42.3 / 43.8; K = 5120: 5504 tokens 19.3 (5) / 19.3 / 22.1,
+// 8256 tokens 24.5 (3) / 24.5 / 31.7.
+static int64_t down64_parts(int64_t tbs, int64_t K, int tpw) {
+  const int64_t p_max = ceil_div(K, 512) < kDownMaxPartsWide ? ceil_div(K, 512) : kDownMaxPartsWide;
+  auto filled = [&](int64_t wgs) { const int64_t p = wgs / tbs < p_max ? wgs / tbs : p_max; return p < 1 ? (int64_t)1 : p; };
+  if (tpw > 1) return filled(256);
+  const int64_t slabs = ceil_div(K, 64), p_most = filled(512), longest = 2 * ceil_div(slabs, p_most) + 2;
+  int64_t best = p_most;
+  double t_best = 0;
+  for (int64_t p = p_most; p >= 1 && ceil_div(slabs, p) <= longest; --p) {
+    const double t = (double)ceil_div(slabs, p) * (tbs * p <= 256 ? 1.0 : 1.6) + (p > 1 ? 1.7 * (double)p + 6.0 : 0.0);
+    if (p == p_most || t < t_best) { best = p; t_best = t; }
+  }
+  return best;
+}
+
 static int launch_lora_down64(const GemmArgs& a0, hipStream_t st) {
   GemmArgs a = a0;
   if (a.g_n == 0) {   // a single adapter, put into the group form
@@ -910,16 +939,9 @@ static int launch_lora_down64(const GemmArgs& a0, hipStream_t st) {
   const int n_tiles = a.g_tile0[a.g_n];
   const int tpw = (n_tiles + 1) / 2;
   const int64_t tbs = ceil_div(a.M, 64);
-  // K-parts until every CU has a workgroup: at most 32, at least 512 columns each, one arrival counter per token block,
-  // and the parts' sums must fit the exchange area.  A slab of 64 columns takes 0.41 us and every part adds about 0.7 us
-  // to the last workgroup's sums, so filling the chip twice over loses: one adapter of r = 64, 2048 tokens, K = 5120 / 13824 at
-  // 8 parts 13.7 / 21.6 us, at 10 / 16 parts 15.3 / 24.8; 4096 tokens, K = 5120 at 4 parts 17.4, at 8 parts 19.3.
   int64_t P = 1;
   if (a.tpart && a.counters && tbs <= kDownMaxSlots) {
-    P = 256 / tbs;
-    const int64_t p_max = ceil_div(a.K, 512);
-    P = P < p_max ? P : p_max;
-    P = P > kDownMaxPartsWide ? kDownMaxPartsWide : (P < 1 ? 1 : P);
+    P = down64_parts(tbs, a.K, tpw);
     if (g_down64_parts > 0) P = g_down64_parts;
     while (P > 1 && (size_t)(tbs * P) * 4 * tpw * 16 * 64 * sizeof(float) > kDownExchangeBytes) --P;
   }

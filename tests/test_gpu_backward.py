@@ -244,9 +244,9 @@ def test_gradient_products_that_do_not_fit_the_area_together(M, K, Ns, rs):
 ])
 def test_gradient_products_are_as_exact_as_eight_short_chains(M, N, K):
     """Adapters of unit rows make t and U exact, so the gradients' distance from float64 is that of their sums over
-    the tokens: no larger than that of at most eight chunks of one fp32 chain of 16-token steps each.  The matrix
-    instruction's own sum of sixteen products is not exact as the chain's here is: where both orders are the same (384 tokens) it
-    costs 8 % (6.5e-8 against 6.0e-8); 5 % more for the statistics of the roundings."""
+    the tokens: no larger than that of at most eight chunks of one fp32 chain each, up to the statistics of the roundings
+    (5 %; 4096 errors and more).  The chain rounds every eight products: in such steps it reproduces the error of the
+    32 x 32 x 16 matrix instruction where the order of the sums is the same (1.86e-7 against 1.87e-7, 1.40e-7 against 1.40e-7)."""
     print("gradient product sums", M, N, K, flush=True)
     r, top = 64, 2688.0 * 2.0 ** -14                       # the weights' largest magnitude: a tensor scale of 2^-14
     W = torch.from_numpy(cases.gaussian(N, K, 7700 + M)).clamp(-top, top)
@@ -262,10 +262,39 @@ def test_gradient_products_are_as_exact_as_eight_short_chains(M, N, K):
         total = torch.zeros((Q.shape[1], r), device="cuda")
         for lo in range(0, M, tokens):
             acc = torch.zeros_like(total)
-            for m in range(lo, min(lo + tokens, M), 16):
-                e = min(m + 16, lo + tokens, M)
+            for m in range(lo, min(lo + tokens, M), 8):
+                e = min(m + 8, lo + tokens, M)
                 acc = (acc.double() + Q[m:e].T.contiguous() @ P[m:e]).float()
             total = total + acc
         want = Q.T.contiguous() @ P
         err, bound = (float((t.double() - want).norm() / want.norm()) for t in (got, total))
-        assert err <= 1.13 * bound, (M, N, K, err, bound)
+        print(err / bound)
+        assert err <= 1.05 * bound, (M, N, K, err, bound)
+
+
+@pytest.mark.parametrize("M,K", [(300, 3584), (777, 13824), (1024, 18944), (1500, 27648), (2048, 13824), (3300, 5120), (4096, 18944), (8256, 1024)])
+def test_down_projection_of_one_adapter_is_as_exact_as_many_short_chains(M, K):
+    """t = x A^T, read back through one-hot rows of dY: its distance from float64 is no larger than that of as many
+    parts of K as fill the chip twice over, each one fp32 chain of 8-column steps; allowance as above."""
+    print("down-projection sums", M, K, flush=True)
+    r, N, top = 64, 256, 2688.0 * 2.0 ** -14
+    W = torch.from_numpy(cases.gaussian(N, K, 7800 + M)).clamp(-top, top)
+    W[0, 0] = top
+    pt = qerl.nvfp4_prepack_t(*qerl.nvfp4_quantize(W.to(torch.bfloat16).cuda()))
+    assert float(pt.tensor_scale) == 2.0 ** -14
+    x = qs.activations(M, K, 7810).cuda()
+    A, B = (t.cuda() for t in qs.lora_pair(N, K, r, 7811))
+    _, _, dB = qerl.nvfp4_lora_linear_backward(x, torch.eye(M, N, dtype=torch.bfloat16, device="cuda"), pt, A, B, 1.0)
+    parts = max(1, min(512 // -(-M // 64), -(-K // 512), 32))
+    cols = -(-(-(-K // 64)) // parts) * 64
+    x64, A64 = x[:N].double(), A.double()
+    total = torch.zeros((N, r), device="cuda")
+    for lo in range(0, K, cols):
+        acc = torch.zeros_like(total)
+        for k in range(lo, min(lo + cols, K), 8):
+            acc = (acc.double() + x64[:, k:k + 8] @ A64[:, k:k + 8].T.contiguous()).float()
+        total = total + acc
+    want = x64 @ A64.T.contiguous()
+    err, bound = (float((t.double() - want).norm() / want.norm()) for t in (dB, total))
+    print(err / bound)
+    assert err <= 1.05 * bound, (M, K, err, bound)
