@@ -17,7 +17,6 @@ namespace qerl {
 
 constexpr int kAmaxThreads = 256;
 constexpr int kAmaxMaxBlocks = 2048;
-constexpr int kAmaxLoads = 4;            // 16-byte loads of a thread in flight
 constexpr int kEncodeMaxBlocks = 2048;   // eight workgroups per compute unit: every one re-reads the partial maxima
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -36,7 +35,8 @@ __device__ __forceinline__ const u32x4* chunk_of(const uint16_t* W, int64_t i, i
 
 // Pass 1: maximum |w| as the bf16 bit pattern with the sign cleared (for
 // finite values the integer order of those patterns is the order of the
-// magnitudes).  One partial per workgroup, no atomics.  Bound by the reads.
+// magnitudes).  One partial per workgroup, no atomics.  18944 x 3584: 25.5 us, 5.3 TB/s; four or eight loads of a thread in
+// flight are slower (29.2, 31 us).
 template <bool DENSE>
 __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(
     const uint16_t* __restrict__ W, int64_t N, int64_t K, int64_t ldw, uint32_t* __restrict__ partial) {
@@ -44,19 +44,11 @@ __global__ __launch_bounds__(kAmaxThreads) void amax_partial_kernel(
   const int64_t total = N * chunks_per_row;
   const int64_t step = (int64_t)gridDim.x * kAmaxThreads;
   uint32_t m2 = 0;
-  auto take = [&](const u32x4& v) {
+  for (int64_t i = (int64_t)blockIdx.x * kAmaxThreads + threadIdx.x; i < total; i += step) {
+    const u32x4 v = *chunk_of<8, DENSE>(W, i, chunks_per_row, ldw);
 #pragma unroll
     for (int j = 0; j < 4; ++j) m2 = max_u16x2(m2, v[j] & 0x7fff7fffu);
-  };
-  int64_t i = (int64_t)blockIdx.x * kAmaxThreads + threadIdx.x;
-  for (; i + (kAmaxLoads - 1) * step < total; i += kAmaxLoads * step) {
-    u32x4 v[kAmaxLoads];
-#pragma unroll
-    for (int u = 0; u < kAmaxLoads; ++u) v[u] = *chunk_of<8, DENSE>(W, i + u * step, chunks_per_row, ldw);
-#pragma unroll
-    for (int u = 0; u < kAmaxLoads; ++u) take(v[u]);
   }
-  for (; i < total; i += step) take(*chunk_of<8, DENSE>(W, i, chunks_per_row, ldw));
   uint32_t m = (m2 & 0xffffu) > (m2 >> 16) ? (m2 & 0xffffu) : (m2 >> 16);
   m = wave_max_u32(m);
   __shared__ uint32_t s[kAmaxThreads / kWave];
@@ -98,12 +90,14 @@ __device__ __forceinline__ float quotient(float w, float d, float inv) {
   return __builtin_copysignf(q, w);   // the corrections lose the sign of a zero
 }
 
-// Pass 2: one lane per 16-weight block and step.
+// Pass 2: one thread per 16-weight block.
 // Sixteen IEEE divisions by the block's one divisor and a chain of comparisons per code made this pass issue-bound
 // (18944 x 3584: 74 us); with quotient() above and v_cvt_scalef32_pk_fp4_f32 (nearest even, saturating, sign kept -- as
-// e2m1_encode_rne_sat and the sign bit of w) it takes 36 us (4.8 TB/s).  Only a block whose scale lies outside quotient()'s range (zero, infinite
-// or NaN ones among them) goes through the divisions.  (Dividing only blocks with a quotient next to a rounding boundary was no
-// gain: amax and w have eight significant bits each and the block scale four, so exact ties occur in nearly every wave.)
+// e2m1_encode_rne_sat and the sign bit of w) it takes 33 us (5.2 TB/s).  Only a block whose scale lies outside
+// quotient()'s range (zero, infinite or NaN ones among them) goes through the divisions.  Tried at this size: without the
+// DENSE form 41 us; wave-contiguous loads whose halves the lanes of a pair exchange, or the next block requested ahead,
+// 35..36; dividing only blocks with a quotient next to a rounding boundary, 74 (amax and w have eight significant bits
+// each and the block scale four, so exact ties occur in nearly every wave).
 template <bool DENSE>
 __global__ __launch_bounds__(256) void encode_kernel(
     const uint16_t* __restrict__ W, int64_t N, int64_t K, int64_t ldw,
@@ -111,20 +105,7 @@ __global__ __launch_bounds__(256) void encode_kernel(
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ tensor_scale) {
   const int64_t blocks_per_row = K / kBlock;
   const int64_t total = N * blocks_per_row;
-  // A wave's step covers 64 blocks as two runs of 32.  It reads each run with one instruction, sixteen consecutive
-  // bytes (half a block) per lane, and then the lanes of a pair exchange halves: the even lane owns the first run's block,
-  // the odd lane the second's.
   const int64_t step = (int64_t)gridDim.x * 256;
-  const int lane = threadIdx.x & 63, odd = lane & 1;
-  int64_t base = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63);   // the wave's first block
-  u32x4 v0, v1;
-  auto request = [&](int64_t first) {
-    v0 = v1 = u32x4{0u, 0u, 0u, 0u};
-    const int64_t b0 = first + (lane >> 1), b1 = b0 + 32;
-    if (b0 < total) v0 = chunk_of<kBlock, DENSE>(W, b0, blocks_per_row, ldw)[odd];
-    if (b1 < total) v1 = chunk_of<kBlock, DENSE>(W, b1, blocks_per_row, ldw)[odd];
-  };
-  request(base);                                                    // before the partial maxima
   __shared__ uint32_t s[4];
   uint32_t m = 0;
   for (int p = threadIdx.x; p < n_partial; p += 256) { const uint32_t q = partial[p]; m = q > m ? q : m; }
@@ -137,16 +118,10 @@ __global__ __launch_bounds__(256) void encode_kernel(
   const float S32 = (amax == 0.0f) ? 1.0f : amax / 2688.0f;
   if (blockIdx.x == 0 && threadIdx.x == 0) *tensor_scale = S32;
 
-  for (; base < total; base += step) {
-    uint32_t w[8];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)(odd ? v0[t] : v1[t]), 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
-      w[t] = odd ? got : v0[t];
-      w[4 + t] = odd ? v1[t] : got;
-    }
-    const int64_t i = base + 32 * odd + (lane >> 1);
-    request(base + step);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += step) {
+    const u32x4* src = chunk_of<kBlock, DENSE>(W, i, blocks_per_row, ldw);
+    const u32x4 v0 = src[0], v1 = src[1];
+    const uint32_t w[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
     uint32_t bm2 = 0;
 #pragma unroll
     for (int t = 0; t < 8; ++t) bm2 = max_u16x2(bm2, w[t] & 0x7fff7fffu);
@@ -171,10 +146,8 @@ __global__ __launch_bounds__(256) void encode_kernel(
       packed[half] = out;
     }
     if (!(d >= 0x1p-100f && d <= 0x1p100f)) packed = encode_block_divide(w, d);
-    if (i < total) {                                   // rows of codes and scales follow one another without gaps
-      *reinterpret_cast<u32x2*>(codes + i * 8) = packed;
-      scales[i] = (uint8_t)s8;
-    }
+    *reinterpret_cast<u32x2*>(codes + i * 8) = packed;   // rows of codes and scales follow one another without gaps
+    scales[i] = (uint8_t)s8;
   }
 }
 
@@ -222,7 +195,7 @@ extern "C" int nvfp4_quantize(const void* W, int64_t N, int64_t K, int64_t ldw, 
   if (!workspace || !aligned(workspace, 4) || workspace_bytes < nvfp4_quantize_workspace_bytes(N, K))
     return QERL_ERR_WORKSPACE;
   const int64_t chunks = N * (K / 8);
-  int64_t nb = ceil_div(chunks, kAmaxThreads * kAmaxLoads);
+  int64_t nb = ceil_div(chunks, kAmaxThreads * 4);
   if (nb > kAmaxMaxBlocks) nb = kAmaxMaxBlocks;
   uint32_t* partial = (uint32_t*)workspace;
   const uint16_t* w = (const uint16_t*)W;

@@ -88,8 +88,8 @@ def test_quantize_every_bf16_below_the_block_maximum(amax):
 @pytest.mark.parametrize("N,K,ldw", [(1, 16, 16), (255, 16 * 129, 16 * 129), (257, 16 * 129, 16 * 131), (1111, 16 * 480, 16 * 480),
                                      (700, 16 * 800, 16 * 800 + 8)])
 def test_quantize_remainders_of_the_two_passes(N, K, ldw):
-    """Less than one load per thread, remainders of the unrolled maximum, several encode steps per thread; rows with
-    and without a gap behind them."""
+    """Less than one load per thread, several steps of either pass and a last one that is partly empty; rows with and
+    without a gap behind them."""
     W = cases.gaussian(N, K, seed=N)
     big = torch.full((N, ldw), 9.0, dtype=torch.bfloat16, device="cuda")
     big[:, :K] = to_gpu_bf16(W)
