@@ -574,7 +574,7 @@ def quantize_bench(args):
         "roofline": {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                      "traffic": None, "kernel": "amax_partial_kernel + encode_kernel", "algorithmic_bytes_per_launch": int(shp.N * shp.K * (4 + 0.5625)),
                      "shape": {"name": shp.name, "N": shp.N, "K": shp.K}, "us_per_launch": round(us, 2),
-                     "note": "one nvfp4_quantize call of the largest linear (three launches: partial maxima, final maximum, encode)"},
+                     "note": "one nvfp4_quantize call of the largest linear (two launches: partial maxima, encode)"},
     }))
 
 

@@ -103,13 +103,14 @@ __global__ __launch_bounds__(256) void backward_prepare_kernel(const PrepareArgs
 // LDS ([8-token group][column][8 tokens]), which the products read back with one ds_read_b128 each: seven reads for
 // six MFMAs, the two pipes about level.  With row-major tiles and sixteen-bit reads, 56 of them for the same six, the LDS
 // pipe was the bound, and each product was a launch of its own: the fourteen products of a 14B layer (2048 tokens, r = 64)
-// took 364 us and their sums 78 us in 28 launches, against 166 us and 29 us in eight.  Guarded 64-bit loads instead of buffer
+// took 364 us and their sums 78 us in 28 launches, against 178 us and 29 us in ten.  Guarded 64-bit loads instead of buffer
 // loads (a branch and an argument fetch each) cost 404 us.
 // A workgroup owns 128 columns of one product (32 per wave), all ranks and one chunk of the tokens; three MFMAs per rank tile and
 // 16 tokens (one per term).  Chunks: as many as give a product 128 workgroups -- their partial sums, 4 r bytes per
 // column and chunk, are written and read once each, so no more than that.  The count depends on the product alone, not on
-// the group it comes in, so a member's gradients are the same bits in a group and by themselves.  The partial sums are added
-// in order by a second launch.
+// the group it comes in, so a member's dA is the same bits in a group and by itself (dB need not be: the K-parts of
+// t = x A^T, which it is made from, depend on the number of adapters that share its launch).  The partial sums are added in
+// order by a second launch.
 constexpr int kGradRanks = 64;       // most ranks
 constexpr int kGradChunksMax = 8;    // token chunks (workgroups along M)
 constexpr int kGradTokens = 64;      // tokens per LDS tile

@@ -910,10 +910,10 @@ static int launch_down64_t(const GemmArgs& a, int n_tiles, int P, dim3 grid, hip
 // workgroup.  One tile per wave: the count that is estimated fastest among those whose parts are no longer than twice what
 // they are when the chip is filled twice over (the kernel's two chains then lose no more than one chain did there).  In
 // units of a 64-column slab (0.41 us of a workgroup that has its CU to itself): 1.6 slabs' time per slab where two share a CU,
-// 1.7 per part for the last workgroup's sums, 6 for the exchange as such.  Measured over K = 1024..27648, r = 16 and 64, the count
-// taken / the chip filled twice over / once, in us: K = 13824: 512 tokens 16.1 (14 parts) / 19.3 / 19.3, 2048 tokens 20.4 (8) / 24.4 /
-// 20.4; K = 18944, 640 tokens 19.3 (16) / 25.8 / 23.4, 4096 tokens 42.3 (8) / 42.3 / 43.8; K = 5120: 5504 tokens 19.3 (5) / 19.3 / 22.1,
-// 8256 tokens 24.5 (3) / 24.5 / 31.7.
+// 1.7 per part for the last workgroup's sums, 6 for the exchange as such.  Measured over 256..16384 tokens, K = 1024..27648,
+// r = 16 and 64, the count taken / the chip filled twice over / once, in us: K = 13824: 512 tokens 16.8 (12 parts) / 20.0 / 20.2,
+// 2048 tokens 20.2 (8) / 24.2 / 20.2; K = 18944: 640 tokens 18.7 (15) / 25.6 / 23.1, 4096 tokens 42.1 (8) / 41.9 / 43.4; K = 5120:
+// 5504 tokens 19.4 (5) / 19.3 / 21.9, 8256 tokens 23.8 (3) / 24.0 / 31.6; over all, 0.94 and 0.92 of the time of either aim.
 static int64_t down64_parts(int64_t tbs, int64_t K, int tpw) {
   const int64_t p_max = ceil_div(K, 512) < kDownMaxPartsWide ? ceil_div(K, 512) : kDownMaxPartsWide;
   auto filled = [&](int64_t wgs) { const int64_t p = wgs / tbs < p_max ? wgs / tbs : p_max; return p < 1 ? (int64_t)1 : p; };
