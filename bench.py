@@ -289,7 +289,7 @@ def dominant_kernel_roofline(stack: Stack, reps: int):
                 stack.mlp(L, "fused")
         shape = {"name": "norm+gate+up+silu_mul+down", "N": by["gate"].N, "K": by["gate"].K, "M": stack.M}
         bytes_per_launch = sum(by[n].packed_bytes for n in ("gate", "up", "down"))
-        kernel = "block_kernel"
+        kernel = "block_kernel" if stack.M <= 8 else "panel_kernel"   # (the call itself sends 9 tokens and more as separate launches)
     elif stack.M <= 16:
         names = ("gate", "up") if stack.block else (stack.cfg["linears"][0].name,)
         for L in stack.layers[:1]:          # any valid t will do for timing: it only feeds the up-projection
@@ -328,13 +328,11 @@ def dominant_kernel_roofline(stack: Stack, reps: int):
     ms = timed(run, reps) / len(stack.layers)
     common = {"shape": shape, "us_per_launch": round(ms * 1e3, 2),
               "note": "one call per launch slot, back to back over the layers' distinct weights, launch gaps included"}
-    # which roof binds the launch at the published peaks, and the kernel that runs it (17..64 tokens, and single
-    # linears up to 128: the weight-streaming mid_kernel; wide groups from 65 tokens on: the GEMM)
+    # which roof binds the launch at the published peaks, and the kernel that runs it (up to 128 tokens: panel_kernel)
     t_hbm = bytes_per_launch / (HBM_PEAK_GBS * 1e9)
     t_mfma = 2 * stack.M * shape["N"] * shape["K"] / (MFMA_BF16_PEAK_TFLOPS * 1e12)
-    gemm = stack.M > 128 or (stack.M > 64 and shape["name"] == "gate+up" and shape["N"] >= 16384)
-    if stack.M <= 16 or (not gemm) or (stack.M <= 128 and t_hbm >= t_mfma):
-        kernel = kernel or ("stream_kernel" if stack.M <= 16 else ("gemm32_kernel" if gemm else "mid_kernel"))
+    kernel = kernel or ("stream_kernel" if stack.M <= 16 else "panel_kernel" if stack.M <= 128 else "gemm32_kernel")
+    if stack.M <= 16 or (stack.M <= 128 and t_hbm >= t_mfma):
         achieved = bytes_per_launch / (ms * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
@@ -344,7 +342,7 @@ def dominant_kernel_roofline(stack: Stack, reps: int):
     achieved = flops / (ms * 1e-3) / 1e12
     return {"bound": "mfma", "achieved": round(achieved, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
-            "traffic": measured_traffic("gemm32_kernel", stack.w.config_no, shape["name"], stack.M), "kernel": "gemm32_kernel",
+            "traffic": measured_traffic(kernel, stack.w.config_no, shape["name"], stack.M), "kernel": kernel,
             "algorithmic_flops_per_launch": flops, **common}
 
 

@@ -23,11 +23,10 @@ static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // workspace: no call's data region may overlap another call's control words (they must stay zero).
 constexpr size_t kCtrlBytes = kCtrlRegionBytes;
 
-// 17..128 tokens: room for the K-splits' partial outputs (up to 8 splits, capped); the K-parts' sums of the
-// LoRA down-projection follow it.
-static size_t mid_partial_bytes(int64_t M, int64_t N) {
+// 17..128 tokens: room for the sums of linear_panel.hip (eight times the outputs in fp32, capped, and a little for t)
+static size_t panel_area_bytes(int64_t M, int64_t N) {
   const size_t b = (size_t)8 * (size_t)(M > 0 ? M : 1) * (size_t)(N > 0 ? N : 1) * sizeof(float);
-  return align256(b < kMidPartialCap ? b : kMidPartialCap);
+  return align256(b < kPanelSumsCap ? b : kPanelSumsCap) + kPanelTBytes;
 }
 
 static WorkspaceLayout workspace_layout(int64_t M, int64_t N, int64_t K, int64_t r) {
@@ -52,12 +51,12 @@ static WorkspaceLayout workspace_layout(int64_t M, int64_t N, int64_t K, int64_t
                               S_down * n_down_ctr * 64 * sizeof(f32x4) + kDecodeTpartWords * sizeof(uint32_t);
   size_t need = skinny_bytes > decode_bytes ? skinny_bytes : decode_bytes;
   if (M > 16 && M <= 128) {
-    const size_t mid = mid_partial_bytes(M, N) + kMidDownBytes;
-    need = need > mid ? need : mid;
+    const size_t panel = panel_area_bytes(M, N);
+    need = need > panel ? need : panel;
   }
   if (M > 128 && need < kDownExchangeBytes) need = kDownExchangeBytes;   // K-parts of the prefill path's LoRA down-projection
   if (M > 16) {
-    // the GEMM path from g_gemm_min_tokens on: a down-projection launched by itself has the whole area for its K-part
+    // the GEMM path: a down-projection launched by itself has the whole area for its K-part
     // sums and is through with it when the GEMM starts; one that rides inside the GEMM launch needs the first
     // kFusedDownBytes at most, and the GEMM's own K-parts start behind them
     size_t g = kFusedDownBytes + gemm_split_bytes(M, N);
@@ -216,9 +215,10 @@ extern "C" int nvfp4_lora_linear(const void* x, int64_t M, int64_t K, int64_t ld
 
 namespace qerl {
 static bool g_use_stream = true;
-static int g_gemm_min_tokens = 96;   // from here on the prefill GEMM (K split over workgroups where the tiles alone would not fill the chip) beats the 17..128-token kernel
-static int64_t g_mid_gemm_min_rows = 16384;   // 65..128 tokens: groups with at least this many output rows go to the prefill GEMM
-static int64_t g_mid_producer_bytes = 24 << 20;   // 17..128 tokens: LoRA down-projections run inside the main launch when it streams at least this many packed bytes (long enough to hide them)
+// From here to 128 tokens linear_panel.hip takes the packed linears.  Whole layers, us per layer, the 1..16-token kernels / the
+// panel kernels: 9 tokens 106 / 93 (7B shapes), 125 / 101 (14B), 140 / 131 (32B); 8 tokens 91 / 93, 108 / 101, 122 / 130 (the
+// decode kernels' cost follows the tokens in steps of eight, the panel kernels' in steps of 32).
+constexpr int64_t kPanelMinTokens = 9;
 
 // One streaming launch for a group of packed linears sharing x (M <= 16; every r in {0} or 8..64 step 8).
 static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
@@ -267,72 +267,44 @@ static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
   return launch_stream(a, lds, MR, st);
 }
 
-// A few dozen tokens (17..128), one linear or a group reading the same x: the LoRA down-projections of all
-// members write lora_scale / S32 * x A^T as three bf16 terms into the workspace (one launch), then the
-// weight-streaming kernel computes every member with those 3r columns appended to K (one launch, plus the
-// reduction of the K-splits if there are any).
-static int mid_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
-                     uint8_t* ws, const WorkspaceLayout& L, hipStream_t st) {
-  const bool few = M <= 128;   // K-splits and their workspace areas exist for these only
-  MidArgs g{};
-  g.x = x; g.ldx = ldx; g.M = M; g.K = K; g.k_tiles = (int)ceil_div(K, kPackTileK); g.n_members = n;
-  GemmArgs dn{};
-  dn.x = x; dn.ldx = ldx; dn.M = M; dn.K = K; dn.k_tiles = g.k_tiles;
-  int64_t n_sum = 0;
-  uint16_t* ts = (uint16_t*)(ws + L.t_off);
-  int tiles = 0;
-  for (int i = 0; i < n; ++i) {
-    MidMember& m = g.mem[i];
-    m.packed = (const uint8_t*)d[i].packed; m.tensor_scale = d[i].tensor_scale; m.N = d[i].N;
-    m.n_tiles = (int)ceil_div(d[i].N, kPackTileRows);
-    m.r = (int)d[i].r; m.B = (const uint16_t*)d[i].B_bf16; m.y = (uint16_t*)d[i].y_bf16; m.ldy = d[i].ldy;
-    m.bias = (const uint16_t*)d[i].bias_bf16;
-    m.ext_stages = (int)ceil_div(3 * d[i].r, 128); m.ts_ld = (int64_t)m.ext_stages * 128; m.ts = ts;
-    ts += M * m.ts_ld;
-    n_sum += d[i].N;
-    if (d[i].r > 0) {
-      const int gi = dn.g_n++;
-      dn.g_tile0[gi] = tiles; dn.g_A[gi] = (const uint16_t*)d[i].A_bf16; dn.g_ts[gi] = m.ts; dn.g_ts_ld[gi] = m.ts_ld;
-      dn.g_r[gi] = (int)d[i].r; dn.g_lora_scale[gi] = d[i].lora_scale; dn.g_tensor_scale[gi] = d[i].tensor_scale;
-      tiles += (int)ceil_div(d[i].r, 32);
+// 9..128 tokens, one linear or a group reading the same x, in two launches (linear_panel.hip); where the sums of all rows do
+// not fit the workspace's area, the rows in several parts of two launches each.  act != null: members 0 and 1 are
+// gate_proj and up_proj and act = SiLU(gate) (.) up is stored instead of their outputs.
+// QERL_ERR_SHAPE: not a shape for it (nothing has been launched).
+static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n, uint8_t* ws,
+                       const WorkspaceLayout& L, uint16_t* act, hipStream_t st) {
+  const int64_t k_tiles = ceil_div(K, kPackTileK);
+  auto part = [&](int c, int parts, PanelArgs& a) {
+    a = PanelArgs{};
+    a.x = x; a.ldx = ldx; a.M = (int)M; a.K = K; a.n_members = n;
+    for (int i = 0; i < n; ++i) {
+      PanelMember& m = a.mem[i];
+      const int64_t tiles = ceil_div(d[i].N, kPackTileRows), t0 = tiles * c / parts, t1 = tiles * (c + 1) / parts, row0 = t0 * kPackTileRows;
+      m.packed = (const uint8_t*)d[i].packed + t0 * k_tiles * kPackTileBytes; m.tensor_scale = d[i].tensor_scale;
+      m.N = (t1 * kPackTileRows < d[i].N ? t1 * kPackTileRows : d[i].N) - row0;
+      m.A = (const uint16_t*)d[i].A_bf16; m.r = (int)d[i].r; m.lora_scale = d[i].lora_scale;
+      m.B = d[i].r > 0 ? (const uint16_t*)d[i].B_bf16 + row0 * d[i].r : nullptr;
+      m.bias = d[i].bias_bf16 ? (const uint16_t*)d[i].bias_bf16 + row0 : nullptr;
+      m.y = d[i].y_bf16 ? (uint16_t*)d[i].y_bf16 + row0 : nullptr; m.ldy = d[i].ldy;
+      if (act && i == 0) { a.pairs = 1; a.act = act + row0; a.ld_act = d[0].N; }
     }
-  }
-  uint32_t* partial = (uint32_t*)(ws + L.partial_off);
-  g.partial = (float*)partial;
-  const int prc = plan_mid(g, few ? mid_partial_bytes(M, n_sum) : 0);
-  if (prc != QERL_OK) return prc;
-  if (dn.g_n > 0) {
-    dn.g_tile0[dn.g_n] = tiles;
-    dn.tpart = few ? partial + mid_partial_bytes(M, n_sum) / sizeof(uint32_t) : nullptr;
-    dn.counters = (uint32_t*)ws + L.n_main_ctr;
-    int64_t packed_bytes = 0;
-    for (int i = 0; i < n; ++i) packed_bytes += (int64_t)g.mem[i].n_tiles * g.k_tiles * kPackTileBytes;
-    // measured on 7B shapes: above 64 tokens it always pays (7.5 against 8.2 ms per step at 128); below, where the
-    // main launch runs long enough to hide producers of two or four waves (gate + up, down: 1-2 % of the step), for
-    // a single adapter (o: 24.9 -> 24.6 us at 32 tokens, 29.9 -> 28.8 at 64; 32B 37.3 -> 32.8) and for groups from 33
-    // tokens on (q + k + v 34.8 -> 31.7 us at 64 tokens, but 30.1 -> 36.4 at 32)
-    if (few && (M > 32 || dn.g_n == 1 || packed_bytes >= g_mid_producer_bytes)) {
-      // the down-projections run as the first workgroups of the main launch: token blocks x rank tiles x K-parts
-      // (parts as the stand-alone launch would choose them: a few dozen workgroups, at least 512 columns each)
-      const int64_t base_wgs = ceil_div(M, 32) * tiles;
-      int64_t P = base_wgs < 32 ? 64 / base_wgs : 1;
-      const int64_t p_max = ceil_div(K, 512);
-      P = P < p_max ? P : p_max;
-      P = P > 8 ? 8 : (P < 1 ? 1 : P);
-      g.p_tbs = (int)ceil_div(M, 32); g.p_tiles = tiles; g.p_parts = (int)P;
-      g.n_prod = (int)(ceil_div(base_wgs * P, 8) * 8);
-      g.ready = (uint32_t*)ws + L.n_main_ctr + L.n_down_ctr;      // the hand-over words (zero between calls)
-      g.done = g.ready + 2;
-      g.n_consumers = g.n_blocks * g.m_chunks * g.S;
-      dn.ready = g.ready;
-      g.dn = dn;
-    } else {
-      const int rc = launch_lora_down_gemm(dn, st);
+    return plan_panel(a, (float*)(ws + L.partial_off), L.total - L.partial_off);
+  };
+  PanelArgs a;
+  for (int parts = 1; parts <= 64; parts *= 2) {
+    bool fits = true;
+    for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
+    if (!fits) continue;
+    for (int c = 0; c < parts; ++c) {
+      int rc = part(c, parts, a);
+      if (rc == QERL_OK) rc = launch_panel(a, st);
       if (rc != QERL_OK) return rc;
     }
+    return QERL_OK;
   }
-  return launch_mid(g, st);
+  return QERL_ERR_SHAPE;
 }
+
 // The GEMM launch and the LoRA down-projections it depends on (dn: the group form, tiles rank tiles; g_n == 0: none).
 // launch_gemm either takes the down-projections into its own launch (few tokens) or runs them first; the scratch
 // serves the down-projection's K-parts from its front and the GEMM's own K-parts from kFusedDownBytes on (inside
@@ -355,7 +327,7 @@ static int gemm_with_down(GemmArgs& g, GemmArgs& dn, int tiles, int64_t n_sum, u
   return launch_gemm(g, st);
 }
 
-// More tokens than mid_kernel takes: one launch of the LoRA down-projection for all adapters of the group, then
+// More than 128 tokens: one launch of the LoRA down-projection for all adapters of the group, then
 // one GEMM launch whose column blocks run over all members (k and v alone would fill half the chip).
 static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
                       uint8_t* ws, const WorkspaceLayout& L, hipStream_t st) {
@@ -388,9 +360,6 @@ static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, cons
 
 #ifdef QERL_TUNING_HOOKS   // built only for tuning sessions: they change process-wide state
 extern "C" QERL_API void qerl_debug_use_stream(int on) { qerl::g_use_stream = on != 0; }
-extern "C" QERL_API void qerl_debug_mid_producer_bytes(long long b) { qerl::g_mid_producer_bytes = b; }
-extern "C" QERL_API void qerl_debug_mid_gemm_min_rows(long long n) { qerl::g_mid_gemm_min_rows = n; }
-extern "C" QERL_API void qerl_debug_gemm_min_tokens(int m) { qerl::g_gemm_min_tokens = m; }
 #endif  // QERL_TUNING_HOOKS
 
 static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const void* packed,
@@ -398,13 +367,14 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
                          int64_t r, float lora_scale, const void* bias, void* y, int64_t ldy, void* workspace,
                          size_t workspace_bytes, void* stream);
 
-extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t K, int64_t ldx,
-                                              const qerl_linear_desc* members, int n_members, void* workspace,
-                                              size_t workspace_bytes, void* stream) {
+// act != null: members 0 and 1 are gate_proj and up_proj; act[M, N] = SiLU(gate) (.) up is stored instead of their
+// outputs where the shape has a kernel for it (QERL_OK), else nothing is launched (kNoFusedAct).
+static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* members, int n_members,
+                             void* workspace, size_t workspace_bytes, uint16_t* act, void* stream) {
   if (!members) return QERL_ERR_NULL;
   if (n_members < 1 || n_members > kMaxGroup) return QERL_ERR_SHAPE;
   int64_t n_sum = 0, r_sum = 0;
-  bool stream_ok = M <= 16, mid_ok = true;
+  bool stream_ok = M <= 16, lora_ok = true, t_given = false;   // (t handed in: only the decode kernels read it)
   for (int i = 0; i < n_members; ++i) {
     const qerl_linear_desc& d = members[i];
     LinearCall c{(const uint16_t*)x, M, K, ldx, d.tensor_scale, d.N, (const uint16_t*)d.A_bf16, (const uint16_t*)d.B_bf16,
@@ -414,7 +384,8 @@ extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t 
     if (d.N < 1) return QERL_ERR_SHAPE;
     n_sum += d.N; r_sum += d.r;
     stream_ok = stream_ok && (d.r == 0 || (d.r <= 64 && d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
-    mid_ok = mid_ok && (d.r == 0 || (d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
+    lora_ok = lora_ok && (d.r == 0 || (d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
+    t_given = t_given || (d.r > 0 && d.t_f32);
     if (d.r > 0 && d.t_f32 && !aligned(d.t_f32, 32)) return QERL_ERR_ALIGN;
   }
   if (M == 0) return QERL_OK;
@@ -422,16 +393,14 @@ extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t 
   if (!aligned(x, 16) || ldx % 8 != 0) return QERL_ERR_ALIGN;
   const WorkspaceLayout L = workspace_layout(M, n_sum, K, r_sum);
   if (!workspace || !aligned(workspace, 256) || workspace_bytes < L.total) return QERL_ERR_WORKSPACE;
+  if (lora_ok && M >= kPanelMinTokens && M <= 128 && (M > 16 || !t_given)) {
+    const int rc = panel_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, act, (hipStream_t)stream);
+    if (rc != QERL_ERR_SHAPE) return rc;
+  }
+  if (act) return kNoFusedAct;
   if (stream_ok && g_use_stream)
     return stream_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream);
-  // 65..128 tokens on a group with many output rows (gate + up): the prefill GEMM has enough column blocks to fill
-  // the chip with one block of tokens and multiplies faster than the weight-streaming kernel (115 against 181 us
-  // for the 32B pair at 128 tokens); the workspace of such a shape holds the GEMM's areas
-  const bool wide = M > 64 && n_sum >= g_mid_gemm_min_rows && mid_partial_bytes(M, n_sum) >= kDownExchangeBytes;
-  const bool to_gemm = M >= g_gemm_min_tokens || M > g_mid_max_tokens || (wide && n_members > 1);
-  if (M > 16 && mid_ok && !to_gemm)
-    return mid_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream);
-  if (to_gemm && mid_ok && n_members > 1)
+  if (M > 16 && lora_ok && n_members > 1)
     return gemm_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream);
   for (int i = 0; i < n_members; ++i) {   // general case: member by member
     const qerl_linear_desc& d = members[i];
@@ -440,6 +409,17 @@ extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t 
     if (rc != QERL_OK) return rc;
   }
   return QERL_OK;
+}
+
+extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t K, int64_t ldx,
+                                              const qerl_linear_desc* members, int n_members, void* workspace,
+                                              size_t workspace_bytes, void* stream) {
+  return packed_group_impl(x, M, K, ldx, members, n_members, workspace, workspace_bytes, nullptr, stream);
+}
+
+int qerl::packed_gate_up_act(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* gate_up, void* workspace,
+                             size_t workspace_bytes, uint16_t* act, void* stream) {
+  return packed_group_impl(x, M, K, ldx, gate_up, 2, workspace, workspace_bytes, act, stream);
 }
 
 extern "C" size_t nvfp4_prepack_bytes(int64_t N, int64_t K) {
@@ -515,9 +495,10 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
   uint32_t* partial = (uint32_t*)(ws + L.partial_off);
 
   const bool lora_gemm_ok = r == 0 || (r % 8 == 0 && aligned(A, 16) && aligned(B, 16));
-  if (M > 16 && M <= g_mid_max_tokens && M < g_gemm_min_tokens && lora_gemm_ok) {
+  if (M >= kPanelMinTokens && M <= 128 && lora_gemm_ok) {
     qerl_linear_desc d{packed, tensor_scale, N, A, B, r, lora_scale, y, ldy, nullptr, bias};
-    return mid_group(c.x, M, K, ldx, &d, 1, ws, L, c.st);
+    const int rc = panel_group(c.x, M, K, ldx, &d, 1, ws, L, nullptr, c.st);
+    if (rc != QERL_ERR_SHAPE) return rc;
   }
   if (M > 16 && lora_gemm_ok) {
     // Prefill: one split-K GEMM writes lora_scale * x A^T as three bf16 terms into the workspace,

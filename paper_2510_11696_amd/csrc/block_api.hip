@@ -7,6 +7,11 @@
 
 namespace qerl {
 
+// Token count from which norm and linears go out as separate launches (the panel kernels), and a whole feed-forward block
+// likewise: us at 9 / 16 tokens, one launch against norm + panel launches: 7B q + k + v 23.4 / 24.3 against 18, feed-forward
+// block 66 / 75 against 62; 32B 27.9 / 29.3 against 21.6 and 89 / 98 against 94.  At 8 tokens one launch: 19.0 and 56.9 (7B), 80.8 (32B).
+constexpr int64_t kBlkSeparateTokens = 9;
+
 static size_t blk_align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // Workspace of a block launch: the control region every linear workspace starts with (arrival words of the tiles,
@@ -103,17 +108,25 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
   int64_t n_sum = 0, r_sum = 0;
   for (int i = 0; i < n; ++i) { d[i] = members + i; n_sum += members[i].N; r_sum += members[i].r; }
   if (M == 0 && launch) return QERL_OK;
+  const size_t lin = nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
+  const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)K * sizeof(uint16_t)) : 0;
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 1;
-    const int rc = blk_fill_stage(a.st[0], launch ? x : (const void*)(uintptr_t)256, K, ldx, gain, noise, eps, d, n, false);
+    int rc = blk_fill_stage(a.st[0], launch ? x : (const void*)(uintptr_t)256, K, ldx, gain, noise, eps, d, n, false);
     if (rc != QERL_OK) return rc;
-    return blk_plan_and_launch(a, (uint8_t*)workspace, bytes, 0, launch, need, (hipStream_t)stream);
+    // from kBlkSeparateTokens on the separate launches are faster; a workspace with room for the one launch only still gets it
+    if (M < kBlkSeparateTokens || (launch && bytes < lin + xn_bytes))
+      return blk_plan_and_launch(a, (uint8_t*)workspace, bytes, 0, launch, need, (hipStream_t)stream);
+    size_t one = 0;
+    rc = blk_plan_and_launch(a, nullptr, 0, 0, false, &one, nullptr);   // shapes that the one launch does not take stay refused
+    if (rc != QERL_OK) return rc;
+    if (need) *need = one > lin + xn_bytes ? one : lin + xn_bytes;
+    if (launch && bytes < one) return QERL_ERR_WORKSPACE;
+  } else if (need) {
+    *need = lin + xn_bytes;
   }
   // more tokens: the norm's launch (output in the workspace), then the grouped linear
-  const size_t lin = nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
-  const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)K * sizeof(uint16_t)) : 0;
-  if (need) *need = lin + xn_bytes;
   if (!launch) return QERL_OK;
   if (!workspace || !aligned(workspace, 256) || bytes < lin + xn_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
@@ -124,7 +137,9 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
     if (rc != QERL_OK) return rc;
     xin = xn; ldin = K;
   }
-  return nvfp4_lora_linear_packed_group(xin, M, K, ldin, members, n, workspace, lin, stream);
+  qerl_linear_desc own[kMaxGroup];
+  for (int i = 0; i < n; ++i) { own[i] = members[i]; own[i].t_f32 = nullptr; }   // this entry point computes t itself
+  return nvfp4_lora_linear_packed_group(xin, M, K, ldin, own, n, workspace, lin, stream);
 }
 
 extern "C" size_t aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(int64_t M, int64_t K, const int64_t* Ns, const int64_t* rs, int n) {
@@ -156,6 +171,12 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   if (M == 0 && launch) return QERL_OK;
   if (launch && (!down->y_bf16 || down->ldy < down->N)) return down->y_bf16 ? QERL_ERR_SHAPE : QERL_ERR_NULL;
   const size_t act_bytes = blk_align256((size_t)(M > 0 ? M : 1) * (size_t)I * sizeof(uint16_t));
+  const size_t lin_gu = nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r);
+  const size_t lin_dn = nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
+  const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
+  const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)H * sizeof(uint16_t)) : 0;
+  const size_t separate_bytes = lin + xn_bytes + 2 * act_bytes;
+  const bool separate = M >= kBlkSeparateTokens && !down->bias_bf16 && (!launch || bytes >= separate_bytes);
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 2;
@@ -173,29 +194,27 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
     if (rc != QERL_OK) return rc;
     if (ctrs > kCtrlMainWords) return QERL_ERR_SHAPE;
     const BlkWorkspace w = blk_workspace(part, act_bytes);
-    if (need) *need = w.total;
+    if (need) *need = separate && separate_bytes > w.total ? separate_bytes : w.total;
     if (!launch) return QERL_OK;
     uint8_t* ws = (uint8_t*)workspace;
     if (!ws || !aligned(ws, 256) || bytes < w.total) return QERL_ERR_WORKSPACE;
-    uint16_t* act = (uint16_t*)(ws + w.act_off);
-    a.st[0].act = act; a.st[1].x = act;
-    a.counters = (uint32_t*)ws;
-    a.ctl = (uint32_t*)ws + kCtrlMainWords + kCtrlDownWords;
-    a.tpart = (uint32_t*)(ws + w.tpart_off);
-    a.tfinal = (float*)(ws + w.tfinal_off);
-    a.partial = (float*)(ws + w.partial_off);
-    return launch_block(a, lds, MR, (hipStream_t)stream);
+    if (!separate) {
+      uint16_t* act = (uint16_t*)(ws + w.act_off);
+      a.st[0].act = act; a.st[1].x = act;
+      a.counters = (uint32_t*)ws;
+      a.ctl = (uint32_t*)ws + kCtrlMainWords + kCtrlDownWords;
+      a.tpart = (uint32_t*)(ws + w.tpart_off);
+      a.tfinal = (float*)(ws + w.tfinal_off);
+      a.partial = (float*)(ws + w.partial_off);
+      return launch_block(a, lds, MR, (hipStream_t)stream);
+    }
   }
   // more tokens: norm, grouped gate + up, down on the gated input, as separate launches; the intermediates live in
   // the workspace behind the linear's own area
-  const size_t lin_gu = nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r);
-  const size_t lin_dn = nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
-  const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
-  const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)H * sizeof(uint16_t)) : 0;
-  if (need) *need = lin + xn_bytes + 2 * act_bytes;
+  if (need) *need = separate_bytes;
   if (!launch) return QERL_OK;
   uint8_t* ws = (uint8_t*)workspace;
-  if (!ws || !aligned(ws, 256) || bytes < lin + xn_bytes + 2 * act_bytes) return QERL_ERR_WORKSPACE;
+  if (!ws || !aligned(ws, 256) || bytes < separate_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
   int64_t ldin = ldx;
   if (gain) {
@@ -207,7 +226,15 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   qerl_linear_desc gu[2] = {*gate, *up};
   gu[0].y_bf16 = ws + lin + xn_bytes; gu[0].ldy = I; gu[0].t_f32 = nullptr;
   gu[1].y_bf16 = ws + lin + xn_bytes + act_bytes; gu[1].ldy = I; gu[1].t_f32 = nullptr;
-  int rc = nvfp4_lora_linear_packed_group(xin, M, H, ldin, gu, 2, ws, lin, stream);
+  uint16_t* act = (uint16_t*)(ws + lin + xn_bytes);   // gate's place: the fused form stores no gate
+  int rc = packed_gate_up_act(xin, M, H, ldin, gu, ws, lin, act, stream);
+  if (rc == QERL_OK) {
+    if (down->bias_bf16) return QERL_ERR_SHAPE;
+    return nvfp4_lora_linear_packed(act, M, I, I, down->packed, down->tensor_scale, down->N, down->A_bf16, down->B_bf16, down->r,
+                                    down->lora_scale, down->y_bf16, down->ldy, ws, lin, stream);
+  }
+  if (rc != kNoFusedAct) return rc;
+  rc = nvfp4_lora_linear_packed_group(xin, M, H, ldin, gu, 2, ws, lin, stream);
   if (rc != QERL_OK) return rc;
   if (down->bias_bf16) return QERL_ERR_SHAPE;   // (the gated entry point takes no bias)
   return nvfp4_lora_linear_packed_swiglu(gu[0].y_bf16, gu[1].y_bf16, M, I, I, I, down->packed, down->tensor_scale, down->N,

@@ -177,32 +177,33 @@ constexpr int kDownMaxSlots = 256;                                           // 
 constexpr size_t kDownExchangeBytes = (size_t)16 << 20;   // the K-parts' partial sums (32-token kernel: kDownMaxSlots workgroups of two 32 x 32 tiles; 64-token kernel: up to eight tiles per wave quartet)
 int launch_lora_down_gemm(const GemmArgs& a, hipStream_t st);
 
-// ---- 17..128 tokens: weight-streaming MFMA kernel on tile-packed weights (linear_mid.hip) ----
-constexpr size_t kMidPartialCap = (size_t)32 << 20;   // most workspace bytes the K-splits' partial outputs may take
-constexpr size_t kMidDownBytes = (size_t)64 * 2 * 16 * 64 * sizeof(float);   // K-parts' sums of the LoRA down-projection: at most 64 workgroups, two 32 x 32 tiles each
-struct MidMember {
-  const uint8_t* packed; const float* tensor_scale; int64_t N; int n_tiles;
-  const uint16_t* ts; int64_t ts_ld; int ext_stages;                        // [M, ts_ld] bf16: hi | mid | lo of lora_scale / S32 * t; stages of 128 columns
-  const uint16_t* B; int r;
+// ---- 9..128 tokens: matrix instructions over units of rows, sums in the workspace, a second launch (linear_panel.hip) ----
+constexpr size_t kPanelSumsCap = (size_t)32 << 20, kPanelTBytes = (size_t)512 << 10;   // most workspace bytes for the sums of W's and A's rows
+struct PanelMember {
+  const uint8_t* packed; const float* tensor_scale; int64_t N;
+  const uint16_t* A; const uint16_t* B; int r; float lora_scale;
   const uint16_t* bias;                                                     // [N] bf16 or null
   uint16_t* y; int64_t ldy;
-  int block_begin;                                                          // first column block (W row-tiles each) of this member
-  int64_t partial_off;                                                      // floats: this member's [S][M][N] partial outputs start here
+  int n_tiles; int unit_begin; int rt_begin;                                // row tiles; first unit; first rank tile (set by the planner)
+  int y_vec;                                                                // rows of the output allow 8-byte stores (set by the planner)
 };
-struct MidArgs {
-  const uint16_t* x; int64_t ldx; int64_t M; int64_t K; int k_tiles;
-  int n_members; MidMember mem[kMaxGroup];                                  // unused entries: block_begin = INT_MAX
-  float* partial;                                                           // K-splits' partial outputs when S > 1
-  int n_blocks; int m_chunks; int S; int kt_per_split; int MT; int W;
-  // LoRA down-projections inside the launch (n_prod > 0): the first n_prod workgroups (a multiple of 8) compute ts
-  // as lora_down_block does -- token block x rank tile x K-part = p_tbs x p_tiles x p_parts of them, the rest idle --
-  // and the workgroups that carry the LoRA columns wait until `ready` has counted p_tbs * p_tiles of them; every
-  // consumer workgroup counts itself in `done` when it leaves, the last one zeroes both words for the next call.
-  GemmArgs dn; int n_prod; int p_tbs; int p_tiles; int p_parts; uint32_t* ready; uint32_t* done; int n_consumers;
+struct PanelArgs {
+  const uint16_t* x; int64_t ldx; int M; int64_t K;
+  int n_members; PanelMember mem[kMaxGroup];                                // unused entries: unit_begin = INT_MAX, r = 0
+  int pairs; uint16_t* act; int64_t ld_act;                                 // members 0, 1 are gate_proj, up_proj: act = SiLU(gate) (.) up instead of their outputs
+  // the plan: token tiles, K-tiles; K-slices of a workgroup, row tiles of a wave and of a unit (and its log2), units, stages of 64 KW inputs; A's rank tiles, K-parts, workgroups
+  int NT; int k_tiles; int KW; int RT; int unit_tiles; int unit_shift; int units; int stages; int rank_tiles; int t_parts; int n_lora;
+  // workgroups over the units' stages: every unit in `split` pieces, or (0) `per` stages each, the first `rem` one more
+  int n_main; int split; int per; int rem; uint32_t per_inv; uint32_t per1_inv;   // 2^32 / per, 2^32 / (per + 1), rounded up
+  float* sums; float* t_sums;                                               // [slot][unit_tiles][NT][1024]; [t_parts][rank_tiles][NT][1024]
 };
-extern int g_mid_max_tokens;
-int plan_mid(MidArgs& a, size_t partial_cap_bytes);
-int launch_mid(const MidArgs& a, hipStream_t st);
+int plan_panel(PanelArgs& a, float* area, size_t area_bytes);
+int launch_panel(const PanelArgs& a, hipStream_t st);
+// gate_proj and up_proj as nvfp4_lora_linear_packed_group, with act[M, N] = bf16(bf16(SiLU(gate)) * up) in place of their
+// outputs; kNoFusedAct (nothing launched) where the shape has no kernel for it (api.hip)
+constexpr int kNoFusedAct = 1;
+int packed_gate_up_act(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* gate_up, void* workspace,
+                       size_t workspace_bytes, uint16_t* act, void* stream);
 
 // General fallback (any K % 16 == 0, any alignment of rows the ABI allows).
 int launch_generic_lora_down(const uint16_t* x, int64_t ldx, int64_t M, int64_t K, const uint16_t* A,

@@ -1,6 +1,6 @@
-// LoRA down-projection for 17 tokens and more: ts = three bf16 terms of (lora_scale / S32) * x A^T   (Eq. 2, first factor)
+// LoRA down-projection for more than 128 tokens (the MXFP4 linears: any count): ts = three bf16 terms of (lora_scale / S32) * x A^T   (Eq. 2, first factor)
 // as a block-level routine, so that it can run as a kernel of its own (prefill) or as the leading workgroups of
-// the 17..128-token kernel's launch.
+// a GEMM launch of few tokens.
 #pragma once
 #include "linear.hpp"
 

@@ -1,0 +1,116 @@
+"""GPU parity of the 9..128-token kernels (linear_panel.hip) at the sizes where their plan changes: edges of token tiles, row
+tiles, units and stages, each way of cutting the units into pieces, ranks beyond one chunk, rows in several launches, outputs
+without 8-byte stores, and workspaces with room for the one-launch kernels only."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2510_11696_amd as qerl
+import qerl_synth as qs
+from oracle import nvfp4_oracle as oracle
+from tests.gpu_util import check_linear
+from tests.test_gpu_block import _bf16, _member, _norm_inputs, _ref
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [9, 16, 17, 32, 33, 64, 65, 96, 97, 128])
+@pytest.mark.parametrize("K,Ns,rs,bias", [
+    (512, (129, 64), (16, 0), True),        # a ragged row tile, one row past a unit; a member without adapter
+    (1168, (1000, 40, 31), (32, 8, 64), False),   # K: ten K-tiles, the last of 16 inputs; stages that end on half a slab
+    (4352, (320,), (72,), True),            # more than 64 ranks, more than one piece per unit
+    (16, (8200,), (8,), False),             # one K-tile: the second half of the stage is beyond K
+])
+def test_edges_of_the_plan(M, K, Ns, rs, bias):
+    print("panel case", M, K, Ns, rs, bias, flush=True)
+    x = qs.activations(M, K, 50 + M)
+    ms = [_member(N, K, r, 60 + 3 * i + M, bias) for i, (N, r) in enumerate(zip(Ns, rs))]
+    ws = qerl.Workspace(qerl.nvfp4_lora_linear_workspace_bytes(M, sum(Ns), K, sum(rs)))
+    # rows of x further apart than K; the first output at an odd leading dimension (no 8-byte stores), with canaries
+    xs = torch.full((M, K + 24), 7.0, dtype=torch.bfloat16, device="cuda")
+    xs[:, :K] = x.cuda()
+    wide = torch.full((M, Ns[0] + 3), -5.0, dtype=torch.bfloat16, device="cuda")
+    outs = [wide[:, :Ns[0]]] + [torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for N in Ns[1:]]
+    call = lambda: qerl.nvfp4_lora_linear_packed_group(xs[:, :K], [m["pw"] for m in ms], [m["Ad"] for m in ms], [m["Bd"] for m in ms],
+                                                       [2.0] * len(ms), workspace=ws, outs=outs, biases=[m["bd"] for m in ms])
+    got = [o.clone() for o in call()]
+    for i, m in enumerate(ms):
+        check_linear(got[i], _ref(m, x.float().numpy(), 2.0), ("panel", i, M, K, Ns, rs))
+    assert torch.all(wide[:, Ns[0]:] == -5.0)
+    assert all(torch.equal(a, b) for a, b in zip(call(), got))
+
+
+@pytest.mark.parametrize("M,N,K,r", [
+    (16, 40000, 512, 16),     # more units than workgroups
+    (40, 36864, 768, 16),     # equal pieces of the line of units (pieces that end inside a unit)
+    (30, 24576, 1536, 8),     # the same at two workgroups per CU
+    (128, 55296, 384, 8),     # whole units of 256 rows
+    (70, 53248, 256, 8),      # the same, three token tiles
+    (128, 70016, 128, 8),     # the sums of all rows do not fit the workspace: several pairs of launches
+])
+def test_wide_launches(M, N, K, r):
+    print("panel wide case", M, N, K, r, flush=True)
+    gen = torch.Generator().manual_seed(M + N)
+    codes = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, generator=gen)
+    scales = torch.randint(0x20, 0x50, (N, K // 16), dtype=torch.uint8, generator=gen)
+    ts = torch.tensor([0.01], dtype=torch.float32)
+    A, B = qs.lora_pair(N, K, r, 5)
+    x = qs.activations(M, K, 6)
+    pw = qerl.nvfp4_prepack(codes.cuda(), scales.cuda(), ts.cuda())
+    y = qerl.nvfp4_lora_linear_packed(x.cuda(), pw, A.cuda(), B.cuda(), 2.0)
+    rows = np.unique(np.concatenate([np.arange(0, N, 997), np.arange(0, N, 128), np.arange(127, N, 128), [N - 1]]))
+    ref = oracle.nvfp4_lora_linear(x.float().numpy(), codes.numpy()[rows], scales.numpy()[rows], float(ts), A.float().numpy(),
+                                   B.float().numpy()[rows], 2.0)
+    check_linear(y[:, torch.from_numpy(rows).cuda()].contiguous(), ref, ("panel wide", M, N, K, r))
+
+
+@pytest.mark.parametrize("M", [9, 16, 33, 100])
+@pytest.mark.parametrize("H,I,r", [(1024, 2736, 16), (512, 400, 72), (512, 4000, 64)])
+def test_feed_forward_block_with_the_gated_second_launch(M, H, I, r):
+    if r > 64 and M <= 16:
+        pytest.skip("up to 16 tokens this entry point takes ranks up to 64")
+    print("panel mlp case", M, H, I, r, flush=True)
+    xin, gain, Z, xn = _norm_inputs(M, H, 11, 1e-2)
+    g, u, d = _member(I, H, r, 12), _member(I, H, r, 15), _member(H, I, r, 18)
+    act = _bf16(oracle.silu_mul(_bf16(_ref(g, xn, 2.0)), _bf16(_ref(u, xn, 2.0))))
+    ref = _ref(d, act, 2.0)
+    lib = qerl.load_library()
+    need = lib.aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes(M, H, I, H, r, r, r)
+
+    def call(ws):
+        return qerl.aqn_rmsnorm_nvfp4_lora_mlp(xin.cuda(), gain.cuda(), Z.cuda(), 1e-6, g["pw"], u["pw"], d["pw"],
+                                               [m["Ad"] for m in (g, u, d)], [m["Bd"] for m in (g, u, d)], (2.0,) * 3,
+                                               workspace=ws)
+    ws = qerl.Workspace(need)
+    y = call(ws)
+    check_linear(y, ref, ("panel mlp", M, H, I, r), slack=4e-3)
+    assert torch.equal(call(ws), y)
+
+
+@pytest.mark.parametrize("M", [9, 16])
+def test_a_workspace_for_the_one_launch_form_is_still_accepted(M):
+    """Up to 16 tokens a buffer that holds the one-launch kernel's areas (what 8 tokens need, scaled to M by its own plan) but
+    not the separate launches' keeps running that kernel."""
+    H, I, r = 1024, 2048, 16
+    xin, gain, Z, xn = _norm_inputs(M, H, 21, 1e-2)
+    g, u, d = _member(I, H, r, 22), _member(I, H, r, 25), _member(H, I, r, 28)
+    act = _bf16(oracle.silu_mul(_bf16(_ref(g, xn, 2.0)), _bf16(_ref(u, xn, 2.0))))
+    lib = qerl.load_library()
+    need = lib.aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes(M, H, I, H, r, r, r)
+    separate = (max(qerl.nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, 2 * r), lib.nvfp4_lora_linear_swiglu_workspace_bytes(M, H, I, r))
+                + 2 * M * H + 4 * M * I)
+    ran = 0
+    for bytes_ in (need, separate - 256):
+        ws = qerl.Workspace(bytes_)
+        try:
+            y = qerl.aqn_rmsnorm_nvfp4_lora_mlp(xin.cuda(), gain.cuda(), Z.cuda(), 1e-6, g["pw"], u["pw"], d["pw"],
+                                                [m["Ad"] for m in (g, u, d)], [m["Bd"] for m in (g, u, d)], (2.0,) * 3, workspace=ws)
+        except (RuntimeError, ValueError):
+            assert bytes_ < need      # smaller than both forms need
+            continue
+        ran += 1
+        check_linear(y, _ref(d, act, 2.0), ("mlp", M, bytes_), slack=4e-3)
+        q = qerl.aqn_rmsnorm_nvfp4_lora_linear_group(xin.cuda(), gain.cuda(), Z.cuda(), 1e-6, [g["pw"]], [g["Ad"]], [g["Bd"]], [2.0], workspace=ws)[0]
+        check_linear(q, _ref(g, xn, 2.0), ("group", M, bytes_))
+    assert ran >= 1
