@@ -30,6 +30,7 @@ inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // ---- device side ----------------------------------------------------------
+__device__ __forceinline__ bool aligned_dev(const void* p, uint32_t a) { return ((uint32_t)(uintptr_t)p & (a - 1)) == 0; }
 __device__ __forceinline__ int64_t ceil_div_dev(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // bf16 <-> fp32 by bit manipulation (bf16 is the top half of an fp32).
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }

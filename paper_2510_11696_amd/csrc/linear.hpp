@@ -170,6 +170,9 @@ struct GemmArgs {
   int g_r[kMaxGroup]; float g_lora_scale[kMaxGroup]; const float* g_tensor_scale[kMaxGroup];
 };
 int launch_gemm(const GemmArgs& a, hipStream_t st);
+// its members by 128 x 256 tiles (linear_prefill.hip): one launch, the down-projections done; false: not this launch
+bool prefill_takes(const GemmArgs& a);
+int launch_prefill(const GemmArgs& a, hipStream_t st);
 constexpr size_t kGemmSplitCap = (size_t)24 << 20;
 constexpr size_t kFusedDownBytes = (size_t)1 << 20;   // K-part sums of down-projections that ride inside a GEMM launch: at most 64 workgroups of one 32 x 32 tile
 size_t gemm_split_bytes(int64_t M, int64_t N_total);   // scratch worth offering launch_gemm as kpartial for this shape (0: it would not split K)

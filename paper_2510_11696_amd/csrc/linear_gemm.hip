@@ -640,10 +640,15 @@ struct GemmConfig { int MT, NT, W, wg_per_cu; float quality, quality_shared, qua
 // (at most 256 of them), quality_shared when a single round puts two on a CU, quality_rounds when the launch takes
 // several rounds.  The one-tile-per-wave shapes hide the conversions behind more waves but re-read x more often.
 static const GemmConfig kConfigs[] = {
-    {4, 2, 4, 1, 0.72f, 0.72f, 0.72f}, {4, 2, 5, 1, 0.75f, 0.75f, 0.75f}, {4, 2, 8, 1, 1.00f, 1.00f, 1.00f},
     {4, 1, 4, 2, 0.95f, 0.84f, 0.85f}, {4, 1, 8, 2, 0.95f, 0.93f, 0.95f},
     {4, 1, 10, 1, 0.90f, 0.90f, 0.86f},   // 320 output rows per workgroup, ten waves: N = 5120 in one full round
+    {4, 2, 4, 2, 1.12f, 1.12f, 1.12f},    // linear_prefill.hip: forward launches without a K split
+    {4, 2, 8, 1, 1.00f, 1.00f, 1.00f},    // the backward pass only
 };
+constexpr int kCfgTall = 2, kCfgPrefill = 3, kCfgBackward = 4;
+// A workgroup of linear_prefill.hip that has its CU to itself takes 0.58 of the time of a pair (7B gate + up, K = 3584, 777 tokens, 12
+// workgroups beyond two rounds of 512: 214 us, 85 of them a round; 32B down at 4096 tokens, 1.25 rounds: 1020 us, 650 a round)
+constexpr double kPrefillAlone = 0.58;
 static int g_force_cfg = -1;
 static bool g_split = true;   // whole rounds and remainder as two launches when that is estimated faster
 static int g_force_ksplit = 0;   // tuning: K-parts of the forward launch (0 = automatic, 1 = never)
@@ -735,11 +740,17 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
     a.p_parts = (int)P;
     prod_wgs = ceil_div(base_wgs * P, 8) * 8;
   }
+  const bool prefill_ok = prefill_takes(a);
+  auto eligible = [&](int c) { return a.transposed ? c == kCfgTall || c == kCfgBackward : c != kCfgBackward && (c != kCfgPrefill || prefill_ok); };
   auto cfg_time = [&](int c, const GemmMember* m, int n, int S = 1) {
     const GemmConfig& g = kConfigs[c];
     const int64_t bm = g.MT * 32, bn = (int64_t)g.W * g.NT * 32;
     int64_t col_blocks = 0;
     for (int i = 0; i < n; ++i) col_blocks += ceil_div(m[i].N, bn);
+    if (c == kCfgPrefill) {
+      const int64_t wgs = ceil_div(a.M, bm) * col_blocks, rest = wgs % 512;
+      return ((double)(wgs / 512) + (rest == 0 ? 0.0 : rest <= 256 ? kPrefillAlone : 1.0)) * 512.0 * (double)bm * (double)bn / g.quality;
+    }
     const int64_t wgs = ceil_div(a.M, bm) * col_blocks * S + prod_wgs;     // S K-parts: S times the workgroups, each 1 / S of the K-loop
     const bool alone = wgs <= 256;                              // every workgroup gets a CU of its own
     const int64_t slots = alone ? 256 : 256 * g.wg_per_cu;
@@ -750,7 +761,7 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
   auto best_cfg = [&](const GemmMember* m, int n, double& t_best) {
     int best = -1;
     for (int c = 0; c < n_cfg; ++c) {
-      if (a.transposed && c != 2 && c != 5) continue;   // the backward pass is instantiated for two shapes
+      if (!eligible(c)) continue;
       if (fuse_wanted && kConfigs[c].W > 8) continue;    // the producers' reduction needs LDS per wave
       const double t = cfg_time(c, m, n);
       if (best < 0 || t < t_best) { t_best = t; best = c; }
@@ -774,7 +785,7 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
         return QERL_ERR_SHAPE;
     }
   }
-  if (a.transposed) return best == 5 ? launch_cfg<4, 1, 10, true>(a, st) : launch_cfg<4, 2, 8, true>(a, st);
+  if (a.transposed) return best == kCfgTall ? launch_cfg<4, 1, 10, true>(a, st) : launch_cfg<4, 2, 8, true>(a, st);
   if (g_force_cfg >= 0) best = g_force_cfg;
   // K split over workgroups when the tiles alone leave most of the chip idle.  In the units above one microsecond is
   // about 5.6e8 / K; a split costs every workgroup its pipeline fill once more per part, and the second launch.
@@ -785,6 +796,7 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
     double t_best = t_single;
     for (int c = 0; c < n_cfg; ++c) {
       if (g_force_cfg >= 0 && c != g_force_cfg) continue;
+      if (!eligible(c) || c == kCfgPrefill) continue;
       if (fuse_wanted && kConfigs[c].W > 8) continue;
       for (int S = 2; S <= kGemmMaxKsplit; ++S) {
         if (g_force_ksplit > 1 && S != g_force_ksplit) continue;
@@ -827,8 +839,8 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
   auto launch_one = [&](int c, const GemmArgs& b) -> int {
 #define QERL_GEMM_CASE(idx, mt, nt, w) \
     if (c == idx) return launch_cfg<mt, nt, w>(b, st);
-    QERL_GEMM_CASE(0, 4, 2, 4) QERL_GEMM_CASE(1, 4, 2, 5) QERL_GEMM_CASE(2, 4, 2, 8)
-    QERL_GEMM_CASE(3, 4, 1, 4) QERL_GEMM_CASE(4, 4, 1, 8) QERL_GEMM_CASE(5, 4, 1, 10)
+    QERL_GEMM_CASE(0, 4, 1, 4) QERL_GEMM_CASE(1, 4, 1, 8) QERL_GEMM_CASE(kCfgTall, 4, 1, 10)
+    if (c == kCfgPrefill) return launch_prefill(b, st);
 #undef QERL_GEMM_CASE
     return QERL_ERR_SHAPE;
   };
@@ -843,6 +855,7 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
     int c_main = -1, c_rem = -1;
     GemmArgs main_args, rem_args;
     for (int c1 = 0; c1 < n_cfg; ++c1) {
+      if (!eligible(c1)) continue;
       const GemmConfig& g = kConfigs[c1];
       const int64_t bm = g.MT * 32, bn = (int64_t)g.W * g.NT * 32, tiles_per_block = (int64_t)g.W * g.NT;
       int64_t col_blocks = 0;

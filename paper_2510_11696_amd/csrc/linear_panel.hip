@@ -29,6 +29,7 @@
 //
 // Operand layouts and the packed tile format are described in linear_decode.hip.
 #include "linear.hpp"
+#include "lds_dma.hpp"
 
 namespace qerl {
 
@@ -38,28 +39,6 @@ constexpr int kPanelRing = 4;                    // weight stages in registers p
 template <int NT, int KW> constexpr int kPanelSlabs = KW == 2 ? 4 : (NT <= 2 ? 4 : (NT == 3 ? 3 : 2));
 template <int NT, int KW> constexpr int kPanelLds = kPanelSlabs<NT, KW> * NT * KW * 4096 > 3 * (16384 + NT * 8192) ? kPanelSlabs<NT, KW> * NT * KW * 4096
                                                                                                                       : 3 * (16384 + NT * 8192);
-
-typedef __attribute__((address_space(3))) u32x4 lds_chunk;
-
-// 16 bytes per lane from base + offset to LDS, the wave's 1 KiB at lds_bytes (uniform).  In assembly because the compiler,
-// which would see the builtin as a store to LDS, waits for ALL requests before every LDS read that follows; nothing it
-// tracks is written here, and its own counts only become stricter.  Waiting for the slab is panel_wait_barrier's.
-__device__ __forceinline__ void panel_request(uint32_t lds_bytes, const void* base, uint32_t offset) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_bytes), "v"(offset), "s"(base) : "memory");
-}
-
-// wait until at most N vector-memory requests of this wave are outstanding, then meet the workgroup
-template <int N>
-__device__ __forceinline__ void panel_wait_barrier() {
-  static_assert(N < 64, "vmcnt has six bits");
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");   // (its own reads of the slab that is refilled next are over)
-}
-__device__ __forceinline__ void panel_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
-// the same from a 64-bit address per lane
-__device__ __forceinline__ void panel_request64(uint32_t lds_bytes, const void* src) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_bytes), "v"(src) : "memory");
-}
 
 __device__ const u32x4 g_panel_zeros = {0u, 0u, 0u, 0u};   // what is beyond the end of a row of x or A
 
@@ -81,7 +60,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n32 = lane & 31, kg = lane >> 5;
   const int kgrp = wave & (KW - 1), rgrp = wave / KW;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_chunk*)xs;
+  const uint32_t lds0 = lds_address(xs);
 
   // ---- x: request i of a wave covers RPI whole slab rows
   const int row0 = wave * RPI + lane / RC;
@@ -97,7 +76,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     k = k < k_cap ? k : k_cap;                   // past the end the other operand is zero; any finite value will do
 #pragma unroll
     for (int i = 0; i < XI; ++i)
-      panel_request(lds0 + (uint32_t)((buf * kSlab + (i * 8 + wave) * 64) * 16), a.x, row_off[i] + k);
+      lds_request(lds0 + (uint32_t)((buf * kSlab + (i * 8 + wave) * 64) * 16), a.x, row_off[i] + k);
   };
   // x fragment of step j, token tile nt: row nt * 32 + n32, chunk 8 kgrp + 2 j + kg
   auto x_frag = [&](int buf, int j, int nt) {
@@ -117,7 +96,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
   // slabs may be overwritten once every wave has passed another barrier.
   float* red = reinterpret_cast<float*>(xs);
   auto add_slices = [&]() {
-    panel_wait_barrier<0>();                     // nothing is on its way to LDS any more
+    lds_wait_barrier<0>();                     // nothing is on its way to LDS any more
     float* mine = red + (rgrp * (KW / 2) + (kgrp & (KW / 2 - 1))) * (RT * NT * 1024) + lane * 4;
     auto put = [&]() {
 #pragma unroll
@@ -142,11 +121,11 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
           }
     };
     if (kgrp >= KW / 2) put();
-    panel_lds_barrier();
+    lds_barrier();
     if (kgrp < KW / 2) get(mine);
     if constexpr (KW == 4) {
       if (kgrp == 1) put();                      // the place it has just read, nobody else's
-      panel_lds_barrier();
+      lds_barrier();
       if (kgrp == 0) get(mine + RT * NT * 1024);
     }
   };
@@ -195,9 +174,9 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       const bool in = k < a.K;                   // past the end: zeros
       const uint32_t dst = lds0 + (uint32_t)((buf * kStage + wave * 64) * 16);
 #pragma unroll
-      for (int i = 0; i < NT; ++i) panel_request64(dst + (uint32_t)(i * 512 * 16), in ? (const void*)(xr[i] + k) : (const void*)&g_panel_zeros);
+      for (int i = 0; i < NT; ++i) lds_request64(dst + (uint32_t)(i * 512 * 16), in ? (const void*)(xr[i] + k) : (const void*)&g_panel_zeros);
 #pragma unroll
-      for (int t = 0; t < 2; ++t) panel_request64(dst + (uint32_t)((kXChunks + t * 512) * 16), in ? (const void*)(ar[t] + k) : (const void*)&g_panel_zeros);
+      for (int t = 0; t < 2; ++t) lds_request64(dst + (uint32_t)((kXChunks + t * 512) * 16), in ? (const void*)(ar[t] + k) : (const void*)&g_panel_zeros);
     };
     // wave -> rank tile t, token tile nt, steps sub, sub + KS, ... of the stage's eight (three token tiles: two waves idle)
     const int t = wave & 1, nt_raw = KS == 4 ? 0 : KS == 2 ? (wave >> 1) & 1 : wave >> 1, sub = KS == 4 ? wave >> 1 : KS == 2 ? wave >> 2 : 0;
@@ -212,7 +191,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     for (int p = 0; p < LB - 1; ++p) request(clamp(s0 + p), p);
     int buf = 0;
     for (int s = s0; s < s1; ++s) {
-      panel_wait_barrier<(LB - 2) * (NT + 2)>();
+      lds_wait_barrier<(LB - 2) * (NT + 2)>();
       int nbuf = buf + LB - 1;
       nbuf = nbuf >= LB ? nbuf - LB : nbuf;
       request(clamp(s + LB - 1), nbuf);
@@ -226,13 +205,13 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       buf = buf + 1 == LB ? 0 : buf + 1;
     }
     if constexpr (KS > 1) {                      // the shares of a tile, in order
-      panel_wait_barrier<0>();
+      lds_wait_barrier<0>();
       float* mine = red + wave * 1024 + lane;
       if (sub > 0) {
 #pragma unroll
         for (int i = 0; i < 16; ++i) mine[i * 64] = sum[i];
       }
-      panel_lds_barrier();
+      lds_barrier();
       if (sub == 0) {
 #pragma unroll
         for (int o = 1; o < KS; ++o)
@@ -240,7 +219,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
           for (int i = 0; i < 16; ++i) sum[i] += mine[o * (8 / KS) * 1024 + i * 64];
       }
     } else {
-      panel_wait_barrier<0>();                   // nothing may be on its way to LDS when the workgroup ends
+      lds_wait_barrier<0>();                   // nothing may be on its way to LDS when the workgroup ends
     }
     const int rt = blk * 2 + t;
     if (sub == 0 && !idle && rt < a.rank_tiles) {
@@ -295,7 +274,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     };
     clear();
     PanelWeights<RT> w[kPanelRing];
-    if (!first) panel_lds_barrier();             // the sums of the previous piece have been read
+    if (!first) lds_barrier();             // the sums of the previous piece have been read
     first = false;
 #pragma unroll
     for (int p = 0; p < XB - 1; ++p) request_x(clamp(s0 + p), p);
@@ -309,7 +288,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     auto stage = [&](int s, int ring, auto tail) {
       // behind slab s: the slabs of XB - 2 stages and, inside the loop, the weights of XB - 1 (two requests a row tile; in
       // the stages behind it the compiler drops requests whose data nothing uses)
-      panel_wait_barrier<(XB - 2) * XI + (decltype(tail)::value ? 0 : (XB - 1) * 2 * RT)>();
+      lds_wait_barrier<(XB - 2) * XI + (decltype(tail)::value ? 0 : (XB - 1) * 2 * RT)>();
       int nbuf = buf + XB - 1;
       nbuf = nbuf >= XB ? nbuf - XB : nbuf;
       request_x(clamp(s + XB - 1), nbuf);

@@ -1,0 +1,304 @@
+// Prefill-sized NVFP4 + LoRA linears: the bf16 MFMA GEMM for launches that fill the chip with 128 x 256 tiles.
+//
+//   y[m,n] = S32 * sum_k x[m,k] * (s[n,k/16] * e[n,k]) + lora_scale * sum_j t[m,j] * B[n,j]
+//                                                                    (Eq. 6, Eq. 2)
+// A workgroup of four waves owns 128 tokens x 256 output rows, a wave 64 of the rows for all 128 tokens: each x fragment
+// read from LDS feeds two matrix instructions, each weight is dequantised once per 128 tokens.  Stages of 64 inputs:
+// x slabs go from memory to LDS directly, three stages ahead, weights into a register ring four stages ahead.  The
+// workgroup meets once a stage, three quarters into it, when the next slab is needed: the first fragments of the next
+// stage are read, and its first weights converted, between the last quarter's matrix instructions, so that nothing
+// waits at a stage's start.  Two workgroups share a CU (64 KB of LDS and 256 registers per lane each) and run against each
+// other's waits; one of eight waves and 512 rows, which fetches a third less, is 5 % slower (27648 + 27648 rows, K = 5120,
+// 4096 tokens: 1780 us against 1700), one of four waves with 256 x 256, which converts half as often, 9 % (1855).
+// The output leaves through LDS in whole 128-byte rows.
+//
+// What bounds it, at that shape: the chip's power.  The matrix pipe is busy 61 % of the cycles at a clock of 1.9 GHz; leaving
+// out the conversions, the x requests, the weight requests or the fragment reads gains 9..12, 10, 7 and 6 % each, the matrix
+// instructions alone take 1380 us (1.68 PFLOP/s).  Against gemm32_kernel (registers between memory and LDS, a barrier that
+// drains them): 1903 -> 1700 us; 13824 rows, 2048 tokens 281 -> 246; 18944 + 18944 rows, K = 3584, 777 tokens 322 -> 214.
+//
+// LoRA and the operand layouts as in linear_gemm.hip.
+#include "linear.hpp"
+#include "lds_dma.hpp"
+
+namespace qerl {
+
+template <int RT> struct PrefillWeights { u32x4 c[RT]; uint32_t sc[RT]; };   // one stage of a wave: 64 inputs of its row tiles
+
+// TT token tiles and RT row tiles of 32 per wave, W waves
+template <int TT, int RT, int W>
+struct PrefillCfg {
+  static constexpr int kTokens = TT * 32, kRows = W * RT * 32;
+  static constexpr int kSlab = TT * 256;          // 16-byte chunks of a slab: TT * 32 rows x 8; chunk c of row r sits at r * 8 + (c ^ ((r >> 1) & 7))
+  static constexpr int XB = 4;                    // slabs in LDS
+  static constexpr int kLdsSlabs = XB * kSlab * 16;
+  static constexpr int kOutStride = RT * 64 + 16;  // bytes per token of a wave's output tile on its way out
+  static constexpr int kLdsOut = W * 64 * kOutStride;
+  static constexpr int kLds = kLdsSlabs > kLdsOut ? kLdsSlabs : kLdsOut;
+};
+
+template <int TT, int RT, int W>
+__global__ __launch_bounds__(W * 64, 2) void prefill_kernel(const GemmArgs a) {
+  using C = PrefillCfg<TT, RT, W>;
+  constexpr int XB = C::XB, kSlab = C::kSlab;
+  constexpr int XI = TT * 4 / W;                   // slab requests per wave and stage (8 rows each)
+  constexpr int R = 4;                             // weight stages in registers
+  extern __shared__ __attribute__((aligned(256))) u32x4 xs[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n32 = lane & 31, kg = lane >> 5;
+  const uint32_t lds0 = lds_address(xs);
+  const int bid = (int)blockIdx.x;
+  const int xcd = bid & 7, local = bid >> 3;
+  // XCD-aware map: workgroup ids go round-robin to the 8 XCDs, each of which takes a contiguous eighth of the column blocks
+  const int nb_local = local % a.nblk_per_xcd, mb = local / a.nblk_per_xcd;
+  const int nb = xcd * a.nblk_per_xcd + nb_local;
+  if (nb >= a.n_blocks) return;
+  const int64_t m0 = (int64_t)mb * C::kTokens;
+  int mi = 0;
+#pragma unroll
+  for (int i = 1; i < kMaxGroup; ++i) mi = (i < a.m_n && nb >= a.m[i].block_begin) ? i : mi;
+  const GemmMember& mem = a.m[__builtin_amdgcn_readfirstlane(mi)];
+  const int rt0 = ((nb - mem.block_begin) * W + wave) * RT;
+
+  // ---- x (or the LoRA columns): rows m0 .. of a row-major matrix of `cols` columns
+  struct Source { const uint8_t* base; uint32_t k_cap; uint32_t row_off[XI]; };
+  const int row0 = wave * 8 + (lane >> 3);
+  const uint32_t col_bytes = (uint32_t)(((lane & 7) ^ ((row0 >> 1) & 7)) * 16);
+  auto source = [&](const uint16_t* p, int64_t ld, int64_t cols) {
+    Source s;
+    s.base = uniform_pointer(p + m0 * ld);
+    s.k_cap = (uint32_t)(cols * 2 - 16);
+#pragma unroll
+    for (int i = 0; i < XI; ++i) {
+      int64_t m = row0 + 8 * W * i;
+      m = m0 + m < a.M ? m : a.M - 1 - m0;
+      s.row_off[i] = (uint32_t)(m * ld * 2) + col_bytes;
+    }
+    return s;
+  };
+  auto request = [&](const Source& s, int stage, int buf) {
+    const uint32_t dst = lds0 + (uint32_t)((buf * kSlab + wave * 64) * 16);
+    if ((uint32_t)stage * 128u + 112u <= s.k_cap) {
+      const uint8_t* base = s.base + (uint32_t)stage * 128u;
+#pragma unroll
+      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), base, s.row_off[i]);
+    } else {                                       // the last stage of a K that is no multiple of 64
+      const uint32_t k = (uint32_t)stage * 128u + col_bytes, over = k > s.k_cap ? k - s.k_cap : 0u;   // past the end the other operand is zero; any finite value will do
+      const uint8_t* base = s.base + (uint32_t)stage * 128u;
+#pragma unroll
+      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), base - 128, s.row_off[i] + 128u - over);
+    }
+  };
+  const Source sx = source(a.x, a.ldx, a.K);
+  auto request_x = [&](int stage, int buf) { request(sx, stage, buf); };
+  const int frag = n32 * 8, sw = (n32 >> 1) & 7;
+  auto x_frag = [&](int buf, int j, int tt) {
+    return __builtin_bit_cast(bf16x8, xs[buf * kSlab + (frag + ((2 * j + kg) ^ sw)) + tt * 256]);
+  };
+  // ---- weights
+  const uint8_t* wbase[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    int tile = rt0 + t;
+    tile = tile < mem.n_tiles ? tile : mem.n_tiles - 1;
+    wbase[t] = mem.packed + (int64_t)tile * a.k_tiles * kPackTileBytes;
+  }
+  auto load_w = [&](PrefillWeights<RT>& w, int stage) {
+    const uint32_t c_off = (uint32_t)((stage & 1) * 1024 + lane * 16), s_off = (uint32_t)(2048 + (stage & 1) * 4 + n32 * 8);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const uint8_t* p = wbase[t] + (int64_t)(stage >> 1) * kPackTileBytes;
+      w.c[t] = *reinterpret_cast<const u32x4*>(p + c_off);
+      w.sc[t] = *reinterpret_cast<const uint32_t*>(p + s_off);
+    }
+  };
+  f32x16 acc[RT][TT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][tt][i] = 0.f;
+
+  const int n_st = (int)((a.K + 63) >> 6), last = n_st - 1;
+  auto clamp = [&](int s) { return s < last ? s : last; };
+  PrefillWeights<RT> w[R];
+#pragma unroll
+  for (int p = 0; p < XB - 1; ++p) request_x(clamp(p), p);
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int p = 0; p < R; ++p) load_w(w[p], clamp(p));
+  lds_wait_barrier<(XB - 2) * XI>();
+  bf16x8 xf[TT], wf[RT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) xf[tt] = x_frag(0, 0, tt);
+#pragma unroll
+  for (int t = 0; t < RT; ++t) wf[t] = dequant8_bf16(w[0].c[t][0], e4m3_byte_f32(w[0].sc[t], 0));
+  // Stage s, its slab in buffer `buf`: on entry the fragments of its first step are in registers.  Between its third and
+  // fourth step the workgroup meets with slab s + 1 in LDS, whose first fragments are read during the fourth; slab s + XB - 1
+  // then goes into the buffer of s - 1.
+  int buf = 0;
+  auto stage = [&](int s, auto ring_c, auto tail) {
+    constexpr int ring = decltype(ring_c)::value;
+    const int next = buf + 1 == XB ? 0 : buf + 1, before = buf == 0 ? XB - 1 : buf - 1;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j == 3) {
+        __builtin_amdgcn_sched_barrier(0);
+        lds_wait_barrier<(XB - 3) * XI + (decltype(tail)::value ? 0 : (XB - 2) * 2 * RT)>();
+        request_x(clamp(s + XB - 1), before);
+        load_w(w[ring], clamp(s + R));             // behind the slab's requests: the compiler, which does not count those, then waits for less
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const PrefillWeights<RT>& wr = w[j < 3 ? ring : (ring + 1) % R];
+      bf16x8 wn[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) wn[t] = dequant8_bf16(wr.c[t][(j + 1) & 3], e4m3_byte_f32(wr.sc[t], (j + 1) & 3));
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) acc[t][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t], xf[tt], acc[t][tt], 0, 0, 0);
+        xf[tt] = j < 3 ? x_frag(buf, j + 1, tt) : x_frag(next, 0, tt);
+      }
+#pragma unroll
+      for (int t = 0; t < RT; ++t) wf[t] = wn[t];
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, (19 + TT - 1) / TT, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    buf = next;
+  };
+  int s = 0;
+  for (; s + R <= n_st; s += R) {
+    stage(s, std::integral_constant<int, 0>{}, std::false_type{});
+    stage(s + 1, std::integral_constant<int, 1>{}, std::false_type{});
+    stage(s + 2, std::integral_constant<int, 2>{}, std::false_type{});
+    stage(s + 3, std::integral_constant<int, 3>{}, std::false_type{});
+  }
+  if (s < n_st) {
+    stage(s, std::integral_constant<int, 0>{}, std::true_type{});
+    if (s + 1 < n_st) {
+      stage(s + 1, std::integral_constant<int, 1>{}, std::true_type{});
+      if (s + 2 < n_st) stage(s + 2, std::integral_constant<int, 2>{}, std::true_type{});
+    }
+  }
+  lds_wait_barrier<0>();                           // nothing on its way to LDS, nobody reading
+
+  // ---- LoRA: 3r more columns [hi | mid | lo] . [B ; B ; B]^T, XB slabs of 64 at a time
+  if (mem.ext_stages > 0) {
+    const Source st = source(mem.ts, mem.ts_ld, mem.ts_ld);
+    const uint16_t* brow[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      int64_t row = (int64_t)(rt0 + t) * 32 + n32;
+      row = row < mem.N ? row : mem.N - 1;
+      brow[t] = mem.B + row * mem.r;
+    }
+    for (int e0 = 0; e0 < mem.ext_stages; e0 += XB) {
+      const int n_e = mem.ext_stages - e0 < XB ? mem.ext_stages - e0 : XB;
+      for (int e = 0; e < n_e; ++e) request(st, e0 + e, e);
+      lds_wait_barrier<0>();
+      for (int e = 0; e < n_e; ++e) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int c = (e0 + e) * 64 + 16 * j + 8 * kg;
+          bf16x8 bf[RT];
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            u32x4 b = {0u, 0u, 0u, 0u};
+            if (c < 3 * mem.r) b = *reinterpret_cast<const u32x4*>(brow[t] + c % mem.r);
+            bf[t] = __builtin_bit_cast(bf16x8, b);
+          }
+#pragma unroll
+          for (int tt = 0; tt < TT; ++tt) {
+            const bf16x8 x1 = x_frag(e, j, tt);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) acc[t][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[t], x1, acc[t][tt], 0, 0, 0);
+          }
+        }
+      }
+      lds_wait_barrier<0>();
+    }
+  }
+
+  // ---- out: 64 tokens at a time through the wave's own part of LDS, then whole rows of RT * 64 bytes
+  const float S32 = *mem.tensor_scale;
+  uint8_t* out = reinterpret_cast<uint8_t*>(xs) + wave * 64 * C::kOutStride;
+  const int64_t n0 = (int64_t)rt0 * 32;
+  if (n0 >= mem.N) return;                         // a wave beyond the member's rows
+  const bool vec = aligned_dev(mem.y, 16) && mem.ldy % 8 == 0;
+#pragma unroll
+  for (int half = 0; half < TT / 2; ++half) {
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16& v = acc[t][half * 2 + tt];
+          float o[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            o[e] = v[4 * q + e] * S32;
+            if (mem.bias) {
+              const int64_t n = n0 + t * 32 + 8 * q + 4 * kg + e;
+              o[e] += bf16_bits_to_f32(mem.bias[n < mem.N ? n : mem.N - 1]);
+            }
+          }
+          *reinterpret_cast<u32x2*>(out + (tt * 32 + n32) * C::kOutStride + t * 64 + q * 16 + kg * 8) = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
+        }
+    __builtin_amdgcn_wave_barrier();
+    constexpr int CH = RT * 4, RPI = 64 / CH;      // 16-byte chunks of a row, rows per instruction
+#pragma unroll 4
+    for (int i = 0; i < 64 / RPI; ++i) {
+      const int row = i * RPI + lane / CH, ch = lane % CH;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(out + row * C::kOutStride + ch * 16);
+      const int64_t m = m0 + half * 64 + row, n = n0 + ch * 8;
+      if (m < a.M) {
+        uint16_t* dst = mem.y + m * mem.ldy + n;
+        if (vec && n + 8 <= mem.N) {
+          *reinterpret_cast<u32x4*>(dst) = v;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < mem.N) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// 32-bit offsets inside a token block
+bool prefill_takes(const GemmArgs& a) {
+  return !a.transposed && a.ldx < (int64_t)1 << 23 && a.K >= 16 && a.K < (int64_t)1 << 30;
+}
+
+template <int TT, int RT, int W>
+static int launch_prefill_t(const GemmArgs& a0, hipStream_t st) {
+  using C = PrefillCfg<TT, RT, W>;
+  GemmArgs a = a0;
+  a.n_blocks = 0;
+  for (int i = 0; i < a.m_n; ++i) {
+    a.m[i].block_begin = a.n_blocks;
+    a.n_blocks += (int)ceil_div(a.m[i].n_tiles, W * RT);
+  }
+  a.nblk_per_xcd = (int)ceil_div(a.n_blocks, 8);
+  prefill_kernel<TT, RT, W><<<dim3((unsigned)(8 * a.nblk_per_xcd * ceil_div(a.M, C::kTokens))), dim3(W * 64), C::kLds, st>>>(a);
+  return launch_status();
+}
+
+int launch_prefill(const GemmArgs& a, hipStream_t st) {
+  if (!prefill_takes(a)) return QERL_ERR_SHAPE;
+  return launch_prefill_t<4, 2, 4>(a, st);
+}
+
+}  // namespace qerl
