@@ -215,7 +215,7 @@ extern "C" int nvfp4_lora_linear(const void* x, int64_t M, int64_t K, int64_t ld
 
 namespace qerl {
 static bool g_use_stream = true;
-// From here to 128 tokens linear_panel.hip takes the packed linears.  Whole layers, us per layer, the 1..16-token kernels / the
+// From here to 128 tokens linear_panel.hip takes the packed linears (to kPanelMaxTokens where it is estimated faster than the GEMM).  Whole layers, us per layer, the 1..16-token kernels / the
 // panel kernels: 9 tokens 106 / 93 (7B shapes), 125 / 101 (14B), 140 / 131 (32B); 8 tokens 91 / 93, 108 / 101, 122 / 130 (the
 // decode kernels' cost follows the tokens in steps of eight, the panel kernels' in steps of 32).
 constexpr int64_t kPanelMinTokens = 9;
@@ -267,49 +267,11 @@ static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
   return launch_stream(a, lds, MR, st);
 }
 
-// 9..128 tokens, one linear or a group reading the same x, in two launches (linear_panel.hip); where the sums of all rows do
-// not fit the workspace's area, the rows in several parts of two launches each.  act != null: members 0 and 1 are
-// gate_proj and up_proj and act = SiLU(gate) (.) up is stored instead of their outputs.
-// QERL_ERR_SHAPE: not a shape for it (nothing has been launched).
-static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n, uint8_t* ws,
-                       const WorkspaceLayout& L, uint16_t* act, hipStream_t st) {
-  const int64_t k_tiles = ceil_div(K, kPackTileK);
-  auto part = [&](int c, int parts, PanelArgs& a) {
-    a = PanelArgs{};
-    a.x = x; a.ldx = ldx; a.M = (int)M; a.K = K; a.n_members = n;
-    for (int i = 0; i < n; ++i) {
-      PanelMember& m = a.mem[i];
-      const int64_t tiles = ceil_div(d[i].N, kPackTileRows), t0 = tiles * c / parts, t1 = tiles * (c + 1) / parts, row0 = t0 * kPackTileRows;
-      m.packed = (const uint8_t*)d[i].packed + t0 * k_tiles * kPackTileBytes; m.tensor_scale = d[i].tensor_scale;
-      m.N = (t1 * kPackTileRows < d[i].N ? t1 * kPackTileRows : d[i].N) - row0;
-      m.A = (const uint16_t*)d[i].A_bf16; m.r = (int)d[i].r; m.lora_scale = d[i].lora_scale;
-      m.B = d[i].r > 0 ? (const uint16_t*)d[i].B_bf16 + row0 * d[i].r : nullptr;
-      m.bias = d[i].bias_bf16 ? (const uint16_t*)d[i].bias_bf16 + row0 : nullptr;
-      m.y = d[i].y_bf16 ? (uint16_t*)d[i].y_bf16 + row0 : nullptr; m.ldy = d[i].ldy;
-      if (act && i == 0) { a.pairs = 1; a.act = act + row0; a.ld_act = d[0].N; }
-    }
-    return plan_panel(a, (float*)(ws + L.partial_off), L.total - L.partial_off);
-  };
-  PanelArgs a;
-  for (int parts = 1; parts <= 64; parts *= 2) {
-    bool fits = true;
-    for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
-    if (!fits) continue;
-    for (int c = 0; c < parts; ++c) {
-      int rc = part(c, parts, a);
-      if (rc == QERL_OK) rc = launch_panel(a, st);
-      if (rc != QERL_OK) return rc;
-    }
-    return QERL_OK;
-  }
-  return QERL_ERR_SHAPE;
-}
-
 // The GEMM launch and the LoRA down-projections it depends on (dn: the group form, tiles rank tiles; g_n == 0: none).
 // launch_gemm either takes the down-projections into its own launch (few tokens) or runs them first; the scratch
 // serves the down-projection's K-parts from its front and the GEMM's own K-parts from kFusedDownBytes on (inside
 // one launch both are alive at once, and the down-projection stays below that mark).
-static int gemm_with_down(GemmArgs& g, GemmArgs& dn, int tiles, int64_t n_sum, uint8_t* ws, const WorkspaceLayout& L, hipStream_t st) {
+static int gemm_with_down(GemmArgs& g, GemmArgs& dn, int tiles, int64_t n_sum, uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, double* estimate_us) {
   if (dn.g_n > 0) {
     dn.g_tile0[dn.g_n] = tiles;
     g.g_n = dn.g_n;
@@ -324,13 +286,14 @@ static int gemm_with_down(GemmArgs& g, GemmArgs& dn, int tiles, int64_t n_sum, u
     g.n_prod = -1;                                                                           // not run yet: the launcher's to place
   }
   g.kpartial = (float*)(ws + L.partial_off + kFusedDownBytes); g.kpartial_bytes = gemm_split_bytes(g.M, n_sum);
+  g.estimate_us = estimate_us;
   return launch_gemm(g, st);
 }
 
 // More than 128 tokens: one launch of the LoRA down-projection for all adapters of the group, then
 // one GEMM launch whose column blocks run over all members (k and v alone would fill half the chip).
 static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
-                      uint8_t* ws, const WorkspaceLayout& L, hipStream_t st) {
+                      uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, double* estimate_us = nullptr) {
   GemmArgs g{};
   g.x = x; g.ldx = ldx; g.M = M; g.K = K; g.k_tiles = ceil_div(K, kPackTileK); g.m_n = n;
   GemmArgs dn{};
@@ -354,7 +317,52 @@ static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, cons
   }
   int64_t n_sum = 0;
   for (int i = 0; i < n; ++i) n_sum += d[i].N;
-  return gemm_with_down(g, dn, tiles, n_sum, ws, L, st);
+  return gemm_with_down(g, dn, tiles, n_sum, ws, L, st, estimate_us);
+}
+// 9..128 tokens, one linear or a group reading the same x, in two launches (linear_panel.hip); where the sums of all rows do
+// not fit the workspace's area, the rows in several parts of two launches each.  act != null: members 0 and 1 are
+// gate_proj and up_proj and act = SiLU(gate) (.) up is stored instead of their outputs.
+// Beyond 128 tokens the same kernels take several token blocks, where they are estimated faster than the GEMM: launches of few
+// rows, whose tiles do not fill the chip (5120 x 5120, r = 64, 256 tokens 49 -> 30 us, 3584 x 18944, r = 32, 777 tokens 216 -> 135).
+// QERL_ERR_SHAPE: not a shape for it (nothing has been launched).
+static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n, uint8_t* ws,
+                       const WorkspaceLayout& L, uint16_t* act, hipStream_t st) {
+  const int64_t k_tiles = ceil_div(K, kPackTileK);
+  auto part = [&](int c, int parts, PanelArgs& a) {
+    a = PanelArgs{};
+    a.x = x; a.ldx = ldx; a.M = (int)M; a.K = K; a.n_members = n;
+    for (int i = 0; i < n; ++i) {
+      PanelMember& m = a.mem[i];
+      const int64_t tiles = ceil_div(d[i].N, kPackTileRows), t0 = tiles * c / parts, t1 = tiles * (c + 1) / parts, row0 = t0 * kPackTileRows;
+      m.packed = (const uint8_t*)d[i].packed + t0 * k_tiles * kPackTileBytes; m.tensor_scale = d[i].tensor_scale;
+      m.N = (t1 * kPackTileRows < d[i].N ? t1 * kPackTileRows : d[i].N) - row0;
+      m.A = (const uint16_t*)d[i].A_bf16; m.r = (int)d[i].r; m.lora_scale = d[i].lora_scale;
+      m.B = d[i].r > 0 ? (const uint16_t*)d[i].B_bf16 + row0 * d[i].r : nullptr;
+      m.bias = d[i].bias_bf16 ? (const uint16_t*)d[i].bias_bf16 + row0 : nullptr;
+      m.y = d[i].y_bf16 ? (uint16_t*)d[i].y_bf16 + row0 : nullptr; m.ldy = d[i].ldy;
+      if (act && i == 0) { a.pairs = 1; a.act = act + row0; a.ld_act = d[0].N; }
+    }
+    return plan_panel(a, (float*)(ws + L.partial_off), L.total - L.partial_off);
+  };
+  PanelArgs a;
+  if (M > 128) {
+    double gemm_us = 0;
+    if (part(0, 1, a) != QERL_OK || gemm_group(x, M, K, ldx, d, n, ws, L, st, &gemm_us) != QERL_OK) return QERL_ERR_SHAPE;
+    if (act) gemm_us += 5.0 + 6.0 * (double)M * (double)d[0].N / 5.0e6;   // and the elementwise pass
+    return panel_estimate_us(a) < gemm_us ? launch_panel(a, st) : QERL_ERR_SHAPE;
+  }
+  for (int parts = 1; parts <= 64; parts *= 2) {
+    bool fits = true;
+    for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
+    if (!fits) continue;
+    for (int c = 0; c < parts; ++c) {
+      int rc = part(c, parts, a);
+      if (rc == QERL_OK) rc = launch_panel(a, st);
+      if (rc != QERL_OK) return rc;
+    }
+    return QERL_OK;
+  }
+  return QERL_ERR_SHAPE;
 }
 }  // namespace qerl
 
@@ -393,7 +401,7 @@ static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, c
   if (!aligned(x, 16) || ldx % 8 != 0) return QERL_ERR_ALIGN;
   const WorkspaceLayout L = workspace_layout(M, n_sum, K, r_sum);
   if (!workspace || !aligned(workspace, 256) || workspace_bytes < L.total) return QERL_ERR_WORKSPACE;
-  if (lora_ok && M >= kPanelMinTokens && M <= 128 && (M > 16 || !t_given)) {
+  if (lora_ok && M >= kPanelMinTokens && M <= kPanelMaxTokens && (M > 16 || !t_given)) {
     const int rc = panel_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, act, (hipStream_t)stream);
     if (rc != QERL_ERR_SHAPE) return rc;
   }
@@ -495,7 +503,7 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
   uint32_t* partial = (uint32_t*)(ws + L.partial_off);
 
   const bool lora_gemm_ok = r == 0 || (r % 8 == 0 && aligned(A, 16) && aligned(B, 16));
-  if (M >= kPanelMinTokens && M <= 128 && lora_gemm_ok) {
+  if (M >= kPanelMinTokens && M <= kPanelMaxTokens && lora_gemm_ok) {
     qerl_linear_desc d{packed, tensor_scale, N, A, B, r, lora_scale, y, ldy, nullptr, bias};
     const int rc = panel_group(c.x, M, K, ldx, &d, 1, ws, L, nullptr, c.st);
     if (rc != QERL_ERR_SHAPE) return rc;
@@ -517,7 +525,7 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
     }
     g.N = N; g.packed = (const uint8_t*)packed; g.n_tiles = (int)ceil_div(N, 32);
     g.B = c.B; g.y = c.y; g.ldy = ldy; g.bias = (const uint16_t*)bias;
-    return gemm_with_down(g, dn, tiles, N, ws, L, c.st);
+    return gemm_with_down(g, dn, tiles, N, ws, L, c.st, nullptr);
   }
 
   if (g_use_stream && M <= 16 && (r == 0 || (r <= 64 && r % 8 == 0 && aligned(A, 16) && aligned(B, 16)))) {

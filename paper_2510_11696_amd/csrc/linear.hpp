@@ -144,6 +144,7 @@ struct GemmArgs {
   const uint16_t* bias;                                                     // [N] bf16 or null
   uint16_t* y; int64_t ldy;
   int n_tiles; int n_blocks; int nblk_per_xcd;
+  double* estimate_us;                                                      // not null: nothing is launched, the launcher's estimate of the time goes here
   int m_n; GemmMember m[kMaxGroup];                                         // the main launch's members (m_n == 0: one, from the fields above)
   int transposed;                                                           // packed is in nvfp4_prepack_t's order: K counts rows of W, N its columns
   // transposed launches only: the contraction runs over seg_n segments one after the other -- the members of a group
@@ -181,6 +182,7 @@ constexpr size_t kDownExchangeBytes = (size_t)16 << 20;   // the K-parts' partia
 int launch_lora_down_gemm(const GemmArgs& a, hipStream_t st);
 
 // ---- 9..128 tokens: matrix instructions over units of rows, sums in the workspace, a second launch (linear_panel.hip) ----
+constexpr int kPanelMaxTokens = 1024;
 constexpr size_t kPanelSumsCap = (size_t)32 << 20, kPanelTBytes = (size_t)512 << 10;   // most workspace bytes for the sums of W's and A's rows
 struct PanelMember {
   const uint8_t* packed; const float* tensor_scale; int64_t N;
@@ -194,14 +196,15 @@ struct PanelArgs {
   const uint16_t* x; int64_t ldx; int M; int64_t K;
   int n_members; PanelMember mem[kMaxGroup];                                // unused entries: unit_begin = INT_MAX, r = 0
   int pairs; uint16_t* act; int64_t ld_act;                                 // members 0, 1 are gate_proj, up_proj: act = SiLU(gate) (.) up instead of their outputs
-  // the plan: token tiles, K-tiles; K-slices of a workgroup, row tiles of a wave and of a unit (and its log2), units, stages of 64 KW inputs; A's rank tiles, K-parts, workgroups
-  int NT; int k_tiles; int KW; int RT; int unit_tiles; int unit_shift; int units; int stages; int rank_tiles; int t_parts; int n_lora;
+  // the plan: token blocks of NT tiles, K-tiles; K-slices of a workgroup, row tiles of a wave and of a unit (and its log2), units (row units x token blocks), stages of 64 KW inputs; A's rank tiles, K-parts, workgroups
+  int tbs; int NT; int k_tiles; int KW; int RT; int unit_tiles; int unit_shift; int units; int stages; int rank_tiles; int t_parts; int n_lora;
   // workgroups over the units' stages: every unit in `split` pieces, or (0) `per` stages each, the first `rem` one more
   int n_main; int split; int per; int rem; uint32_t per_inv; uint32_t per1_inv;   // 2^32 / per, 2^32 / (per + 1), rounded up
-  float* sums; float* t_sums;                                               // [slot][unit_tiles][NT][1024]; [t_parts][rank_tiles][NT][1024]
+  float* sums; float* t_sums;                                               // [slot][unit_tiles][NT][1024]; [t_parts][rank_tiles][tbs * NT][1024]
 };
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes);
 int launch_panel(const PanelArgs& a, hipStream_t st);
+double panel_estimate_us(const PanelArgs& a);
 // gate_proj and up_proj as nvfp4_lora_linear_packed_group, with act[M, N] = bf16(bf16(SiLU(gate)) * up) in place of their
 // outputs; kNoFusedAct (nothing launched) where the shape has no kernel for it (api.hip)
 constexpr int kNoFusedAct = 1;

@@ -809,13 +809,16 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
         if (t < t_best || (g_force_ksplit > 1 && a.ksplit == 1)) { t_best = t; best = c; a.ksplit = S; }
       }
     }
+    t_single = t_best;
     if (a.ksplit > 1) {
       a.kp_ld = ld;
       int64_t col = 0;
       for (int i = 0; i < a.m_n; ++i) { a.m[i].col0 = col; col += (a.m[i].N + 3) / 4 * 4; }
     }
   }
-  if (a.n_prod < 0) {
+  const bool dry = a.estimate_us != nullptr;       // only the time is asked for
+  double t_final = t_single;                       // (t_single: one launch, K split or not)
+  if (a.n_prod < 0 && !dry) {
     // measured on 32B shapes at 128 and 256 tokens: worth it where K is split because the tiles alone leave the chip
     // idle (q + k + v 69 -> 49 us, o 45 -> 37, down 92 -> 82 at 128 tokens); a launch that fills the chip by itself
     // (gate + up) only loses its first slots to the producers (193 -> 240 us at 256 tokens)
@@ -848,7 +851,7 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
   // the remaining columns as a launch of their own in whatever shape suits them (smaller tiles fill the chip
   // where a part round of large ones would leave CUs idle).  A member cut by the boundary appears in both
   // launches; the second sees it from a row-tile offset on (the packed tiles of 32 rows are contiguous per row tile).
-  if (g_split && g_force_cfg < 0 && a.ksplit == 1 && a.n_prod == 0) {
+  if (g_split && g_force_cfg < 0 && a.ksplit == 1 && (a.n_prod == 0 || dry)) {
     // ~15 us in the units above: the gap between the launches, the second one's fill and drain
     const double overhead = 8.4e9 / (double)a.K;
     double t_split = 0.97 * t_single;   // what a pair of launches has to beat
@@ -892,10 +895,16 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
       const double t = cfg_time(c1, ma.m, ma.m_n) + t_rem + overhead;
       if (t < t_split) { t_split = t; c_main = c1; c_rem = cr; main_args = ma; rem_args = ra; }
     }
-    if (c_main >= 0) {
+    if (c_main >= 0 && dry) t_final = t_split;
+    if (c_main >= 0 && !dry) {
       const int rc = launch_one(c_main, main_args);
       return rc != QERL_OK ? rc : launch_one(c_rem, rem_args);
     }
+  }
+  if (dry) {
+    // the launch's fill, drain and gap, and the down-projections (14 us for one rank tile, 21 for three at 777 tokens)
+    *a.estimate_us = t_final * (double)a.K / 5.6e8 + 6.0 + (a.g_n > 0 ? 11.0 + 3.0 * a.g_tile0[a.g_n] : 0.0);
+    return QERL_OK;
   }
   return launch_one(best, a);
 }

@@ -66,11 +66,13 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
   const int row0 = wave * RPI + lane / RC;
   const uint32_t col_bytes = (uint32_t)(((lane % RC) ^ (row0 & 15)) * 16), k_cap = (uint32_t)(a.K * 2 - 16);
   uint32_t row_off[XI];
+  auto set_tokens = [&](int tb) {
 #pragma unroll
-  for (int i = 0; i < XI; ++i) {
-    const int m = row0 + 8 * RPI * i;
-    row_off[i] = (uint32_t)(m < a.M ? m : a.M - 1) * (uint32_t)(a.ldx * 2);
-  }
+    for (int i = 0; i < XI; ++i) {
+      const int m = tb * (NT * 32) + row0 + 8 * RPI * i;
+      row_off[i] = (uint32_t)(m < a.M ? m : a.M - 1) * (uint32_t)(a.ldx * 2);
+    }
+  };
   auto request_x = [&](int stage, int buf) {
     uint32_t k = (uint32_t)stage * (uint32_t)(RC * 16) + col_bytes;
     k = k < k_cap ? k : k_cap;                   // past the end the other operand is zero; any finite value will do
@@ -146,14 +148,15 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     constexpr int LB = 3;                        // stages in LDS
     constexpr int kXChunks = NT * 512, kStage = kXChunks + 1024;   // 16-byte chunks: x, then 64 rows of A; chunk c of row r sits at r * 16 + (c ^ (r & 15))
     constexpr int KS = NT == 1 ? 4 : NT == 2 ? 2 : 1;               // waves that share an output tile
-    const int blk = (int)blockIdx.x / a.t_parts, part = (int)blockIdx.x % a.t_parts;
+    const int id = (int)blockIdx.x / a.tbs, tb = (int)blockIdx.x % a.tbs;
+    const int blk = id / a.t_parts, part = id % a.t_parts;
     const int n_st = (int)((a.K + 127) >> 7);
     const int s0 = (int)((int64_t)part * n_st / a.t_parts), s1 = (int)((int64_t)(part + 1) * n_st / a.t_parts);
     const int lrow = wave * 4 + (lane >> 4), lcol = ((lane & 15) ^ (lrow & 15)) * 8;
     const uint16_t* xr[NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-      const int m = lrow + 32 * i;
+      const int m = tb * (NT * 32) + lrow + 32 * i;
       xr[i] = a.x + (int64_t)(m < a.M ? m : a.M - 1) * a.ldx;
     }
     const uint16_t* ar[2];
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     }
     const int rt = blk * 2 + t;
     if (sub == 0 && !idle && rt < a.rank_tiles) {
-      float* p = a.t_sums + (((int64_t)part * a.rank_tiles + rt) * NT + nt) * 1024 + lane * 4;
+      float* p = a.t_sums + (((int64_t)part * a.rank_tiles + rt) * (a.tbs * NT) + tb * NT + nt) * 1024 + lane * 4;
 #pragma unroll
       for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(p + q * 256) = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
     }
@@ -248,14 +251,16 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
     const int s0 = lo - u * a.stages;
     const int s1 = s0 + (hi - lo) < a.stages ? s0 + (hi - lo) : a.stages;
     lo += s1 - s0;
+    const int ru = a.tbs == 1 ? u : u / a.tbs;   // unit of rows; token block
+    set_tokens(u - ru * a.tbs);
     int mi = 0;
 #pragma unroll
-    for (int i = 1; i < kMaxGroup; ++i) mi = u >= a.mem[i].unit_begin ? i : mi;
+    for (int i = 1; i < kMaxGroup; ++i) mi = ru >= a.mem[i].unit_begin ? i : mi;
     const PanelMember& mem = a.mem[__builtin_amdgcn_readfirstlane(mi)];
     const uint8_t* wbase[RT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      int tile = (u - mem.unit_begin) * kUnitTiles + rgrp * RT + t;
+      int tile = (ru - mem.unit_begin) * kUnitTiles + rgrp * RT + t;
       tile = tile < mem.n_tiles ? tile : mem.n_tiles - 1;     // repeated; its slot is not read
       wbase[t] = mem.packed + (int64_t)tile * a.k_tiles * kPackTileBytes;
     }
@@ -364,7 +369,8 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
   __shared__ __attribute__((aligned(16))) uint16_t tl[NM][3][32 * kFinishStride];
   const int tid = threadIdx.x, lane = tid & 63, n32 = lane & 31, kg = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = blockIdx.y, NT = a.NT;
+  const int NT = a.NT, nt_all = blockIdx.y;
+  const int tb = a.tbs == 1 ? 0 : nt_all / NT, nt = nt_all - tb * NT;   // token block, tile in it
   const PanelMember& m0 = a.mem[PAIR ? 0 : (int)blockIdx.z];
   const int n_tiles = m0.n_tiles;
   if ((int)blockIdx.x * 8 >= n_tiles) return;    // (members of one launch differ in width)
@@ -376,12 +382,12 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
 
   // t: wave (h, q4) owns ranks 8 q4 + 4 (lane / 32) + 0..3 of rank tile 2 chunk + h, token lane % 32
   const int h = wave >> 2, q4 = wave & 3;
-  const int64_t t_stride = (int64_t)a.rank_tiles * NT * 1024;
+  const int64_t t_stride = (int64_t)a.rank_tiles * (a.tbs * NT) * 1024;
   f32x4 tp[NM][TB];
   auto load_t = [&](int i, const PanelMember& m, int c0) {
     int q = m.rt_begin + (c0 >> 5) + h;
     q = q < a.rank_tiles ? q : 0;
-    const float* p = a.t_sums + ((int64_t)q * NT + nt) * 1024 + q4 * 256 + lane * 4;
+    const float* p = a.t_sums + ((int64_t)q * (a.tbs * NT) + nt_all) * 1024 + q4 * 256 + lane * 4;
 #pragma unroll
     for (int z = 0; z < TB; ++z) tp[i][z] = *reinterpret_cast<const f32x4*>(p + (z < a.t_parts ? z : 0) * t_stride);
   };
@@ -426,7 +432,7 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
   for (int i = 0; i < NM; ++i) {
     const PanelMember& m = PAIR ? a.mem[i] : m0;
     // the pieces of this row tile's unit, in K order
-    const int ul = rt_ld >> unit_shift, u = m.unit_begin + ul;
+    const int ul = rt_ld >> unit_shift, u = (m.unit_begin + ul) * a.tbs + tb;
     // split == 0: the workgroups that own the unit's first and last stage.  A stage x belongs to x / (per + 1) below
     // `big`, counted in pieces of `per` from there on
     const int big = a.rem * (a.per + 1);
@@ -518,7 +524,7 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
         }
     }
   }
-  const int tok = nt * 32 + n32;
+  const int tok = nt_all * 32 + n32;
   if (rt >= n_tiles || tok >= a.M) return;
   uint16_t* dst = PAIR ? a.act + (int64_t)tok * a.ld_act : m0.y + (int64_t)tok * m0.ldy;
   const int64_t n0 = (int64_t)rt * 32 + 4 * kg;
@@ -546,9 +552,10 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
 // Fills in the plan: token tiles, units, workgroups and the places of the sums in `area` bytes of workspace.
 // QERL_ERR_SHAPE: not a shape for these kernels (the sums do not fit the area, or x's rows are too far apart).
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
-  if (a.M < 1 || a.M > 128 || a.K < 16 || a.K % 16 != 0 || a.n_members < 1 || a.n_members > kMaxGroup) return QERL_ERR_SHAPE;
+  if (a.M < 1 || a.M > kPanelMaxTokens || a.K < 16 || a.K % 16 != 0 || a.n_members < 1 || a.n_members > kMaxGroup) return QERL_ERR_SHAPE;
   if ((int64_t)a.M * a.ldx * 2 + a.K * 2 >= (int64_t)1 << 31) return QERL_ERR_SHAPE;   // 32-bit offsets into x
-  a.NT = (int)ceil_div(a.M, 32);
+  a.tbs = (int)ceil_div(a.M, 128);               // token blocks of NT tiles each
+  a.NT = (int)ceil_div(ceil_div(a.M, a.tbs), 32);
   a.k_tiles = (int)ceil_div(a.K, kPackTileK);
   a.rank_tiles = 0;
   int64_t tiles = 0;
@@ -575,19 +582,25 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
     const int64_t t_most = a.pairs ? kPanelTPartsPair : kPanelTParts;
     parts = parts > t_most ? t_most : parts;
     parts = parts > k128 ? k128 : parts;
+    if (a.tbs > 1) {
+      // a stage of A's rows takes 0.75 us, one of a unit 1.8: as many parts as let both end together
+      const int64_t main_us10 = ceil_div(ceil_div(tiles, 4) * a.tbs * ceil_div(a.k_tiles, 2), 256) * 18;
+      const int64_t want = ceil_div((int64_t)k128 * 15, 2 * (main_us10 > 100 ? main_us10 : 100));
+      parts = parts > want ? want : parts;
+    }
     a.t_parts = (int)(parts < 1 ? 1 : parts);
-    a.n_lora = (int)(blocks * a.t_parts);
+    a.n_lora = (int)(blocks * a.t_parts * a.tbs);
   }
-  const int64_t t_bytes = (int64_t)a.t_parts * a.rank_tiles * a.NT * 4096;
+  const int64_t t_bytes = (int64_t)a.t_parts * a.rank_tiles * a.tbs * a.NT * 4096;
   const int64_t room = slots - a.n_lora > 1 ? slots - a.n_lora : 1;
   // Units of 256 rows (two K-slices per workgroup, half the sums through LDS) when whole units of that size fill the
   // chip (32B gate + up at 128 tokens 98 us against 111), else of 128 (down 53 against 59); of 64 where few tokens meet few rows,
   // so that half as many pieces of K fill the chip (7B o at 32 tokens 13.1 against 14.8, 14B 15.8 against 18.1; not for a long K
   // with more than 32 tokens, where twice the slab traffic per weight shows: 32B down at 64 tokens 45 against 40)
-  const int64_t big_units = ceil_div(tiles, 8);
+  const int64_t big_units = ceil_div(tiles, 8) * a.tbs;
   a.KW = (a.NT >= 2 && big_units * 5 >= slots * 4) ? 2 : 4;
   const int64_t one_each = 256 - a.n_lora > 1 ? 256 - a.n_lora : 1;   // consumers at one workgroup per CU
-  a.RT = (a.NT <= 2 && ceil_div(tiles, 4) * 2 <= one_each && (a.NT == 1 || a.k_tiles <= 64)) ? 1 : 2;
+  a.RT = (a.NT <= 2 && a.tbs == 1 && ceil_div(tiles, 4) * 2 <= one_each && (a.NT == 1 || a.k_tiles <= 64)) ? 1 : 2;
   a.unit_shift = a.RT == 1 ? 1 : a.KW == 2 ? 3 : 2;
   a.unit_tiles = 1 << a.unit_shift;
   a.units = 0;
@@ -596,6 +609,7 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
     a.units += (int)ceil_div(a.mem[i].n_tiles, a.unit_tiles);
   }
   for (int i = a.n_members; i < kMaxGroup; ++i) a.mem[i].unit_begin = 0x7fffffff;
+  a.units *= a.tbs;
   a.stages = (int)ceil_div(a.k_tiles, a.KW / 2);
   const int64_t total = (int64_t)a.units * a.stages;
   if (total >= (int64_t)1 << 30 || a.units > 1 << 20) return QERL_ERR_SHAPE;
@@ -629,6 +643,16 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
   return QERL_OK;
 }
 
+// Time of both launches beyond 128 tokens (blocks of 65 tokens and more): a stage of 256 inputs 1.7 us (three token tiles: 1.4),
+// every slot written and read once at about 4 TB/s, 12 us of fixed chain.  Measured / estimated, us, r = 64: 5120 x 5120, 256 tokens
+// 30 / 32; 5120 x 13824, 256 tokens 52 / 51; 3584 x 18944, 777 tokens (r = 32) 135 / 144; 5120 x 5120, 1000 tokens 92 / 90.
+double panel_estimate_us(const PanelArgs& a) {
+  const double per = a.split > 0 ? (double)(ceil_div(a.stages, a.split) * ceil_div(a.n_main, 256)) : (double)(a.per + 2);
+  const double stage = (a.NT == 4 ? 1.7 : 1.4) * (a.KW == 2 ? 0.5 : 1.0);
+  const double slots = (double)(a.split > 0 ? a.n_main : a.n_main + a.units) * a.unit_tiles * a.NT * 4096.0;
+  return per * stage + 2.0 * slots / 4.0e6 + 12.0;
+}
+
 template <int NT, int KW, int RT>
 static int launch_panel_t(const PanelArgs& a, hipStream_t st) {
   panel_kernel<NT, KW, RT><<<dim3((unsigned)(a.n_lora + a.n_main)), dim3(512), (kPanelLds<NT, KW>), st>>>(a);
@@ -638,11 +662,11 @@ static int launch_panel_t(const PanelArgs& a, hipStream_t st) {
 int launch_panel(const PanelArgs& a, hipStream_t st) {
   // every pointer and size the kernels' indexing assumes
   if (!a.x || !a.sums || (a.rank_tiles > 0 && !a.t_sums) || (a.pairs && !a.act)) return QERL_ERR_NULL;
-  if (a.M < 1 || a.NT < 1 || a.NT > 4 || a.M > a.NT * 32 || (a.KW != 2 && a.KW != 4) || a.unit_tiles * a.KW != 8 * a.RT ||
+  if (a.M < 1 || a.NT < 1 || a.NT > 4 || a.tbs < 1 || a.M > a.tbs * a.NT * 32 || (a.KW != 2 && a.KW != 4) || a.unit_tiles * a.KW != 8 * a.RT ||
       a.unit_tiles != 1 << a.unit_shift || a.K < 16 ||
       (int64_t)a.k_tiles * kPackTileK < a.K || a.stages * (a.KW / 2) < a.k_tiles || a.units < 1 || a.per < 1 ||
       a.n_main < 1 || (a.split > 0 && (a.n_main != a.units * a.split || a.split > a.stages)) ||
-      (int64_t)a.per * a.n_main + a.rem != (int64_t)a.units * a.stages || a.n_lora != ceil_div(a.rank_tiles, 2) * a.t_parts ||
+      (int64_t)a.per * a.n_main + a.rem != (int64_t)a.units * a.stages || a.n_lora != ceil_div(a.rank_tiles, 2) * a.t_parts * a.tbs ||
       a.t_parts > (a.pairs ? kPanelTPartsPair : kPanelTParts) || (a.pairs && (a.n_members != 2 || a.mem[0].N != a.mem[1].N)))
     return QERL_ERR_SHAPE;
   int tiles_max = 0, r_max = 0;
@@ -657,7 +681,7 @@ int launch_panel(const PanelArgs& a, hipStream_t st) {
   else if (a.KW == 4) rc = a.NT == 1 ? launch_panel_t<1, 4, 2>(a, st) : a.NT == 2 ? launch_panel_t<2, 4, 2>(a, st) : a.NT == 3 ? launch_panel_t<3, 4, 2>(a, st) : launch_panel_t<4, 4, 2>(a, st);
   else if (a.RT == 2) rc = a.NT == 2 ? launch_panel_t<2, 2, 2>(a, st) : a.NT == 3 ? launch_panel_t<3, 2, 2>(a, st) : a.NT == 4 ? launch_panel_t<4, 2, 2>(a, st) : rc;
   if (rc != QERL_OK) return rc;
-  const dim3 grid((unsigned)ceil_div(tiles_max, 8), (unsigned)a.NT, (unsigned)(a.pairs ? 1 : a.n_members));
+  const dim3 grid((unsigned)ceil_div(tiles_max, 8), (unsigned)(a.tbs * a.NT), (unsigned)(a.pairs ? 1 : a.n_members));
   const bool wide = r_max > 64;
   if (a.pairs && wide) panel_finish_kernel<true, true><<<grid, dim3(512), 0, st>>>(a);
   else if (a.pairs) panel_finish_kernel<true, false><<<grid, dim3(512), 0, st>>>(a);

@@ -41,6 +41,24 @@ def test_edges_of_the_plan(M, K, Ns, rs, bias):
     assert all(torch.equal(a, b) for a, b in zip(call(), got))
 
 
+@pytest.mark.parametrize("M", [129, 192, 193, 256, 300, 640, 1000])
+@pytest.mark.parametrize("K,Ns,rs", [
+    (512, (129, 64), (16, 0)),
+    (2064, (520, 40), (40, 64)),
+])
+def test_several_token_blocks(M, K, Ns, rs):
+    """More than 128 tokens on few rows: blocks of three or four token tiles, the last one partly beyond M."""
+    print("panel token blocks", M, K, Ns, rs, flush=True)
+    x = qs.activations(M, K, 70 + M)
+    ms = [_member(N, K, r, 80 + 3 * i + M, True) for i, (N, r) in enumerate(zip(Ns, rs))]
+    call = lambda: qerl.nvfp4_lora_linear_packed_group(x.cuda(), [m["pw"] for m in ms], [m["Ad"] for m in ms], [m["Bd"] for m in ms],
+                                                       [2.0] * len(ms), biases=[m["bd"] for m in ms])
+    got = call()
+    for i, m in enumerate(ms):
+        check_linear(got[i], _ref(m, x.float().numpy(), 2.0), ("token blocks", i, M, K, Ns, rs))
+    assert all(torch.equal(a, b) for a, b in zip(call(), got))
+
+
 @pytest.mark.parametrize("M,N,K,r", [
     (16, 40000, 512, 16),     # more units than workgroups
     (40, 36864, 768, 16),     # equal pieces of the line of units (pieces that end inside a unit)
