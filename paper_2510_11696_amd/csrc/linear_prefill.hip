@@ -20,6 +20,7 @@
 // LoRA and the operand layouts as in linear_gemm.hip.
 #include "linear.hpp"
 #include "lds_dma.hpp"
+#include "tile_out.hpp"
 
 namespace qerl {
 
@@ -32,8 +33,7 @@ struct PrefillCfg {
   static constexpr int kSlab = TT * 256;          // 16-byte chunks of a slab: TT * 32 rows x 8; chunk c of row r sits at r * 8 + (c ^ ((r >> 1) & 7))
   static constexpr int XB = 4;                    // slabs in LDS
   static constexpr int kLdsSlabs = XB * kSlab * 16;
-  static constexpr int kOutStride = RT * 64 + 16;  // bytes per token of a wave's output tile on its way out
-  static constexpr int kLdsOut = W * 64 * kOutStride;
+  static constexpr int kLdsOut = W * tile_out_bytes(RT);
   static constexpr int kLds = kLdsSlabs > kLdsOut ? kLdsSlabs : kLdsOut;
 };
 
@@ -229,52 +229,9 @@ __global__ __launch_bounds__(W * 64, 2) void prefill_kernel(const GemmArgs a) {
     }
   }
 
-  // ---- out: 64 tokens at a time through the wave's own part of LDS, then whole rows of RT * 64 bytes
-  const float S32 = *mem.tensor_scale;
-  uint8_t* out = reinterpret_cast<uint8_t*>(xs) + wave * 64 * C::kOutStride;
   const int64_t n0 = (int64_t)rt0 * 32;
   if (n0 >= mem.N) return;                         // a wave beyond the member's rows
-  const bool vec = aligned_dev(mem.y, 16) && mem.ldy % 8 == 0;
-#pragma unroll
-  for (int half = 0; half < TT / 2; ++half) {
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& v = acc[t][half * 2 + tt];
-          float o[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            o[e] = v[4 * q + e] * S32;
-            if (mem.bias) {
-              const int64_t n = n0 + t * 32 + 8 * q + 4 * kg + e;
-              o[e] += bf16_bits_to_f32(mem.bias[n < mem.N ? n : mem.N - 1]);
-            }
-          }
-          *reinterpret_cast<u32x2*>(out + (tt * 32 + n32) * C::kOutStride + t * 64 + q * 16 + kg * 8) = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
-        }
-    __builtin_amdgcn_wave_barrier();
-    constexpr int CH = RT * 4, RPI = 64 / CH;      // 16-byte chunks of a row, rows per instruction
-#pragma unroll 4
-    for (int i = 0; i < 64 / RPI; ++i) {
-      const int row = i * RPI + lane / CH, ch = lane % CH;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(out + row * C::kOutStride + ch * 16);
-      const int64_t m = m0 + half * 64 + row, n = n0 + ch * 8;
-      if (m < a.M) {
-        uint16_t* dst = mem.y + m * mem.ldy + n;
-        if (vec && n + 8 <= mem.N) {
-          *reinterpret_cast<u32x4*>(dst) = v;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (n + e < mem.N) dst[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
-        }
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
+  store_tiles<TT, RT>(acc, *mem.tensor_scale, mem.bias, mem.y, mem.ldy, a.M, mem.N, m0, n0, reinterpret_cast<uint8_t*>(xs) + wave * tile_out_bytes(RT), lane);
 }
 
 // 32-bit offsets inside a token block

@@ -39,6 +39,8 @@
 // kernels leaves lora_scale * x A^T as three bf16 terms), and the up-projection is 3 r more input columns on the bf16
 // matrix instruction, whose 32 x 32 output layout is the block-scaled one's.
 #include "linear.hpp"
+#include "lds_dma.hpp"
+#include "tile_out.hpp"
 
 namespace qerl {
 
@@ -418,15 +420,12 @@ static int launch_mx(const MxArgs& a, int NG, int grid, hipStream_t st) {
 
 // ---- more than 32 tokens: a GEMM on the block-scaled matrix instruction ---------------------------------------
 // y = MXFP8(x) . MXFP4(W)^T, x quantised beforehand (mx_quantize_kernel<8>) into codes [M, K] and scales [M, K / 32].
-// No conversion arithmetic at all: packed weights go global -> registers -> matrix instruction.  Workgroup tile
-// 128 tokens x 256 rows, eight waves as 2 x 4: a wave owns 64 tokens x 64 rows (2 x 2 accumulator tiles), so every
-// x fragment read from LDS and every weight fragment feeds two instructions.  A stage is one packed tile (256
-// inputs, four instruction steps, 16 instructions per wave between barriers): its weights are requested one stage
-// ahead into registers, its x slab (128 tokens x 256 bytes + 8 scale bytes per token) one stage ahead into
-// registers and then into the other of two LDS buffers (16-byte chunks XOR-swizzled by row; the scale bytes of a
-// row regrouped so that a lane finds the four bytes of its half in one dword and the instruction picks by an
-// immediate).  No branch inside a stage depends on the thread or the stage: requests past the end are redirected
-// to the last stage, so the compiler's wait counts stay exact.  Bound by the FP8 matrix rate.
+// No conversion arithmetic at all: packed weights go global -> registers -> matrix instruction.  The shape of
+// linear_prefill.hip: four waves own 128 tokens x 256 rows, a wave 64 of the rows for all tokens, two workgroups share a CU.
+// A stage is 128 inputs, two instruction steps of 2 x 4 tiles: x slabs (128 tokens x 128 bytes) go to LDS directly, three
+// stages ahead, weights into a register ring three stages ahead; the workgroup meets once a stage, between its two steps, with
+// the next stage's first fragments read behind it.  The E8M0 bytes of x come from memory, eight per token and 256 inputs:
+// blocks 2 j + g are picked for the lane half g, and the instruction selects byte j by an immediate, as for the weights.
 struct MxGemmArgs {
   const uint8_t* xq; const uint8_t* xs; int64_t M, K;     // MXFP8 codes [M, K], scales [M, K / 32]
   const uint8_t* packed; int k_tiles; int n_tiles; int64_t N;
@@ -436,195 +435,206 @@ struct MxGemmArgs {
   const uint16_t* bias;
 };
 
-constexpr int kMxgBM = 128, kMxgThreads = 512, kMxgMT = 2, kMxgNT = 2;
-struct MxgW { u32x4 c[kMxgNT][4]; uint32_t sc[kMxgNT]; };          // one wave's weights of a stage
-struct MxgX { u32x4 c[4]; uint32_t s0, s1; };                       // one thread's share of an x slab: four chunks, two scale bytes
+constexpr int kMxgTT = 4, kMxgRT = 2, kMxgW = 4, kMxgSlabs = 4;
+constexpr int kMxgTokens = kMxgTT * 32, kMxgSlab = kMxgTokens * 8;   // 16-byte chunks of a slab; chunk c of row r sits at r * 8 + (c ^ ((r >> 1) & 7))
+constexpr int kMxgLds = kMxgSlabs * kMxgSlab * 16;
+static_assert(kMxgLds >= kMxgW * tile_out_bytes(kMxgRT), "the outputs leave through the slabs' place");
+__device__ const u32x4 g_mx_zeros = {0u, 0u, 0u, 0u};   // what is beyond the end of a row of x
 
-__global__ __launch_bounds__(kMxgThreads) void mx_gemm_kernel(const MxGemmArgs a) {
-  constexpr int BM = kMxgBM, MT = kMxgMT, NT = kMxgNT;
-  constexpr int kChunks = BM * 16;                         // 16-byte chunks of one x slab (BM rows x 256 bytes)
-  __shared__ u32x4 xs[2 * kChunks];                        // chunk c of row r at r * 16 + (c ^ (r & 15))
-  __shared__ __attribute__((aligned(8))) uint8_t xsc[2 * BM * 8];   // row r: bytes [g * 4 + j] = scale of block 2 j + g
+__global__ __launch_bounds__(kMxgW * 64, 2) void mx_gemm_kernel(const MxGemmArgs a) {
+  constexpr int TT = kMxgTT, RT = kMxgRT, W = kMxgW, XB = kMxgSlabs;
+  constexpr int XI = TT * 4 / W;                           // slab requests per wave and stage (8 rows each)
+  extern __shared__ __attribute__((aligned(256))) u32x4 xs[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 2, wn = wave & 3;                 // the wave's token half and row quarter
   const int n32 = lane & 31, kg = lane >> 5;
+  const uint32_t lds0 = lds_address(xs);
   const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;   // each XCD walks a contiguous eighth of the column blocks
   const int nb_local = local % a.nblk_per_xcd, mb = local / a.nblk_per_xcd;
   const int nb = xcd * a.nblk_per_xcd + nb_local;
   if (nb >= a.n_blocks) return;
-  const int64_t m0 = (int64_t)mb * BM;
-  const int nt0 = (nb * 4 + wn) * NT;
-  const int64_t n_blk = a.K / 32;
+  const int64_t m0 = (int64_t)mb * kMxgTokens;
+  const int rt0 = (nb * W + wave) * RT;
 
-  f32x16 acc[MT][NT];
+  // ---- x: codes
+  const int row0 = wave * 8 + (lane >> 3);
+  const uint32_t col = (uint32_t)(((lane & 7) ^ ((row0 >> 1) & 7)) * 16);
+  const uint8_t* xbase = uniform_pointer(a.xq + m0 * a.K);
+  uint32_t row_off[XI];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.f;
-
-  // thread -> (row, chunk) of the slab: chunks tid, tid + 512, ...; scale bytes: row tid / 4, blocks 2 (tid % 4), + 1
-  auto gload_x = [&](MxgX& r, int kt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + i * kMxgThreads, row = idx >> 4, ch = idx & 15;
-      int64_t gr = m0 + row;
-      gr = gr < a.M ? gr : a.M - 1;
-      int64_t k = (int64_t)kt * 256 + ch * 16;
-      k = k < a.K ? k : a.K - 16;                          // past the end of K: any bytes, zeroed before they reach LDS
-      r.c[i] = *reinterpret_cast<const u32x4*>(a.xq + gr * a.K + k);
-    }
-    int64_t gr = m0 + (tid >> 2);
-    gr = gr < a.M ? gr : a.M - 1;
-    int64_t b0 = (int64_t)kt * 8 + 2 * (tid & 3), b1 = b0 + 1;
-    b0 = b0 < n_blk ? b0 : n_blk - 1;
-    b1 = b1 < n_blk ? b1 : n_blk - 1;
-    r.s0 = a.xs[gr * n_blk + b0];
-    r.s1 = a.xs[gr * n_blk + b1];
-  };
-  auto swrite_x = [&](int buf, const MxgX& r, int kt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = tid + i * kMxgThreads, row = idx >> 4, ch = idx & 15;
-      // beyond K (K % 256 != 0): zero codes -- a stray byte could be an FP8 NaN, and the weights there are zero
-      const u32x4 v = (int64_t)kt * 256 + ch * 16 < a.K ? r.c[i] : u32x4{0u, 0u, 0u, 0u};
-      xs[buf * kChunks + row * 16 + (ch ^ (row & 15))] = v;
-    }
-    const int row = tid >> 2, j = tid & 3;                  // blocks 2 j (half 0) and 2 j + 1 (half 1) of the row
-    const bool in0 = (int64_t)kt * 8 + 2 * j < n_blk, in1 = (int64_t)kt * 8 + 2 * j + 1 < n_blk;
-    xsc[(buf * BM + row) * 8 + j] = in0 ? (uint8_t)r.s0 : (uint8_t)0;
-    xsc[(buf * BM + row) * 8 + 4 + j] = in1 ? (uint8_t)r.s1 : (uint8_t)0;
-  };
-  auto gload_w = [&](MxgW& w, int kt) {
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      int tile = nt0 + nt;
-      tile = tile < a.n_tiles ? tile : a.n_tiles - 1;
-      const uint8_t* base = a.packed + ((int64_t)tile * a.k_tiles + kt) * kMxTileBytes;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) w.c[nt][j] = *reinterpret_cast<const u32x4*>(base + j * 1024 + lane * 16);
-      w.sc[nt] = *reinterpret_cast<const uint32_t*>(base + 4096 + lane * 4);
-    }
-  };
-  auto compute = [&](int buf, const MxgW& w) {
-    const u32x4* xst = xs + buf * kChunks;
-    int xscale[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int row = wm * 64 + mt * 32 + n32;
-      xscale[mt] = (int)*reinterpret_cast<const uint32_t*>(xsc + (buf * BM + row) * 8 + kg * 4);
-    }
-    // x fragments of step j + 1 are requested from LDS before the instructions of step j are issued
-    auto frags = [&](v8i (&xa)[MT], int j) {
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const int row = wm * 64 + mt * 32 + n32, sw = row & 15;
-        const u32x4 c0 = xst[row * 16 + ((4 * j + kg) ^ sw)], c1 = xst[row * 16 + ((4 * j + 2 + kg) ^ sw)];
-        xa[mt] = v8i{(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], (int)c1[2], (int)c1[3]};
-      }
-    };
-    auto step = [&](const v8i (&xa)[MT], auto jc) {
-      constexpr int j = decltype(jc)::value;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        const v8i b = v8i{(int)w.c[nt][j][0], (int)w.c[nt][j][1], (int)w.c[nt][j][2], (int)w.c[nt][j][3], 0, 0, 0, 0};
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(xa[mt], b, acc[mt][nt], 0, 4, j, xscale[mt], j, (int)w.sc[nt]);
-      }
-    };
-    v8i xa[MT], xb[MT];
-    frags(xa, 0);
-    frags(xb, 1);
-    step(xa, std::integral_constant<int, 0>{});
-    frags(xa, 2);
-    step(xb, std::integral_constant<int, 1>{});
-    frags(xb, 3);
-    step(xa, std::integral_constant<int, 2>{});
-    step(xb, std::integral_constant<int, 3>{});
-  };
-
-  {
-    const int n = a.k_tiles, last = n - 1;
-    auto clamp_kt = [&](int kt) { return kt < last ? kt : last; };
-    MxgW w0, w1;
-    MxgX x0, x1;
-    gload_x(x0, 0);
-    gload_x(x1, clamp_kt(1));
-    gload_w(w0, 0);
-    swrite_x(0, x0, 0);
-    __syncthreads();
-    // Two stages per round so that buffer and register names are constants.  Stage kt: the slab of kt + 2 and the
-    // weights of kt + 1 are requested, kt is multiplied, the slab of kt + 1 (requested a stage ago) goes to LDS.
-    auto stage = [&](int kt, int buf, MxgW& wcur, MxgW& wnext, MxgX& xfar, const MxgX& xnear) {
-      gload_x(xfar, clamp_kt(kt + 2));
-      gload_w(wnext, clamp_kt(kt + 1));
-      __builtin_amdgcn_sched_barrier(0);   // the requests stay ahead of the stage's arithmetic
-      compute(buf, wcur);
-      __builtin_amdgcn_sched_barrier(0);
-      swrite_x(buf ^ 1, xnear, clamp_kt(kt + 1));
-      __syncthreads();
-    };
-    int kt = 0;
-    for (; kt + 2 <= n; kt += 2) {
-      stage(kt, 0, w0, w1, x0, x1);
-      stage(kt + 1, 1, w1, w0, x1, x0);
-    }
-    if (kt < n) stage(kt, 0, w0, w1, x0, x1);
+  for (int i = 0; i < XI; ++i) {
+    int64_t m = row0 + 8 * W * i;
+    m = m0 + m < a.M ? m : a.M - 1 - m0;
+    row_off[i] = (uint32_t)(m * a.K) + col;
   }
+  auto request_x = [&](int stage, int buf) {
+    const uint32_t dst = lds0 + (uint32_t)((buf * kMxgSlab + wave * 64) * 16), k = (uint32_t)stage * 128u;
+    const bool in = k + col < (uint32_t)a.K;               // beyond K: zero codes -- a stray byte could be an FP8 NaN, and the weights there are zero
+    // (no branch around the two sources: the compiler would move a stage's matrix instructions behind it)
+#pragma unroll
+    for (int i = 0; i < XI; ++i) lds_request64(dst + (uint32_t)(i * W * 1024), in ? (const void*)(xbase + k + row_off[i]) : (const void*)&g_mx_zeros);
+  };
+  // fragment of step j (64 inputs) of a slab: chunks 4 j + kg and 4 j + 2 + kg of row 32 tt + n32
+  const int frag = n32 * 8, sw = (n32 >> 1) & 7;
+  auto x_frag = [&](int buf, int j, int tt) {
+    const u32x4* p = xs + buf * kMxgSlab + tt * 256 + frag;
+    const u32x4 c0 = p[(4 * j + kg) ^ sw], c1 = p[(4 * j + 2 + kg) ^ sw];
+    return v8i{(int)c0[0], (int)c0[1], (int)c0[2], (int)c0[3], (int)c1[0], (int)c1[1], (int)c1[2], (int)c1[3]};
+  };
+  // ---- x: scales of 256 inputs: eight bytes of the token's row from block 8 kt on (what lies beyond the row multiplies zeros;
+  // at the very end of the array the read is moved back and shifted)
+  const uint32_t n_blk = (uint32_t)(a.K / 32), xs_end = (uint32_t)(a.M * n_blk - 8);
+  uint32_t xs_row[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) {
+    int64_t m = m0 + tt * 32 + n32;
+    m = m < a.M ? m : a.M - 1;
+    xs_row[tt] = (uint32_t)m * n_blk;
+  }
+  auto load_xs = [&](u32x2 (&raw)[TT], int kt) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const uint32_t at = xs_row[tt] + (uint32_t)kt * 8u;
+      __builtin_memcpy(&raw[tt], a.xs + (at < xs_end ? at : xs_end), 8);
+    }
+  };
+  auto pick_xs = [&](int (&out)[TT], const u32x2 (&raw)[TT], int kt) {
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+      const uint32_t at = xs_row[tt] + (uint32_t)kt * 8u;
+      const uint64_t v = __builtin_bit_cast(uint64_t, raw[tt]) >> (at > xs_end ? (at - xs_end) * 8u : 0u);
+      out[tt] = (int)__builtin_amdgcn_perm((uint32_t)(v >> 32), (uint32_t)v, kg ? 0x07050301u : 0x06040200u);
+    }
+  };
+  // ---- weights
+  const uint8_t* wbase[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    int tile = rt0 + t;
+    tile = tile < a.n_tiles ? tile : a.n_tiles - 1;
+    wbase[t] = a.packed + (int64_t)tile * a.k_tiles * kMxTileBytes;
+  }
+  u32x4 w[4][RT];                                          // codes of four steps: slot j is refilled a step after its use, three ahead
+  auto load_w = [&](auto jc, int kt) {
+    constexpr int j = decltype(jc)::value;
+#pragma unroll
+    for (int t = 0; t < RT; ++t) w[j][t] = *reinterpret_cast<const u32x4*>(wbase[t] + (int64_t)kt * kMxTileBytes + j * 1024 + lane * 16);
+  };
+  auto load_ws = [&](uint32_t (&s)[RT], int kt) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t) s[t] = *reinterpret_cast<const uint32_t*>(wbase[t] + (int64_t)kt * kMxTileBytes + 4096 + lane * 4);
+  };
+  f32x16 acc[RT][TT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[t][tt][i] = 0.f;
+
+  const int n = a.k_tiles, last = 2 * n - 1;
+  auto clamp = [&](int s) { return s < last ? s : last; };
+  uint32_t wsc[RT], wsc_next[RT];
+  u32x2 xraw[TT];
+  int xsc[TT];
+#pragma unroll
+  for (int p = 0; p < XB - 1; ++p) request_x(clamp(p), p);
+  asm volatile("" ::: "memory");
+  load_xs(xraw, 0);
+  load_ws(wsc, 0);
+  load_w(std::integral_constant<int, 0>{}, 0);
+  load_w(std::integral_constant<int, 1>{}, 0);
+  load_w(std::integral_constant<int, 2>{}, 0);
+  pick_xs(xsc, xraw, 0);
+  lds_wait_barrier<(XB - 2) * XI>();
+  v8i xf[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; ++tt) xf[tt] = x_frag(0, 0, tt);
+  int buf = 0;
+  // A packed tile of 256 inputs: two stages of two steps.  On entry of a step its fragments are in registers.
+  for (int kt = 0; kt < n; ++kt) {
+    const int kn = kt + 1 < n ? kt + 1 : kt;
+    load_xs(xraw, kn);                                     // the next tile's scales
+    load_ws(wsc_next, kn);
+    auto step = [&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      const int next = buf + 1 == XB ? 0 : buf + 1;
+      if constexpr (j & 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        // behind the next stage's slab: one slab, the codes of four steps (two requests each; every one is used) and more
+        lds_wait_barrier<XI + 8>();
+        request_x(clamp(2 * kt + (j >> 1) + XB - 1), buf == 0 ? XB - 1 : buf - 1);
+      }
+      load_w(std::integral_constant<int, (j + 3) & 3>{}, j == 0 ? kt : kn);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          const v8i wf = v8i{(int)w[j][t][0], (int)w[j][t][1], (int)w[j][t][2], (int)w[j][t][3], 0, 0, 0, 0};
+          acc[t][tt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wf, xf[tt], acc[t][tt], 4, 0, j, (int)wsc[t], j, xsc[tt]);
+        }
+        xf[tt] = j & 1 ? x_frag(next, 0, tt) : x_frag(buf, 1, tt);
+      }
+#pragma unroll
+      for (int tt = 0; tt < TT; ++tt) {
+        __builtin_amdgcn_sched_group_barrier(0x008, RT, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (j & 1) buf = next;
+    };
+    step(std::integral_constant<int, 0>{});
+    step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 2>{});
+    step(std::integral_constant<int, 3>{});
+    pick_xs(xsc, xraw, kn);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) wsc[t] = wsc_next[t];
+  }
+  lds_wait_barrier<0>();                                   // nothing on its way to LDS, nobody reading
   // ---- LoRA up-projection (Eq. 2): 3 r more input columns, [hi | mid | lo] . [B B B]^T, on the bf16 matrix
   // instruction of the same output layout; operands straight from memory, four chunks of 16 columns requested at a time
   for (int c0 = 0; c0 < a.n_chunks; c0 += 4) {
-    u32x4 tf[4][MT], bf[4][NT];
+    u32x4 tf[4][TT], bf[4][RT];
 #pragma unroll
     for (int cc = 0; cc < 4; ++cc) {
       const bool live = c0 + cc < a.n_chunks;
-      const int col = 16 * (live ? c0 + cc : a.n_chunks - 1) + 8 * kg;
-      const int bc = lora_b_col(col, a.r);
+      const int tcol = 16 * (live ? c0 + cc : a.n_chunks - 1) + 8 * kg;
+      const int bc = lora_b_col(tcol, a.r);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        int64_t row = m0 + wm * 64 + mt * 32 + n32;
+      for (int tt = 0; tt < TT; ++tt) {
+        int64_t row = m0 + tt * 32 + n32;
         row = row < a.M ? row : a.M - 1;
-        tf[cc][mt] = *reinterpret_cast<const u32x4*>(a.ts + row * a.ts_ld + col);
-        if (!live) tf[cc][mt] = u32x4{0u, 0u, 0u, 0u};
+        tf[cc][tt] = *reinterpret_cast<const u32x4*>(a.ts + row * a.ts_ld + tcol);
+        if (!live) tf[cc][tt] = u32x4{0u, 0u, 0u, 0u};
       }
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        int64_t n = (int64_t)(nt0 + nt) * 32 + n32;
+      for (int t = 0; t < RT; ++t) {
+        int64_t n = (int64_t)(rt0 + t) * 32 + n32;
         n = n < a.N ? n : a.N - 1;
-        bf[cc][nt] = *reinterpret_cast<const u32x4*>(a.B + n * a.r + bc);
+        bf[cc][t] = *reinterpret_cast<const u32x4*>(a.B + n * a.r + bc);
       }
     }
 #pragma unroll
     for (int cc = 0; cc < 4; ++cc)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, tf[cc][mt]), __builtin_bit_cast(bf16x8, bf[cc][nt]),
-                                                                acc[mt][nt], 0, 0, 0);
+        for (int t = 0; t < RT; ++t)
+          acc[t][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[cc][t]), __builtin_bit_cast(bf16x8, tf[cc][tt]),
+                                                               acc[t][tt], 0, 0, 0);
   }
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int64_t nn = (int64_t)(nt0 + nt) * 32 + n32;
-      const float bias = (a.bias && nn < a.N) ? bf16_bits_to_f32(a.bias[nn]) : 0.f;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int64_t m = m0 + wm * 64 + mt * 32 + 8 * (i >> 2) + 4 * kg + (i & 3);
-        if (m < a.M && nn < a.N) a.y[m * a.ldy + nn] = (uint16_t)f32_to_bf16_bits(acc[mt][nt][i] + bias);
-      }
-    }
+  const int64_t n0 = (int64_t)rt0 * 32;
+  if (n0 >= a.N) return;
+  store_tiles<TT, RT>(acc, 1.0f, a.bias, a.y, a.ldy, a.M, a.N, m0, n0, reinterpret_cast<uint8_t*>(xs) + wave * tile_out_bytes(RT), lane);
 }
 
 static int launch_mx_gemm(MxGemmArgs a, hipStream_t st) {
-  a.n_blocks = (int)ceil_div(a.n_tiles, 4 * kMxgNT);
+  a.n_blocks = (int)ceil_div(a.n_tiles, kMxgW * kMxgRT);
   a.nblk_per_xcd = (int)ceil_div(a.n_blocks, 8);
-  const int64_t m_blocks = ceil_div(a.M, kMxgBM);
-  mx_gemm_kernel<<<dim3((unsigned)(8 * a.nblk_per_xcd * m_blocks)), dim3(kMxgThreads), 0, st>>>(a);
+  const int64_t m_blocks = ceil_div(a.M, kMxgTokens);
+  mx_gemm_kernel<<<dim3((unsigned)(8 * a.nblk_per_xcd * m_blocks)), dim3(kMxgW * 64), kMxgLds, st>>>(a);
   return launch_status();
 }
 
