@@ -20,6 +20,7 @@
 // LoRA and the operand layouts as in linear_gemm.hip.
 #include "linear.hpp"
 #include "lds_dma.hpp"
+#include "lora_up.hpp"
 #include "tile_out.hpp"
 
 namespace qerl {
@@ -61,37 +62,28 @@ __global__ __launch_bounds__(W * 64, 2) void prefill_kernel(const GemmArgs a) {
   const GemmMember& mem = a.m[__builtin_amdgcn_readfirstlane(mi)];
   const int rt0 = ((nb - mem.block_begin) * W + wave) * RT;
 
-  // ---- x (or the LoRA columns): rows m0 .. of a row-major matrix of `cols` columns
-  struct Source { const uint8_t* base; uint32_t k_cap; uint32_t row_off[XI]; };
+  // ---- x
   const int row0 = wave * 8 + (lane >> 3);
-  const uint32_t col_bytes = (uint32_t)(((lane & 7) ^ ((row0 >> 1) & 7)) * 16);
-  auto source = [&](const uint16_t* p, int64_t ld, int64_t cols) {
-    Source s;
-    s.base = uniform_pointer(p + m0 * ld);
-    s.k_cap = (uint32_t)(cols * 2 - 16);
+  const uint32_t col_bytes = (uint32_t)(((lane & 7) ^ ((row0 >> 1) & 7)) * 16), k_cap = (uint32_t)(a.K * 2 - 16);
+  const uint8_t* xbase = uniform_pointer(a.x + m0 * a.ldx);
+  uint32_t row_off[XI];
 #pragma unroll
-    for (int i = 0; i < XI; ++i) {
-      int64_t m = row0 + 8 * W * i;
-      m = m0 + m < a.M ? m : a.M - 1 - m0;
-      s.row_off[i] = (uint32_t)(m * ld * 2) + col_bytes;
-    }
-    return s;
-  };
-  auto request = [&](const Source& s, int stage, int buf) {
-    const uint32_t dst = lds0 + (uint32_t)((buf * kSlab + wave * 64) * 16);
-    if ((uint32_t)stage * 128u + 112u <= s.k_cap) {
-      const uint8_t* base = s.base + (uint32_t)stage * 128u;
+  for (int i = 0; i < XI; ++i) {
+    int64_t m = row0 + 8 * W * i;
+    m = m0 + m < a.M ? m : a.M - 1 - m0;
+    row_off[i] = (uint32_t)(m * a.ldx * 2) + col_bytes;
+  }
+  auto request_x = [&](int stage, int buf) {
+    const uint32_t dst = lds0 + (uint32_t)((buf * kSlab + wave * 64) * 16), k = (uint32_t)stage * 128u;
+    if (k + 112u <= k_cap) {
 #pragma unroll
-      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), base, s.row_off[i]);
+      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), xbase + k, row_off[i]);
     } else {                                       // the last stage of a K that is no multiple of 64
-      const uint32_t k = (uint32_t)stage * 128u + col_bytes, over = k > s.k_cap ? k - s.k_cap : 0u;   // past the end the other operand is zero; any finite value will do
-      const uint8_t* base = s.base + (uint32_t)stage * 128u;
+      const uint32_t at = k + col_bytes, back = at > k_cap ? at - k_cap : 0u;   // past the end the other operand is zero; any finite value will do
 #pragma unroll
-      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), base - 128, s.row_off[i] + 128u - over);
+      for (int i = 0; i < XI; ++i) lds_request(dst + (uint32_t)(i * W * 1024), xbase + k - 128, row_off[i] + 128u - back);
     }
   };
-  const Source sx = source(a.x, a.ldx, a.K);
-  auto request_x = [&](int stage, int buf) { request(sx, stage, buf); };
   const int frag = n32 * 8, sw = (n32 >> 1) & 7;
   auto x_frag = [&](int buf, int j, int tt) {
     return __builtin_bit_cast(bf16x8, xs[buf * kSlab + (frag + ((2 * j + kg) ^ sw)) + tt * 256]);
@@ -192,43 +184,7 @@ __global__ __launch_bounds__(W * 64, 2) void prefill_kernel(const GemmArgs a) {
   }
   lds_wait_barrier<0>();                           // nothing on its way to LDS, nobody reading
 
-  // ---- LoRA: 3r more columns [hi | mid | lo] . [B ; B ; B]^T, XB slabs of 64 at a time
-  if (mem.ext_stages > 0) {
-    const Source st = source(mem.ts, mem.ts_ld, mem.ts_ld);
-    const uint16_t* brow[RT];
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-      int64_t row = (int64_t)(rt0 + t) * 32 + n32;
-      row = row < mem.N ? row : mem.N - 1;
-      brow[t] = mem.B + row * mem.r;
-    }
-    for (int e0 = 0; e0 < mem.ext_stages; e0 += XB) {
-      const int n_e = mem.ext_stages - e0 < XB ? mem.ext_stages - e0 : XB;
-      for (int e = 0; e < n_e; ++e) request(st, e0 + e, e);
-      lds_wait_barrier<0>();
-      for (int e = 0; e < n_e; ++e) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int c = (e0 + e) * 64 + 16 * j + 8 * kg;
-          bf16x8 bf[RT];
-#pragma unroll
-          for (int t = 0; t < RT; ++t) {
-            u32x4 b = {0u, 0u, 0u, 0u};
-            if (c < 3 * mem.r) b = *reinterpret_cast<const u32x4*>(brow[t] + c % mem.r);
-            bf[t] = __builtin_bit_cast(bf16x8, b);
-          }
-#pragma unroll
-          for (int tt = 0; tt < TT; ++tt) {
-            const bf16x8 x1 = x_frag(e, j, tt);
-#pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[t], x1, acc[t][tt], 0, 0, 0);
-          }
-        }
-      }
-      lds_wait_barrier<0>();
-    }
-  }
-
+  if (mem.r > 0) lora_up<TT, RT, W, XB>(acc, mem.ts, mem.ts_ld, mem.B, mem.r, a.M, mem.N, m0, rt0, xs, wave, lane);
   const int64_t n0 = (int64_t)rt0 * 32;
   if (n0 >= mem.N) return;                         // a wave beyond the member's rows
   store_tiles<TT, RT>(acc, *mem.tensor_scale, mem.bias, mem.y, mem.ldy, a.M, mem.N, m0, n0, reinterpret_cast<uint8_t*>(xs) + wave * tile_out_bytes(RT), lane);

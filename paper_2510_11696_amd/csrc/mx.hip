@@ -40,6 +40,7 @@
 // matrix instruction, whose 32 x 32 output layout is the block-scaled one's.
 #include "linear.hpp"
 #include "lds_dma.hpp"
+#include "lora_up.hpp"
 #include "tile_out.hpp"
 
 namespace qerl {
@@ -593,38 +594,7 @@ __global__ __launch_bounds__(kMxgW * 64, 2) void mx_gemm_kernel(const MxGemmArgs
     for (int t = 0; t < RT; ++t) wsc[t] = wsc_next[t];
   }
   lds_wait_barrier<0>();                                   // nothing on its way to LDS, nobody reading
-  // ---- LoRA up-projection (Eq. 2): 3 r more input columns, [hi | mid | lo] . [B B B]^T, on the bf16 matrix
-  // instruction of the same output layout; operands straight from memory, four chunks of 16 columns requested at a time
-  for (int c0 = 0; c0 < a.n_chunks; c0 += 4) {
-    u32x4 tf[4][TT], bf[4][RT];
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc) {
-      const bool live = c0 + cc < a.n_chunks;
-      const int tcol = 16 * (live ? c0 + cc : a.n_chunks - 1) + 8 * kg;
-      const int bc = lora_b_col(tcol, a.r);
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt) {
-        int64_t row = m0 + tt * 32 + n32;
-        row = row < a.M ? row : a.M - 1;
-        tf[cc][tt] = *reinterpret_cast<const u32x4*>(a.ts + row * a.ts_ld + tcol);
-        if (!live) tf[cc][tt] = u32x4{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int t = 0; t < RT; ++t) {
-        int64_t n = (int64_t)(rt0 + t) * 32 + n32;
-        n = n < a.N ? n : a.N - 1;
-        bf[cc][t] = *reinterpret_cast<const u32x4*>(a.B + n * a.r + bc);
-      }
-    }
-#pragma unroll
-    for (int cc = 0; cc < 4; ++cc)
-#pragma unroll
-      for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int t = 0; t < RT; ++t)
-          acc[t][tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bf[cc][t]), __builtin_bit_cast(bf16x8, tf[cc][tt]),
-                                                               acc[t][tt], 0, 0, 0);
-  }
+  if (a.r > 0) lora_up<TT, RT, W, XB>(acc, a.ts, a.ts_ld, a.B, a.r, a.M, a.N, m0, rt0, xs, wave, lane);
   const int64_t n0 = (int64_t)rt0 * 32;
   if (n0 >= a.N) return;
   store_tiles<TT, RT>(acc, 1.0f, a.bias, a.y, a.ldy, a.M, a.N, m0, n0, reinterpret_cast<uint8_t*>(xs) + wave * tile_out_bytes(RT), lane);
