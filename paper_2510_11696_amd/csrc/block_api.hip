@@ -1,16 +1,19 @@
 // C-ABI entry points of the fused decode launches (block_kernel, linear_block.hip):
 //   aqn_rmsnorm_nvfp4_lora_linear_group  RMSNorm with noisy gain (Eq. 10) -> up to four NVFP4 + LoRA linears (Eq. 6, Eq. 2)
 //   aqn_rmsnorm_nvfp4_lora_mlp           RMSNorm -> gate_proj, up_proj -> SiLU(gate) (.) up -> down_proj
-// one launch each up to 16 tokens; beyond that they run the same operators as separate launches.
+// as separate launches of the same operators, or (up to 16 tokens) one launch each.
 #include <stdlib.h>
 #include "linear.hpp"
 
 namespace qerl {
 
-// Token count from which norm and linears go out as separate launches (the panel kernels), and a whole feed-forward block
-// likewise: us at 9 / 16 tokens, one launch against norm + panel launches: 7B q + k + v 23.4 / 24.3 against 18, feed-forward
-// block 66 / 75 against 62; 32B 27.9 / 29.3 against 21.6 and 89 / 98 against 94.  At 8 tokens one launch: 19.0 and 56.9 (7B), 80.8 (32B).
-constexpr int64_t kBlkSeparateTokens = 9;
+// Up to 16 tokens norm and linears can go out as ONE launch (block_kernel) or as separate ones: the norm with the adapters'
+// down-projections, the grouped linear, the gated down projection (up to 8 tokens), the norm and the panel kernels (from 9 on).
+// The separate launches are the faster ones; the one launch serves workspaces of the size that it needs alone.
+// Measured, us in graph replay, one launch / separate: feed-forward block 7B shapes 1 token 55 / 49, 8 tokens 59 / 52, 9 tokens 66 / 62;
+// 14B 65 / 51, 67 / 55; 32B 75 / 73, 79 / 80, 89 / 94; 2048 x 5504 38 / 30, 39 / 34; norm + q + k + v
+// 7B 18 / 14, 19 / 15, 23 / 18; 14B 21 / 17, 22 / 20; 32B 20 / 17, 22 / 20, 28 / 22; 2048 wide 18 / 13, 19 / 13.
+constexpr int64_t kBlkPanelTokens = 9;
 
 static size_t blk_align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -96,6 +99,33 @@ static int blk_plan_and_launch(BlkArgs& a, uint8_t* ws, size_t ws_bytes, size_t 
   return launch_block(a, lds, MR, st);
 }
 
+// t of the adapters of up to 8 tokens, behind the other areas of a composed call
+static size_t blk_t_bytes(int64_t M, const qerl_linear_desc* const* d, int n) {
+  size_t b = 0;
+  for (int i = 0; i < n; ++i) b += blk_align256((size_t)QERL_T_PARTS * (size_t)(M > 0 ? M : 1) * (size_t)(d[i]->r > 0 ? d[i]->r : 0) * sizeof(float));
+  return b;
+}
+// The norm's launch: xn = aqn_rmsnorm(x), and up to 8 tokens with it t_i = xn A_i^T of the members with an adapter (m[i].t_f32).
+static int blk_norm(const void* x, int64_t M, int64_t K, int64_t ldx, const void* gain, const float* noise, float eps, uint16_t* xn,
+                    qerl_linear_desc* m, int n, uint8_t* t_area, void* stream) {
+  const void* A[kMaxGroup];
+  float* t[kMaxGroup];
+  int64_t r[kMaxGroup];
+  int na = 0;
+  for (int i = 0; i < n && M < kBlkPanelTokens; ++i)
+    if (m[i].r > 0) {
+      A[na] = m[i].A_bf16; r[na] = m[i].r; t[na] = (float*)t_area; m[i].t_f32 = (float*)t_area;
+      t_area += blk_align256((size_t)QERL_T_PARTS * (size_t)M * (size_t)m[i].r * sizeof(float));
+      ++na;
+    }
+  if (na > 0) {
+    const int rc = aqn_rmsnorm_lora_down(x, M, K, ldx, gain, noise, eps, xn, K, A, r, t, na, stream);
+    if (rc != QERL_ERR_SHAPE) return rc;
+    for (int i = 0; i < n; ++i) m[i].t_f32 = nullptr;   // (rows beyond 8192: the linears compute t themselves)
+  }
+  return aqn_rmsnorm(x, M, K, ldx, gain, noise, eps, xn, K, stream);
+}
+
 }  // namespace qerl
 
 using namespace qerl;
@@ -110,35 +140,35 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
   if (M == 0 && launch) return QERL_OK;
   const size_t lin = nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)K * sizeof(uint16_t)) : 0;
+  const size_t separate_bytes = lin + xn_bytes + (gain && M < kBlkPanelTokens ? blk_t_bytes(M, d, n) : 0);
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 1;
     int rc = blk_fill_stage(a.st[0], launch ? x : (const void*)(uintptr_t)256, K, ldx, gain, noise, eps, d, n, false);
     if (rc != QERL_OK) return rc;
-    // from kBlkSeparateTokens on the separate launches are faster; a workspace with room for the one launch only still gets it
-    if (M < kBlkSeparateTokens || (launch && bytes < lin + xn_bytes))
+    if ((!gain && M < kBlkPanelTokens) || M == 0 || (launch && bytes < separate_bytes))
       return blk_plan_and_launch(a, (uint8_t*)workspace, bytes, 0, launch, need, (hipStream_t)stream);
     size_t one = 0;
     rc = blk_plan_and_launch(a, nullptr, 0, 0, false, &one, nullptr);   // shapes that the one launch does not take stay refused
     if (rc != QERL_OK) return rc;
-    if (need) *need = one > lin + xn_bytes ? one : lin + xn_bytes;
+    if (need) *need = one > separate_bytes ? one : separate_bytes;
     if (launch && bytes < one) return QERL_ERR_WORKSPACE;
   } else if (need) {
-    *need = lin + xn_bytes;
+    *need = separate_bytes;
   }
-  // more tokens: the norm's launch (output in the workspace), then the grouped linear
+  // the norm's launch (output in the workspace), then the grouped linear
   if (!launch) return QERL_OK;
-  if (!workspace || !aligned(workspace, 256) || bytes < lin + xn_bytes) return QERL_ERR_WORKSPACE;
+  if (!workspace || !aligned(workspace, 256) || bytes < separate_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
   int64_t ldin = ldx;
+  qerl_linear_desc own[kMaxGroup];
+  for (int i = 0; i < n; ++i) { own[i] = members[i]; own[i].t_f32 = nullptr; }   // this entry point computes t itself
   if (gain) {
     uint16_t* xn = (uint16_t*)((uint8_t*)workspace + lin);
-    const int rc = aqn_rmsnorm(x, M, K, ldx, gain, noise, eps, xn, K, stream);
+    const int rc = blk_norm(x, M, K, ldx, gain, noise, eps, xn, own, n, (uint8_t*)workspace + lin + xn_bytes, stream);
     if (rc != QERL_OK) return rc;
     xin = xn; ldin = K;
   }
-  qerl_linear_desc own[kMaxGroup];
-  for (int i = 0; i < n; ++i) { own[i] = members[i]; own[i].t_f32 = nullptr; }   // this entry point computes t itself
   return nvfp4_lora_linear_packed_group(xin, M, K, ldin, own, n, workspace, lin, stream);
 }
 
@@ -175,8 +205,9 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   const size_t lin_dn = nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
   const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)H * sizeof(uint16_t)) : 0;
-  const size_t separate_bytes = lin + xn_bytes + 2 * act_bytes;
-  const bool separate = M >= kBlkSeparateTokens && !down->bias_bf16 && (!launch || bytes >= separate_bytes);
+  const qerl_linear_desc* gu_d[2] = {gate, up};
+  const size_t separate_bytes = lin + xn_bytes + 2 * act_bytes + (gain && M < kBlkPanelTokens ? blk_t_bytes(M, gu_d, 2) : 0);
+  const bool separate = M > 0 && !down->bias_bf16 && (!launch || bytes >= separate_bytes);
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 2;
@@ -209,7 +240,7 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
       return launch_block(a, lds, MR, (hipStream_t)stream);
     }
   }
-  // more tokens: norm, grouped gate + up, down on the gated input, as separate launches; the intermediates live in
+  // norm, grouped gate + up, down on the gated input, as separate launches; the intermediates live in
   // the workspace behind the linear's own area
   if (need) *need = separate_bytes;
   if (!launch) return QERL_OK;
@@ -217,15 +248,15 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   if (!ws || !aligned(ws, 256) || bytes < separate_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
   int64_t ldin = ldx;
-  if (gain) {
-    uint16_t* xn = (uint16_t*)(ws + lin);
-    const int rc = aqn_rmsnorm(x, M, H, ldx, gain, noise, eps, xn, H, stream);
-    if (rc != QERL_OK) return rc;
-    xin = xn; ldin = H;
-  }
   qerl_linear_desc gu[2] = {*gate, *up};
   gu[0].y_bf16 = ws + lin + xn_bytes; gu[0].ldy = I; gu[0].t_f32 = nullptr;
   gu[1].y_bf16 = ws + lin + xn_bytes + act_bytes; gu[1].ldy = I; gu[1].t_f32 = nullptr;
+  if (gain) {
+    uint16_t* xn = (uint16_t*)(ws + lin);
+    const int rc = blk_norm(x, M, H, ldx, gain, noise, eps, xn, gu, 2, ws + lin + xn_bytes + 2 * act_bytes, stream);
+    if (rc != QERL_OK) return rc;
+    xin = xn; ldin = H;
+  }
   uint16_t* act = (uint16_t*)(ws + lin + xn_bytes);   // gate's place: the fused form stores no gate
   int rc = packed_gate_up_act(xin, M, H, ldin, gu, ws, lin, act, stream);
   if (rc == QERL_OK) {
