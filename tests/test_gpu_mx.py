@@ -63,6 +63,30 @@ def test_mxfp8_activation_quantize_bit_exact(M, K):
     assert np.array_equal(c.cpu().numpy(), rc)
 
 
+@pytest.mark.parametrize("M,K", [(1, 32), (3, 512), (9, 544), (130, 1056), (2051, 5120)])
+def test_mxfp8_quantize_of_any_bits_with_and_without_wide_loads(M, K):
+    """Rows that 16-byte loads may read and rows offset by four bytes go to different kernels: the same bytes, over all bf16 bit
+    patterns (infinities and NaNs too), and the oracle's where the values are finite."""
+    print("mxfp8 any bits", M, K, flush=True)
+    g = torch.Generator().manual_seed(M + K)
+    bits = torch.randint(0, 1 << 16, (M, K), generator=g, dtype=torch.int32)
+    near = torch.randint(0, 256, (M, K // 32, 1), generator=g, dtype=torch.int32)       # most blocks: exponents that lie close together
+    exp = (near - torch.randint(0, 20, (M, K // 32, 32), generator=g, dtype=torch.int32)).clamp(0, 254).reshape(M, K)
+    bits = torch.where((torch.arange(K) // 32 % 4 != 3)[None, :], (bits & 0x807f) | (exp << 7), bits)
+    x = bits.to(torch.int16).view(torch.bfloat16)
+    wide = torch.zeros((M, K + 8), dtype=torch.bfloat16, device="cuda")
+    wide[:, 2:K + 2] = x.cuda()
+    c, s = qerl.mxfp8_quantize(x.cuda())
+    co, so = qerl.mxfp8_quantize(wide[:, 2:K + 2])
+    assert torch.equal(s, so) and torch.equal(c, co)
+    finite = torch.isfinite(x.float().reshape(M, K // 32, 32)).all(-1)
+    xf = torch.where(finite.repeat_interleave(32, 1), x.float(), torch.zeros(()))
+    rc, rs = mx.mxfp8_quantize(xf.numpy())
+    f = finite.numpy()
+    assert np.array_equal(s.cpu().numpy()[f], rs[f])
+    assert np.array_equal(c.cpu().numpy().reshape(M, K // 32, 32)[f], rc.reshape(M, K // 32, 32)[f])
+
+
 def _pack_reference(codes, scales):
     """Tiles of 32 rows x 256 inputs, 4352 bytes: step j (64 inputs) holds, for lane l = (n = l % 32, g = l // 32),
     the 16 code bytes of inputs 64 j + 32 g .. + 31 of row n at j * 1024 + l * 16 and their scale byte at 4096 + 4 l + j."""
