@@ -169,6 +169,9 @@ struct GemmArgs {
   // tiles of all adapters; member i owns tiles [g_tile0[i], g_tile0[i+1]) and has its own A, ts and scales
   int g_n; int g_tile0[kMaxGroup + 1]; const uint16_t* g_A[kMaxGroup]; const uint16_t* g_ts[kMaxGroup]; int64_t g_ts_ld[kMaxGroup];
   int g_r[kMaxGroup]; float g_lora_scale[kMaxGroup]; const float* g_tensor_scale[kMaxGroup];
+  // launch_lora_down_gemm only, where lora_down_quantizes says so: the launch also leaves x as MXFP8, codes [M, K] and scale
+  // bytes [M, K / 32] (K a multiple of 32, xq to 8 bytes); or null
+  uint8_t* xq; uint8_t* xsc;
 };
 int launch_gemm(const GemmArgs& a, hipStream_t st);
 // its members by 128 x 256 tiles (linear_prefill.hip): one launch, the down-projections done; false: not this launch
@@ -180,6 +183,7 @@ size_t gemm_split_bytes(int64_t M, int64_t N_total);   // scratch worth offering
 constexpr int kDownMaxSlots = 256;                                           // workgroups of a K-split LoRA down-projection
 constexpr size_t kDownExchangeBytes = (size_t)16 << 20;   // the K-parts' partial sums (32-token kernel: kDownMaxSlots workgroups of two 32 x 32 tiles; 64-token kernel: up to eight tiles per wave quartet)
 int launch_lora_down_gemm(const GemmArgs& a, hipStream_t st);
+bool lora_down_quantizes(int64_t M, int64_t K, int64_t r);
 
 // ---- 9..128 tokens: matrix instructions over units of rows, sums in the workspace, a second launch (linear_panel.hip) ----
 constexpr int kPanelMaxTokens = 1024;

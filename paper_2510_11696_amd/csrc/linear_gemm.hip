@@ -26,6 +26,7 @@
 //
 // Operand layouts and the packed tile format are described in linear_decode.hip.
 #include "linear.hpp"
+#include "mxfp8.hpp"
 #include "lora_down.hpp"
 
 namespace qerl {
@@ -395,7 +396,9 @@ __global__ __launch_bounds__(512) void lora_down32_kernel(const GemmArgs a) {
 // GEMM above).  Wave w owns token half w & 1 and the rank tiles (w >> 1), (w >> 1) + 2, ...: no sums across waves.
 // K-parts meet in the workspace as in lora_down_block: the workgroup that arrives last adds them in part order.
 // The adapters come in the group form of GemmArgs (g_*); ts as lora_down_block writes it.
-template <int TPW>   // rank tiles per wave
+// Q: every slab of x also leaves as MXFP8 (the thread layout of the requests has a block of 32 in four neighbouring lanes),
+// while its matrix instructions run: one pass over x and one launch less for the MX linear.
+template <int TPW, bool Q>   // TPW: rank tiles per wave
 __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, const int n_tiles, const int P) {
   constexpr int T = 2 * TPW;                      // rank tiles held in LDS (the last one a repeat when n_tiles is odd)
   constexpr int kXChunks = 64 * 8, kAChunks = T * 32 * 8;
@@ -467,6 +470,19 @@ __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, cons
       base[kXChunks + row * 8 + (lchunk ^ ((row >> 1) & 7))] = sl.w[i];
     }
   };
+  auto quantize = [&](int s, const u32x4& q0, const u32x4& q1, bool in) {
+    const int64_t k = k_lo + (int64_t)s * 64 + lchunk * 8;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      uint32_t sbyte;
+      const uint2 out = mxfp8_encode8(i == 0 ? q0 : q1, sbyte);
+      const int64_t m = m0 + lrow + 32 * i;
+      if (in && m < a.M) {
+        *reinterpret_cast<uint2*>(a.xq + m * a.K + k) = out;
+        if ((lchunk & 3) == 0) a.xsc[m * (a.K >> 5) + (k >> 5)] = (uint8_t)sbyte;
+      }
+    }
+  };
   // With one tile per wave the parts are up to twice as long (down64_parts): every second slab is summed in a chain of its own,
   // so that the fp32 chains stay as short, at no cost (0.4 %; sums slab by slab, added up: 3 %).
   constexpr int kChains = TPW == 1 ? 2 : 1;
@@ -501,11 +517,14 @@ __global__ __launch_bounds__(256) void lora_down64_kernel(const GemmArgs a, cons
       for (int u = 0; u < D; ++u) {
         const int buf = (s0 + u) & 1;   // consecutive slabs alternate (D may be odd)
         to_lds(buf, ring[u]);
+        const u32x4 q0 = ring[u].x[0], q1 = ring[u].x[1];
+        const bool q_in = ring[u].in;
         __builtin_amdgcn_sched_barrier(0);   // the requests stay here, D slabs ahead of their use
         load(ring[u], s0 + u + D);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         compute(buf, kChains == 2 && (u & 1) ? odd : acc);
+        if constexpr (Q) quantize(s0 + u, q0, q1, q_in);
       }
     }
     if constexpr (kChains == 2) {
@@ -914,18 +933,23 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
 static int g_down64_min_tokens = 256;
 static int g_down64_parts = 0;   // tuning: force the number of K-parts (0 = automatic)
 
-template <int TPW>
-static int launch_down64_t(const GemmArgs& a, int n_tiles, int P, dim3 grid, hipStream_t st) {
+template <int TPW, bool Q>
+static int launch_down64_q(const GemmArgs& a, int n_tiles, int P, dim3 grid, hipStream_t st) {
   constexpr size_t lds = 2 * ((size_t)64 * 8 + (size_t)2 * TPW * 32 * 8) * sizeof(u32x4);   // up to 80 KB
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&lora_down64_kernel<TPW>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&lora_down64_kernel<TPW, Q>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return launch_status();
     attr_set = true;
   }
-  lora_down64_kernel<TPW><<<grid, 256, lds, st>>>(a, n_tiles, P);
+  lora_down64_kernel<TPW, Q><<<grid, 256, lds, st>>>(a, n_tiles, P);
   return launch_status();
+}
+
+template <int TPW>
+static int launch_down64_t(const GemmArgs& a, int n_tiles, int P, dim3 grid, hipStream_t st) {
+  return a.xq ? launch_down64_q<TPW, true>(a, n_tiles, P, grid, st) : launch_down64_q<TPW, false>(a, n_tiles, P, grid, st);
 }
 
 // K-parts of the 64-token kernel: at most 32, at least 512 columns each.  Two and more tiles per wave: until every CU has a
@@ -949,6 +973,8 @@ static int64_t down64_parts(int64_t tbs, int64_t K, int tpw) {
   }
   return best;
 }
+
+bool lora_down_quantizes(int64_t M, int64_t K, int64_t r) { return M >= g_down64_min_tokens && ceil_div(r, 32) <= 8 && K % 32 == 0; }
 
 static int launch_lora_down64(const GemmArgs& a0, hipStream_t st) {
   GemmArgs a = a0;

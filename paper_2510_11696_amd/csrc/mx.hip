@@ -33,7 +33,8 @@
 //                          flight while the current one is multiplied), the seven partial tiles are added
 //                          through LDS in wave order by the eighth wave, which also stores.  Bound by streaming the packed weights:
 //                          0.53125 B per weight.
-//   mx_gemm_kernel         more tokens: x quantised by a launch of mxfp8_quantize_rows_kernel, then a GEMM with
+//   mx_gemm_kernel         more tokens: x quantised by a launch of mxfp8_quantize_rows_kernel (with an adapter and 256 tokens or
+//                          more: on the way through the down-projection, whose launch reads all of x), then a GEMM with
 //                          128 x 256 tiles on the same instruction (described at the kernel).
 // The LoRA branch of Eq. (2) rides on both: the adapter reads bf16 x (a launch of the NVFP4 path's down-projection
 // kernels leaves lora_scale * x A^T as three bf16 terms), and the up-projection is 3 r more input columns on the bf16
@@ -454,7 +455,7 @@ static int launch_mx(const MxArgs& a, int NG, int grid, hipStream_t st) {
 }
 
 // ---- more than 32 tokens: a GEMM on the block-scaled matrix instruction ---------------------------------------
-// y = MXFP8(x) . MXFP4(W)^T, x quantised beforehand (mxfp8_quantize_rows_kernel) into codes [M, K] and scales [M, K / 32].
+// y = MXFP8(x) . MXFP4(W)^T, x quantised beforehand into codes [M, K] and scales [M, K / 32].
 // No conversion arithmetic at all: packed weights go global -> registers -> matrix instruction.  The shape of
 // linear_prefill.hip: four waves own 128 tokens x 256 rows, a wave 64 of the rows for all tokens, two workgroups share a CU.
 // A stage is 128 inputs, two instruction steps of 2 x 4 tiles: x slabs (128 tokens x 128 bytes) go to LDS directly, three
@@ -700,6 +701,7 @@ extern "C" int mxfp4_prepack(const uint8_t* codes, const uint8_t* scales, int64_
 }
 
 // beyond the decode kernel's 32 tokens: x as MXFP8 codes and scales
+static uint8_t* mx_scales_of(uint8_t* xq, int64_t M, int64_t K) { return xq + (((size_t)M * (size_t)K + 255) & ~(size_t)255); }
 static size_t mx_gemm_workspace(int64_t M, int64_t K) {
   auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
   return al((size_t)M * (size_t)K) + al((size_t)M * (size_t)(K / 32));
@@ -749,7 +751,7 @@ static MxLoraWorkspace mx_lora_workspace(int64_t M, int64_t N, int64_t K, int64_
   return w;
 }
 
-struct MxLora { const uint16_t* ts; int64_t ts_ld; int n_chunks; const uint16_t* B; int r; const uint16_t* bias; };
+struct MxLora { const uint16_t* ts; int64_t ts_ld; int n_chunks; const uint16_t* B; int r; const uint16_t* bias; bool quantized; };   // quantized: x has been, by the down-projection
 
 static int mx_linear(const void* x, int64_t M, int64_t K, int64_t ldx, const void* packed, int64_t N, void* y, int64_t ldy,
                      const MxLora& lo, void* workspace, size_t workspace_bytes, hipStream_t st) {
@@ -758,9 +760,11 @@ static int mx_linear(const void* x, int64_t M, int64_t K, int64_t ldx, const voi
     const size_t need = mx_gemm_workspace(M, K);
     if (!workspace || !aligned(workspace, 256) || workspace_bytes < need) return QERL_ERR_WORKSPACE;
     uint8_t* xq = (uint8_t*)workspace;
-    uint8_t* xsc = xq + (((size_t)M * (size_t)K + 255) & ~(size_t)255);
-    int rc = launch_mxfp8_quantize(x, M, K, ldx, xq, xsc, st);
-    if (rc != QERL_OK) return rc;
+    uint8_t* xsc = mx_scales_of(xq, M, K);
+    if (!lo.quantized) {
+      const int rc = launch_mxfp8_quantize(x, M, K, ldx, xq, xsc, st);
+      if (rc != QERL_OK) return rc;
+    }
     MxGemmArgs g{};
     g.xq = xq; g.xs = xsc; g.M = M; g.K = K; g.packed = (const uint8_t*)packed;
     g.k_tiles = (int)ceil_div(K, 256); g.n_tiles = (int)ceil_div(N, 32); g.N = N; g.y = (uint16_t*)y; g.ldy = ldy;
@@ -836,6 +840,11 @@ extern "C" int mxfp4_lora_linear_native(const void* x, int64_t M, int64_t K, int
     d.tensor_scale = one; d.lora_scale = lora_scale; d.r = (int)r;
     d.ts = (const uint16_t*)(ws + L.ts_off); d.ts_ld = L.ts_ld;
     d.tpart = (uint32_t*)(ws + L.tpart_off); d.counters = (uint32_t*)(ws + L.ctr_off);
+    lo.quantized = M > 32 && lora_down_quantizes(M, K, r);   // (5120 x 13824, r = 64, 2048 tokens: 198 -> 193 us; 5120 x 13824, r = 128, 777 tokens: 140 -> 135)
+    if (lo.quantized) {
+      d.xq = ws + L.base_off;
+      d.xsc = mx_scales_of(d.xq, M, K);
+    }
     rc = launch_lora_down_gemm(d, st);
     if (rc != QERL_OK) return rc;
     lo.ts = d.ts; lo.ts_ld = L.ts_ld; lo.n_chunks = L.n_chunks; lo.B = (const uint16_t*)B; lo.r = (int)r;

@@ -87,6 +87,21 @@ def test_mxfp8_quantize_of_any_bits_with_and_without_wide_loads(M, K):
     assert np.array_equal(c.cpu().numpy().reshape(M, K // 32, 32)[f], rc.reshape(M, K // 32, 32)[f])
 
 
+@pytest.mark.parametrize("M,K,r", [(255, 544, 16), (256, 32, 8), (257, 1056, 72), (700, 13824, 64), (2051, 2592, 128)])
+def test_mx_lora_linear_quantises_x_like_the_plain_one(M, K, r):
+    """From 256 tokens the launch of the down-projection quantises x too.  With B = 0 the adapter adds zeros: the same bytes as the
+    linear without one, which quantises in a launch of its own; on rows with a stride and a second pass on the same workspace too."""
+    print("mx lora quantise", M, K, r, flush=True)
+    N = 96
+    wide = qs.activations(M, K + 8, 40 + M).cuda()
+    w = qerl.mxfp4_prepack(*qerl.mxfp4_quantize(qs.activations(N, K, 41).cuda()))
+    A, B = qs.activations(r, K, 42).cuda(), torch.zeros((N, r), dtype=torch.bfloat16, device="cuda")
+    wk = qerl.Workspace(qerl.load_library().mxfp4_lora_linear_native_workspace_bytes(M, N, K, r))
+    for x in (wide[:, :K], wide[:, 8:].contiguous()):
+        ref = qerl.mxfp4_linear_native(x, w)
+        assert torch.equal(qerl.mxfp4_lora_linear_native(x, w, A, B, 2.0, workspace=wk), ref)
+
+
 def _pack_reference(codes, scales):
     """Tiles of 32 rows x 256 inputs, 4352 bytes: step j (64 inputs) holds, for lane l = (n = l % 32, g = l // 32),
     the 16 code bytes of inputs 64 j + 32 g .. + 31 of row n at j * 1024 + l * 16 and their scale byte at 4096 + 4 l + j."""
