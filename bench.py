@@ -125,9 +125,9 @@ class Stack:
         self.packed_bytes_per_layer = weights.packed_bytes_per_layer
         self.flops_per_layer = sum(2 * M * s.N * s.K for s in cfg["linears"])
         # Decode (up to 16 tokens) of a decoder block: down reads SiLU(gate) * up of this step's gate / up outputs,
-        # and each of {norm, q, k, v} and {norm, gate, up, SiLU-mul, down} can go out as ONE persistent launch
-        # (block_kernel) or as the separate launches (norm + LoRA down-projections, the grouped stream_kernel,
-        # stream_kernel with the SiLU-mul prologue).  Both compute the same thing; which is faster depends on the
+        # and each of {norm, q, k, v} and {norm, gate, up, SiLU-mul, down} can go out as one composed call ("fused": the
+        # library chooses its launches) or as one call per operator (norm + LoRA down-projections, the grouped linear,
+        # the linear with the SiLU-mul prologue).  Both compute the same thing; which is faster depends on the
         # shapes, so the stack times both over all layers when it is set up and keeps the faster ("auto").
         self.decode_block = self.block and M <= 16
         self.plan = {"qkv": "separate", "mlp": "separate"}
@@ -275,21 +275,21 @@ def measured_traffic(kernel: str, config_no: int, shape_name: str, M: int):
 
 def dominant_kernel_roofline(stack: Stack, reps: int):
     """Average duration of one launch of the kernel most of the step's bytes / flops go through, run back
-    to back over every layer's distinct weights.  Decode (M <= 16): the feed-forward block's single launch of
-    block_kernel where the step uses it, else the grouped gate_proj + up_proj launch of stream_kernel, fed
+    to back over every layer's distinct weights.  Decode (M <= 16): the feed-forward block's composed call
+    where the step uses it, else the grouped gate_proj + up_proj launch of stream_kernel, fed
     with the LoRA down-projections the norm's launch left in memory, exactly as in the step.  M > 16: the grouped
     gate_proj + up_proj call of the step (the LoRA down-projection's launch belongs to it), or the largest linear
     where the configuration is not a decoder block; priced against HBM or MFMA, whichever binds it at the peaks."""
     by = {s.name: s for s in stack.cfg["linears"]}
     kernel = None
     if stack.decode_block and stack.plan["mlp"] == "fused":
-        # the feed-forward block's persistent launch: norm, gate + up, SiLU-mul and down in block_kernel
+        # the feed-forward block's composed call: norm, gate + up, SiLU-mul and down, named by the kernel that streams the weights
         def sweep():
             for L in stack.layers:
                 stack.mlp(L, "fused")
         shape = {"name": "norm+gate+up+silu_mul+down", "N": by["gate"].N, "K": by["gate"].K, "M": stack.M}
         bytes_per_launch = sum(by[n].packed_bytes for n in ("gate", "up", "down"))
-        kernel = "block_kernel" if stack.M <= 8 else "panel_kernel"   # (the call itself sends 9 tokens and more as separate launches)
+        kernel = "stream_kernel" if stack.M <= 8 else "panel_kernel"
     elif stack.M <= 16:
         names = ("gate", "up") if stack.block else (stack.cfg["linears"][0].name,)
         for L in stack.layers[:1]:          # any valid t will do for timing: it only feeds the up-projection
@@ -331,7 +331,7 @@ def dominant_kernel_roofline(stack: Stack, reps: int):
     # which roof binds the launch at the published peaks, and the kernel that runs it (up to 128 tokens: panel_kernel)
     t_hbm = bytes_per_launch / (HBM_PEAK_GBS * 1e9)
     t_mfma = 2 * stack.M * shape["N"] * shape["K"] / (MFMA_BF16_PEAK_TFLOPS * 1e12)
-    kernel = kernel or ("stream_kernel" if stack.M <= 16 else "panel_kernel" if stack.M <= 128 else "gemm32_kernel")
+    kernel = kernel or ("stream_kernel" if stack.M <= 16 else "panel_kernel" if stack.M <= 128 else "prefill_kernel")
     if stack.M <= 16 or (stack.M <= 128 and t_hbm >= t_mfma):
         achieved = bytes_per_launch / (ms * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",

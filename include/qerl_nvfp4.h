@@ -104,7 +104,8 @@ QERL_API int nvfp4_dequantize(const uint8_t* codes, const uint8_t* scales, const
  *     words sit at fixed offsets, so one workspace sized for the largest call
  *     (every argument at its maximum) serves calls of any smaller shape.
  *     Where the adapters' down-projections run as the first workgroups of the
- *     launch (M <= 128), the other workgroups wait for them: a bounded wait under
+ *     launch and the others wait for them (up to 8 tokens; up to 512 in some
+ *     launches of the GEMM), it is a bounded wait under
  *     the co-residency assumption stated with aqn_rmsnorm_nvfp4_lora_mlp below.  A
  *     wait that gives up writes NaN into y, sets the sticky error word of the
  *     workspace and leaves the hand-over words as they are (the call has already
@@ -208,8 +209,9 @@ typedef struct {
   const float* t_f32;          /* x A^T of this member computed before the call, as aqn_rmsnorm_lora_down
                                   writes it: QERL_T_PARTS partial sums over slices of K, fp32
                                   [QERL_T_PARTS][M][r], 32-byte aligned (the kernel adds them in slice order);
-                                  or NULL: the call computes x A^T itself.  Used at M <= 16 only; larger M
-                                  recompute it. */
+                                  or NULL: the call computes x A^T itself.  Used at M <= 16 only (there a
+                                  member that has it keeps the whole group on the kernels that read it);
+                                  larger M recompute it. */
   const void* bias_bf16;       /* [N] bf16 added to every output row before the one rounding to bf16 (the
                                   q/k/v projections of the Qwen2.5 blocks carry one), or NULL */
 } qerl_linear_desc;
@@ -218,15 +220,13 @@ QERL_API int nvfp4_lora_linear_packed_group(const void* x_bf16, int64_t M, int64
                                             void* workspace, size_t workspace_bytes, void* stream);
 
 /* ---------------------------------------------------------------------------
- * Fused decode launches.  Up to 16 tokens each of these is ONE persistent launch
- * (one workgroup per compute unit) in which the weight stream never stops: the
- * RMSNorm with the noisy gain (Eq. 10; Section 3.3 "Noise Merging": q, k, v share
- * one such norm, gate and up another) is applied while the input is staged, the
- * adapters' down-projections x A^T (Eq. 2) run on a few workgroups of the same
- * launch, and -- in the feed-forward call -- SiLU(gate) (.) up is formed in the
- * epilogue of the gate / up tiles, a device-wide hand-over follows, and down_proj
- * streams on behind it.  For more tokens the same operators run as separate
- * launches (same results contract).
+ * Parts of a decoder block in one call: the RMSNorm with the noisy gain (Eq. 10;
+ * Section 3.3 "Noise Merging": q, k, v share one such norm, gate and up another),
+ * the linears that read it and, in the feed-forward call, SiLU(gate) (.) up and
+ * down_proj.  The call sends a few launches that hand their results through the
+ * workspace.  Up to 16 tokens a workspace too small for those intermediate results
+ * (the size functions returned less in the past) gets ONE persistent launch instead,
+ * one workgroup per compute unit, with the same results contract.
  *
  * aqn_rmsnorm_nvfp4_lora_linear_group:
  *   xn = aqn_rmsnorm(x, gain, noise, eps) rounded to bf16 (gain == NULL: xn = x),

@@ -595,8 +595,8 @@ def _norm_args(x, gain, noise):
 
 def aqn_rmsnorm_nvfp4_lora_linear_group(x, gain, noise, eps, weights, As=None, Bs=None, lora_scales=None,
                                         workspace: Optional[Workspace] = None, outs=None, biases=None):
-    """AQN RMSNorm of x (gain None: x as it is), then the packed linears `weights` on it; one launch up to
-    16 tokens.  Returns the list of outputs."""
+    """AQN RMSNorm of x (gain None: x as it is), then the packed linears `weights` on it, in one call.
+    Returns the list of outputs."""
     lib = load_library()
     M, K, ldx, g_ptr, n_ptr = _norm_args(x, gain, noise)
     n = len(weights)
@@ -630,7 +630,7 @@ def aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(M: int, K: int, Ns, rs) 
 def aqn_rmsnorm_nvfp4_lora_mlp(x, gain, noise, eps, gate: PackedWeight, up: PackedWeight, down: PackedWeight,
                                As=(None, None, None), Bs=(None, None, None), lora_scales=(0.0, 0.0, 0.0),
                                workspace: Optional[Workspace] = None, out: Optional[torch.Tensor] = None):
-    """Feed-forward block: AQN RMSNorm -> gate, up -> SiLU(gate) * up -> down; one launch up to 16 tokens.
+    """Feed-forward block: AQN RMSNorm -> gate, up -> SiLU(gate) * up -> down, in one call.
     As / Bs / lora_scales are (gate, up, down) triples.  Returns down's output [M, down.N]."""
     lib = load_library()
     M, H, ldx, g_ptr, n_ptr = _norm_args(x, gain, noise)

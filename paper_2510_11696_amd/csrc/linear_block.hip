@@ -1,4 +1,5 @@
-// Persistent block kernel for decode (M <= 16 tokens): up to three dependent stages of NVFP4 + LoRA linears in ONE
+// Persistent block kernel for decode (M <= 16 tokens), for workspaces that hold no intermediate results (the composed calls
+// otherwise send separate launches, which are faster: block_api.hip has both sides measured): up to three dependent stages of NVFP4 + LoRA linears in ONE
 // launch, each stage one linear or a group of linears that share their input,
 //
 //   y_g[m,n] = S32_g * sum_b s_g[n,b] * ( sum_{k in block b} x[m,k] * e_g[n,k] )           (Eq. 6)

@@ -1,5 +1,6 @@
-// Prefill-sized NVFP4 + LoRA linear (M > 16 tokens): a bf16 MFMA GEMM that
-// dequantises the tile-packed weights in registers.
+// NVFP4 + LoRA linear for more than 128 tokens: a bf16 MFMA GEMM that dequantises the tile-packed weights in
+// registers, in the tile shapes that launches of few tiles need and in the transposed form of the backward pass; launches that
+// fill the chip with 128 x 256 tiles go to linear_prefill.hip (the launcher below prices both).
 //
 //   y[m,n] = S32 * sum_k x[m,k] * (s[n,k/16] * e[n,k]) + lora_scale * sum_j t[m,j] * B[n,j]
 //                                                                    (Eq. 6, Eq. 2)
