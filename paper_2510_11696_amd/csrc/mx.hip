@@ -496,12 +496,12 @@ __global__ __launch_bounds__(kMxgW * 64, 2) void mx_gemm_kernel(const MxGemmArgs
   const int row0 = wave * 8 + (lane >> 3);
   const uint32_t col = (uint32_t)(((lane & 7) ^ ((row0 >> 1) & 7)) * 16);
   const uint8_t* xbase = uniform_pointer(a.xq + m0 * a.K);
-  uint32_t row_off[XI];
+  int64_t row_off[XI];
 #pragma unroll
   for (int i = 0; i < XI; ++i) {
     int64_t m = row0 + 8 * W * i;
     m = m0 + m < a.M ? m : a.M - 1 - m0;
-    row_off[i] = (uint32_t)(m * a.K) + col;
+    row_off[i] = m * a.K + col;
   }
   auto request_x = [&](int stage, int buf) {
     const uint32_t dst = lds0 + (uint32_t)((buf * kMxgSlab + wave * 64) * 16), k = (uint32_t)stage * 128u;
