@@ -351,7 +351,9 @@ static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, con
     if (act) gemm_us += 5.0 + 6.0 * (double)M * (double)d[0].N / 5.0e6;   // and the elementwise pass
     return panel_estimate_us(a) < gemm_us ? launch_panel(a, st) : QERL_ERR_SHAPE;
   }
-  for (int parts = 1; parts <= 64; parts *= 2) {
+  int64_t tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += ceil_div(d[i].N, kPackTileRows);
+  for (int parts = 1; parts <= 64 && parts <= tiles; parts *= 2) {   // (ranks whose sums alone exceed the area fit in no number of parts)
     bool fits = true;
     for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
     if (!fits) continue;

@@ -563,7 +563,7 @@ __global__ __launch_bounds__(512, PAIR || WIDE ? 2 : 4) void panel_finish_kernel
 
 // ---- host -----------------------------------------------------------------------------------------
 // Fills in the plan: token tiles, units, workgroups and the places of the sums in `area` bytes of workspace.
-// QERL_ERR_SHAPE: not a shape for these kernels (the sums do not fit the area, or x's rows are too far apart).
+// QERL_ERR_SHAPE: not a shape for these kernels (no rows, the sums do not fit the area, or x's rows are too far apart).
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
   if (a.M < 1 || a.M > kPanelMaxTokens || a.K < 16 || a.K % 16 != 0 || a.n_members < 1 || a.n_members > kMaxGroup) return QERL_ERR_SHAPE;
   if ((int64_t)a.M * a.ldx * 2 + a.K * 2 >= (int64_t)1 << 31) return QERL_ERR_SHAPE;   // 32-bit offsets into x
@@ -605,6 +605,7 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
     a.n_lora = (int)(blocks * a.t_parts * a.tbs);
   }
   const int64_t t_bytes = (int64_t)a.t_parts * a.rank_tiles * a.tbs * a.NT * 4096;
+  if (tiles < 1 || t_bytes >= (int64_t)area_bytes) return QERL_ERR_SHAPE;   // no rows, or ranks whose sums alone exceed the area
   const int64_t room = slots - a.n_lora > 1 ? slots - a.n_lora : 1;
   // Units of 256 rows (two K-slices per workgroup, half the sums through LDS) when whole units of that size fill the
   // chip (32B gate + up at 128 tokens 98 us against 111), else of 128 (down 53 against 59); of 64 where few tokens meet few rows,

@@ -1,8 +1,36 @@
 // Host-only exercise of the C ABI under AddressSanitizer / UBSan: argument validation and the planners.
+// The runtime calls that the entry points make are defined here: a launch is written down and nothing runs, so that a call with
+// placeholder pointers walks its whole host path.
 #include <cstdio>
 #include <cstdint>
+#include <cstring>
+#include <map>
+#include <string>
 #include <vector>
 #include "qerl_nvfp4.h"
+
+struct Dim3 { uint32_t x, y, z; };
+static std::map<const void*, std::string>& kernel_names() { static std::map<const void*, std::string> m; return m; }
+static std::vector<std::string> launched;
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* device, unsigned, void*, void*, void*, void*, int*) { kernel_names()[host] = device; }
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+int __hipPushCallConfiguration(Dim3, Dim3, size_t, void*) { return 0; }
+int __hipPopCallConfiguration(Dim3*, Dim3*, size_t*, void**) { return 0; }
+int hipLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void*) { launched.push_back(kernel_names()[f]); return 0; }
+int hipGetLastError() { return 0; }
+int hipFuncSetAttribute(const void*, int, int) { return 0; }
+int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
+int hipGetSymbolAddress(void** p, const void*) { *p = (void*)0x100000; return 0; }
+}
+static int count_launches(const char* kernel) {   // since the last call; null: of any kernel
+  int n = 0;
+  for (const std::string& k : launched) n += !kernel || k.find(kernel) != std::string::npos;
+  return n;
+}
 int main() {
   int bad = 0;
   void* fake = (void*)0x10000;
@@ -47,6 +75,35 @@ int main() {
     bad += mxfp4_lora_linear_native(fake, 4, 64, 64, fake, 8, nullptr, nullptr, 0, 0.f, nullptr, fake, 8, fake, 16, nullptr) != QERL_ERR_WORKSPACE;
   }
   bad += nvfp4_prepack_bytes(27648, 5120) != (size_t)864 * 40 * 2304;
+  // 9..16 tokens, ranks whose sums of x A^T alone exceed the workspace's area: the decode kernels, as below 9 tokens
+  {
+    const int64_t shapes[][4] = {{16, 1024, 1024, 512}, {9, 256, 2048, 512}, {16, 64, 1024, 512}, {9, 32, 1024, 296}, {9, 256, 1024, 384}};
+    for (auto& s : shapes) {
+      const int64_t M = s[0], N = s[1], K = s[2], r = s[3];
+      launched.clear();
+      bad += nvfp4_lora_linear_packed(fake, M, K, K, fake, (const float*)fake, N, fake, fake, r, 1.f, fake, N, fake, nvfp4_lora_linear_workspace_bytes(M, N, K, r), nullptr) != QERL_OK;
+      bad += count_launches("panel") != 0 || count_launches("decode") == 0;
+    }
+    long walks = 0;
+    for (int64_t M = 1; M <= 20; ++M)
+      for (int64_t K : {16, 896, 1024, 1536, 4096})
+        for (int64_t N : {1, 32, 129, 256, 1024, 5000})
+          for (int64_t r : {0, 64, 72, 256, 296, 512, 1096, 4096}) {
+            qerl_linear_desc d[3] = {};
+            const int64_t Ns[3] = {N, 256, 40}, rs[3] = {r, r, 8};
+            int64_t n_sum = 0, r_sum = 0;
+            for (int i = 0; i < 3; ++i) {
+              d[i].packed = fake; d[i].tensor_scale = (const float*)fake; d[i].N = d[i].ldy = Ns[i]; d[i].y_bf16 = fake; d[i].A_bf16 = d[i].B_bf16 = fake;
+              d[i].r = rs[i]; d[i].lora_scale = 1.f;
+              n_sum += Ns[i]; r_sum += rs[i];
+            }
+            bad += nvfp4_lora_linear_packed_group(fake, M, K, K, d, 3, fake, nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum), nullptr) != QERL_OK;
+            bad += nvfp4_lora_linear_packed(fake, M, K, K, fake, (const float*)fake, N, fake, fake, r, 1.f, fake, N, fake, nvfp4_lora_linear_workspace_bytes(M, N, K, r), nullptr) != QERL_OK;
+            bad += nvfp4_lora_linear_packed_swiglu(fake, fake, M, K, K, K, fake, (const float*)fake, N, fake, fake, r, 1.f, fake, N, fake, nvfp4_lora_linear_swiglu_workspace_bytes(M, N, K, r), nullptr) != QERL_OK;
+            walks += 3;
+          }
+    printf("host check: %ld calls walked to their launches\n", walks);
+  }
   printf("host check: %ld sizing calls, %d unexpected results\n", plans, bad);
   return bad != 0;
 }

@@ -83,6 +83,16 @@ def test_wide_launches(M, N, K, r):
     check_linear(y[:, torch.from_numpy(rows).cuda()].contiguous(), ref, ("panel wide", M, N, K, r))
 
 
+@pytest.mark.parametrize("M", [9, 16])
+@pytest.mark.parametrize("N,K,r", [(256, 1024, 512), (32, 1024, 296), (1, 16, 1096)])
+def test_ranks_whose_sums_exceed_the_workspace(M, N, K, r):
+    """9..16 tokens and few rows: x A^T's parts alone take more than the workspace's area, and the decode kernels take the call."""
+    print("panel, large rank", M, N, K, r, flush=True)
+    x, m = qs.activations(M, K, 90 + M), _member(N, K, r, 95 + M)
+    y = qerl.nvfp4_lora_linear_packed(x.cuda(), m["pw"], m["Ad"], m["Bd"], 2.0)
+    check_linear(y, _ref(m, x.float().numpy(), 2.0), ("large rank", M, N, K, r))
+
+
 @pytest.mark.parametrize("M", [9, 16, 33, 100])
 @pytest.mark.parametrize("H,I,r", [(1024, 2736, 16), (512, 400, 72), (512, 4000, 64)])
 def test_feed_forward_block_with_the_gated_second_launch(M, H, I, r):
