@@ -75,7 +75,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
   };
   auto request_x = [&](int stage, int buf) {
     uint32_t k = (uint32_t)stage * (uint32_t)(RC * 16) + col_bytes;
-    k = k < k_cap ? k : k_cap;                   // past the end the other operand is zero; any finite value will do
+    k = k < k_cap ? k : k_cap;                   // past the end: read again, never multiplied
 #pragma unroll
     for (int i = 0; i < XI; ++i)
       lds_request(lds0 + (uint32_t)((buf * kSlab + (i * 8 + wave) * 64) * 16), a.x, row_off[i] + k);
@@ -312,7 +312,10 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       request_x(clamp(s + XB - 1), nbuf);
       asm volatile("" ::: "memory");
       load_w(w[(ring + kPanelRing - 1) % kPanelRing], clamp(s + kPanelRing - 1));
-      if (KW == 2 || 2 * s + (kgrp >> 1) < a.k_tiles) {     // (the last stage of 256 inputs may have one K-tile only)
+      // Steps (16 inputs each) of this wave's slice.  A stage that passes the end of K comes in the tail and stops there: what lies in
+      // the slab beyond K may be an infinity, and zero weights times that are NaN.
+      const int steps = decltype(tail)::value ? (int)((a.K - (int64_t)s * (KW * 64) - kgrp * 64) >> 4) : 4;
+      {
         // The conversions of step j + 1 (at the end: of the next stage's first step) and the x fragments of step j + 1
         // stand between the matrix instructions of step j.
         bf16x8 xf[NT];
@@ -321,6 +324,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
         __builtin_amdgcn_sched_group_barrier(0x100, NT, 0);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+          if (decltype(tail)::value && j >= steps) break;
           bf16x8 wn[RT];
           const PanelWeights<RT>& wr = w[j < 3 ? ring : (ring + 1) % kPanelRing];
 #pragma unroll
@@ -347,12 +351,13 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       buf = buf + 1 == XB ? 0 : buf + 1;
     };
     int s = s0;
-    for (; s + kPanelRing <= s1; s += kPanelRing) {
+    const int full = (int)(a.K / (KW * 64)), s_main = s1 < full ? s1 : full;   // whole stages
+    for (; s + kPanelRing <= s_main; s += kPanelRing) {
 #pragma unroll
       for (int ring = 0; ring < kPanelRing; ++ring) stage(s + ring, ring, std::false_type{});
     }
 #pragma unroll
-    for (int ring = 0; ring < kPanelRing - 1; ++ring) {
+    for (int ring = 0; ring < kPanelRing; ++ring) {
       if (s + ring >= s1) break;
       stage(s + ring, ring, std::true_type{});
     }

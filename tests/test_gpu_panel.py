@@ -83,6 +83,27 @@ def test_wide_launches(M, N, K, r):
     check_linear(y[:, torch.from_numpy(rows).cuda()].contiguous(), ref, ("panel wide", M, N, K, r))
 
 
+@pytest.mark.parametrize("M", [9, 16, 40, 100, 128])
+@pytest.mark.parametrize("N,K", [(96, 16), (160, 272), (129, 1168), (64, 2064), (4100, 144)])
+def test_infinities_in_the_last_inputs_of_a_row(M, N, K):
+    """K no multiple of a stage: what stands beyond it is padding and takes no part, so an infinity among a token's last inputs gives
+    infinities with the weights' signs (and NaN at zero weights), and the other tokens keep their values."""
+    print("panel, infinities", M, N, K, flush=True)
+    x, m = qs.activations(M, K, 150 + M), _member(N, K, 0, 155)
+    clean = qerl.nvfp4_lora_linear_packed(x.cuda(), m["pw"])
+    rows = torch.arange(0, M, 3)
+    x[rows, K - 1 - rows % 8] = torch.where(rows % 2 == 0, float("inf"), float("-inf")).to(torch.bfloat16)
+    y = qerl.nvfp4_lora_linear_packed(x.cuda(), m["pw"]).cpu().float()
+    w = oracle.nvfp4_dequantize(m["codes"], m["scales"], m["ts"])
+    with np.errstate(invalid="ignore"):
+        want = torch.from_numpy((x[rows, K - 1 - rows % 8].double().numpy()[:, None] * w[:, (K - 1 - rows % 8).numpy()].T).astype(np.float32))
+    assert torch.equal(torch.isnan(y[rows]), torch.isnan(want))
+    assert torch.equal(torch.nan_to_num(y[rows], nan=0.0, posinf=1.0, neginf=-1.0), torch.nan_to_num(want, nan=0.0, posinf=1.0, neginf=-1.0))
+    keep = torch.ones(M, dtype=torch.bool)
+    keep[rows] = False
+    assert torch.equal(y[keep], clean.cpu().float()[keep])
+
+
 @pytest.mark.parametrize("M", [9, 16])
 @pytest.mark.parametrize("N,K,r", [(256, 1024, 512), (32, 1024, 296), (1, 16, 1096)])
 def test_ranks_whose_sums_exceed_the_workspace(M, N, K, r):
