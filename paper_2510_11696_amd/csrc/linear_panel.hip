@@ -312,54 +312,73 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       request_x(clamp(s + XB - 1), nbuf);
       asm volatile("" ::: "memory");
       load_w(w[(ring + kPanelRing - 1) % kPanelRing], clamp(s + kPanelRing - 1));
-      // Steps (16 inputs each) of this wave's slice.  A stage that passes the end of K comes in the tail and stops there: what lies in
-      // the slab beyond K may be an infinity, and zero weights times that are NaN.
-      const int steps = decltype(tail)::value ? (int)((a.K - (int64_t)s * (KW * 64) - kgrp * 64) >> 4) : 4;
-      {
-        // The conversions of step j + 1 (at the end: of the next stage's first step) and the x fragments of step j + 1
-        // stand between the matrix instructions of step j.
-        bf16x8 xf[NT];
+      // Each stage is scheduled by itself (four at a time take the compiler minutes).  Boundary here / at the stage's end, us of o and down of the
+      // 7B, 14B and 32B layers together: 128 tokens 185 / 192, 16 tokens 105 / 99.
+      if constexpr (NT == 4) __builtin_amdgcn_sched_barrier(0);
+      // The conversions of step j + 1 (at the end: of the next stage's first step) and the x fragments of step j + 1
+      // stand between the matrix instructions of step j.
+      bf16x8 xf[NT];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) xf[nt] = x_frag(buf, 0, nt);
-        __builtin_amdgcn_sched_group_barrier(0x100, NT, 0);
+      for (int nt = 0; nt < NT; ++nt) xf[nt] = x_frag(buf, 0, nt);
+      __builtin_amdgcn_sched_group_barrier(0x100, NT, 0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (decltype(tail)::value && j >= steps) break;
-          bf16x8 wn[RT];
-          const PanelWeights<RT>& wr = w[j < 3 ? ring : (ring + 1) % kPanelRing];
+      for (int j = 0; j < 4; ++j) {
+        bf16x8 wn[RT];
+        const PanelWeights<RT>& wr = w[j < 3 ? ring : (ring + 1) % kPanelRing];
 #pragma unroll
-          for (int t = 0; t < RT; ++t) wn[t] = dequant8_bf16(wr.c[t][(j + 1) & 3], e4m3_byte_f32(wr.sc[t], (j + 1) & 3));
+        for (int t = 0; t < RT; ++t) wn[t] = dequant8_bf16(wr.c[t][(j + 1) & 3], e4m3_byte_f32(wr.sc[t], (j + 1) & 3));
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-            for (int t = 0; t < RT; ++t) acc[t][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t], xf[nt], acc[t][nt], 0, 0, 0);
-            if (j < 3) xf[nt] = x_frag(buf, j + 1, nt);
+          for (int t = 0; t < RT; ++t) acc[t][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[t], xf[nt], acc[t][nt], 0, 0, 0);
+          if (j < 3) xf[nt] = x_frag(buf, j + 1, nt);
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t) wf[t] = wn[t];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+          for (int t = 0; t < RT; ++t) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // a matrix instruction
+            __builtin_amdgcn_sched_group_barrier(0x002, (19 + NT - 1) / NT, 0);   // its share of the step's conversions
           }
-#pragma unroll
-          for (int t = 0; t < RT; ++t) wf[t] = wn[t];
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-            for (int t = 0; t < RT; ++t) {
-              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                     // a matrix instruction
-              __builtin_amdgcn_sched_group_barrier(0x002, (19 + NT - 1) / NT, 0);   // its share of the step's conversions
-            }
-            if (j < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);            // an x fragment
-          }
+          if (j < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);            // an x fragment
         }
       }
+      if constexpr (NT < 4) __builtin_amdgcn_sched_barrier(0);
       buf = buf + 1 == XB ? 0 : buf + 1;
     };
     int s = s0;
-    const int full = (int)(a.K / (KW * 64)), s_main = s1 < full ? s1 : full;   // whole stages
-    for (; s + kPanelRing <= s_main; s += kPanelRing) {
+    const int full = (int)(a.K / (KW * 64)), s_full = s1 < full ? s1 : full;   // whole stages of 64 KW inputs
+    for (; s + kPanelRing <= s_full; s += kPanelRing) {
 #pragma unroll
       for (int ring = 0; ring < kPanelRing; ++ring) stage(s + ring, ring, std::false_type{});
     }
+    PanelWeights<RT> wlast;
 #pragma unroll
     for (int ring = 0; ring < kPanelRing; ++ring) {
-      if (s + ring >= s1) break;
+      wlast = w[ring];
+      if (ring == kPanelRing - 1 || s + ring >= s_full) break;
       stage(s + ring, ring, std::true_type{});
+    }
+    if (s_full < s1) {
+      // The stage that passes the end of K stops at its last step (16 inputs) inside: what lies in the slab beyond K may be an
+      // infinity, and zero weights times that are NaN.
+      lds_wait_barrier<(XB - 2) * XI>();
+      const int steps = (int)((a.K - (int64_t)full * (KW * 64) - kgrp * 64) >> 4);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (j >= steps) break;
+        bf16x8 wl[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) wl[t] = dequant8_bf16(wlast.c[t][j], e4m3_byte_f32(wlast.sc[t], j));
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8 xf = x_frag(buf, j, nt);
+#pragma unroll
+          for (int t = 0; t < RT; ++t) acc[t][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl[t], xf, acc[t][nt], 0, 0, 0);
+        }
+      }
     }
     add_slices();
     if (kgrp == 0) {
