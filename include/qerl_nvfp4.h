@@ -162,10 +162,11 @@ QERL_API int nvfp4_lora_linear_packed(const void* x_bf16, int64_t M, int64_t K, 
  * one copy per GPU, held until the process ends; the call allocates nothing and
  * frees nothing, and enqueues one small fill kernel (which clears the control
  * words at the front of the array) ahead of the linear's own launches.
- *   Limit: nvfp4_lora_linear_workspace_bytes(M, N, K, r) must not exceed
+ *   Limit: what the call itself needs must not exceed
  *   nvfp4_lora_linear_packed_noalloc_max_bytes(), else QERL_ERR_WORKSPACE and
- *   nothing is enqueued (every single linear of Qwen2.5-7B/14B/32B shape up to
- *   4096 tokens and rank 64 fits).
+ *   nothing is enqueued.  nvfp4_lora_linear_workspace_bytes(M, N, K, r), which
+ *   also covers smaller calls, answers that much or more (every single linear of
+ *   Qwen2.5-7B/14B/32B shape up to 4096 tokens and rank 64 fits).
  *   The sticky error word of a wait that gave up is among the control words the
  *   next call clears: with this entry point only the NaN in y shows it.
  *   All calls on one GPU share that GPU's array: calls that overlap in time on

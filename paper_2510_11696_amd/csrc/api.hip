@@ -66,6 +66,20 @@ static WorkspaceLayout workspace_layout(int64_t M, int64_t N, int64_t K, int64_t
   L.total = L.partial_off + align256(need);
   return L;
 }
+size_t linear_need_bytes(int64_t M, int64_t N, int64_t K, int64_t r) { return workspace_layout(M, N, K, r).total; }
+
+// What the size function answers: the call's own need (all that a call is checked against), and from 17 tokens on the areas that
+// fewer tokens or rows take and this call does not, so that a buffer for the largest call holds every smaller one.
+static size_t linear_bytes_of_largest(int64_t M, int64_t N, int64_t K, int64_t r) {
+  const WorkspaceLayout L = workspace_layout(M, N, K, r);
+  if (M <= 16) return L.total;
+  const size_t panel = panel_area_bytes(M < 128 ? M : 128, N);
+  size_t g = gemm_split_bytes(M, N);
+  if (g == 0 && N > 0) g = kGemmSplitCap;        // tiles enough to fill the chip; a smaller call may split K up to the cap
+  g += kFusedDownBytes;
+  const size_t most = L.partial_off + align256(panel > g ? panel : g);
+  return most > L.total ? most : L.total;
+}
 
 // act[m, k] = bf16(bf16(SiLU(gate[m, k])) * up[m, k]), eight values per thread
 __global__ __launch_bounds__(256) void silu_mul_kernel(const uint16_t* __restrict__ gate, int64_t ldg, const uint16_t* __restrict__ up,
@@ -111,7 +125,7 @@ extern "C" double aqn_sigma(int k, int num_stages, double s0, double s1) {
 }
 
 extern "C" size_t nvfp4_lora_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t r) {
-  return workspace_layout(M, N, K, r).total;
+  return linear_bytes_of_largest(M, N, K, r);
 }
 
 extern "C" int qerl_workspace_init(void* workspace, size_t bytes, void* stream) {
@@ -455,7 +469,7 @@ extern "C" int nvfp4_lora_linear_packed(const void* x, int64_t M, int64_t K, int
 }
 
 extern "C" size_t nvfp4_lora_linear_swiglu_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t r) {
-  return workspace_layout(M, N, K, r).total + align256((size_t)(M > 0 ? M : 0) * (size_t)(K > 0 ? K : 0) * sizeof(uint16_t));
+  return linear_bytes_of_largest(M, N, K, r) + align256((size_t)(M > 0 ? M : 0) * (size_t)(K > 0 ? K : 0) * sizeof(uint16_t));
 }
 
 extern "C" int nvfp4_lora_linear_packed_swiglu(const void* gate, const void* up, int64_t M, int64_t K, int64_t ldg, int64_t ldu,

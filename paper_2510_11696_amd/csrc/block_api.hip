@@ -138,7 +138,7 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
   int64_t n_sum = 0, r_sum = 0;
   for (int i = 0; i < n; ++i) { d[i] = members + i; n_sum += members[i].N; r_sum += members[i].r; }
   if (M == 0 && launch) return QERL_OK;
-  const size_t lin = nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
+  const size_t lin = launch ? linear_need_bytes(M, n_sum, K, r_sum) : nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)K * sizeof(uint16_t)) : 0;
   const size_t separate_bytes = lin + xn_bytes + (gain && M < kBlkPanelTokens ? blk_t_bytes(M, d, n) : 0);
   if (M <= 16) {
@@ -201,8 +201,9 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   if (M == 0 && launch) return QERL_OK;
   if (launch && (!down->y_bf16 || down->ldy < down->N)) return down->y_bf16 ? QERL_ERR_SHAPE : QERL_ERR_NULL;
   const size_t act_bytes = blk_align256((size_t)(M > 0 ? M : 1) * (size_t)I * sizeof(uint16_t));
-  const size_t lin_gu = nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r);
-  const size_t lin_dn = nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
+  const size_t lin_gu = launch ? linear_need_bytes(M, 2 * I, H, gate->r + up->r) : nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r);
+  const size_t lin_dn = launch ? linear_need_bytes(M, down->N, I, down->r) + blk_align256((size_t)M * (size_t)I * sizeof(uint16_t))
+                               : nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
   const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)H * sizeof(uint16_t)) : 0;
   const qerl_linear_desc* gu_d[2] = {gate, up};

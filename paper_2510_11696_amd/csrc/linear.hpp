@@ -209,6 +209,8 @@ struct PanelArgs {
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes);
 int launch_panel(const PanelArgs& a, hipStream_t st);
 double panel_estimate_us(const PanelArgs& a);
+// bytes of workspace that a linear or group of this shape is checked against (the size function may answer more)
+size_t linear_need_bytes(int64_t M, int64_t N, int64_t K, int64_t r);
 // gate_proj and up_proj as nvfp4_lora_linear_packed_group, with act[M, N] = bf16(bf16(SiLU(gate)) * up) in place of their
 // outputs; kNoFusedAct (nothing launched) where the shape has no kernel for it (api.hip)
 constexpr int kNoFusedAct = 1;

@@ -147,6 +147,22 @@ def test_workspace_size_is_monotone_enough(lib):
     assert f(8, 3584, 18944, 32) < 64 << 20
 
 
+def test_linear_workspace_of_the_largest_call_serves_every_smaller_one(lib):
+    """The size functions of the linears never fall when an argument grows, across the kernels' ranges of token counts and of widths
+    whose tiles fill the chip by themselves."""
+    tokens = list(range(1, 300)) + [128 * t + d for t in range(3, 40) for d in (-1, 0, 1)]
+    widths = sorted({64 * i for i in range(1, 300, 7)} | {16 * i for i in range(1, 4000, 111)} | {65408, 65536, 65664})
+    for f in (lib.nvfp4_lora_linear_workspace_bytes, lib.nvfp4_lora_linear_swiglu_workspace_bytes):
+        for N, K, r in ((55296, 5120, 128), (512, 512, 16), (5120, 27648, 64), (9086, 21584, 56), (65536, 128, 0), (1, 16, 4096)):
+            assert (s := [f(M, N, K, r) for M in tokens]) == sorted(s), (N, K, r)
+        for M in (1, 16, 17, 128, 129, 777, 1000, 4096):
+            for K in (512, 5120):
+                assert (s := [f(M, N, K, 64) for N in widths]) == sorted(s), (M, K)
+                assert (s := [f(M, N, K, 64) for N in range(1, 20000, 577)]) == sorted(s), (M, K)
+            assert (s := [f(M, 5120, 16 * K, 64) for K in range(1, 2000, 37)]) == sorted(s), M
+            assert (s := [f(M, 5120, 5120, r) for r in range(0, 520, 8)]) == sorted(s), M
+
+
 def _backward_group_bytes(lib, M, K, members):
     from paper_2510_11696_amd.binding import _BackwardDesc
     d = (_BackwardDesc * len(members))()
