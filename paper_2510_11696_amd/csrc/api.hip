@@ -410,7 +410,6 @@ static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, c
     stream_ok = stream_ok && (d.r == 0 || (d.r <= 64 && d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
     lora_ok = lora_ok && (d.r == 0 || (d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
     t_given = t_given || (d.r > 0 && d.t_f32);
-    lora_ok = lora_ok && !(M <= 16 && d.bias_bf16 && d.r > 64);   // not among the forms that this call takes
     if (d.r > 0 && d.t_f32 && !aligned(d.t_f32, 32)) return QERL_ERR_ALIGN;
   }
   if (M == 0) return QERL_OK;
@@ -520,7 +519,7 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
   uint32_t* partial = (uint32_t*)(ws + L.partial_off);
 
   const bool lora_gemm_ok = r == 0 || (r % 8 == 0 && aligned(A, 16) && aligned(B, 16));
-  if (M >= kPanelMinTokens && M <= kPanelMaxTokens && lora_gemm_ok && !(M <= 16 && bias && r > 64)) {
+  if (M >= kPanelMinTokens && M <= kPanelMaxTokens && lora_gemm_ok) {
     qerl_linear_desc d{packed, tensor_scale, N, A, B, r, lora_scale, y, ldy, nullptr, bias};
     const int rc = panel_group(c.x, M, K, ldx, &d, 1, ws, L, nullptr, c.st);
     if (rc != QERL_ERR_SHAPE) return rc;
