@@ -194,7 +194,8 @@ QERL_API int nvfp4_lora_linear_packed_noalloc(const void* x_bf16, int64_t M, int
  *            nvfp4_lora_linear_workspace_bytes(M, sum of N, K, sum of r).
  * Errors: as nvfp4_lora_linear_packed, plus n_members outside 1..4; a bias with an
  * adapter the fast kernels do not take (rank not a multiple of 8, or above 64 at
- * M <= 16, or A/B not 16-byte aligned): QERL_ERR_SHAPE.
+ * M <= 8 -- at 9..16 tokens where its sums do not fit the workspace --, or A/B not
+ * 16-byte aligned): QERL_ERR_SHAPE.
  */
 #define QERL_T_PARTS 8
 typedef struct {
