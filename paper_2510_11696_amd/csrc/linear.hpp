@@ -185,7 +185,7 @@ constexpr size_t kDownExchangeBytes = (size_t)16 << 20;   // the K-parts' partia
 int launch_lora_down_gemm(const GemmArgs& a, hipStream_t st);
 bool lora_down_quantizes(int64_t M, int64_t K, int64_t r);
 
-// ---- 9..128 tokens: matrix instructions over units of rows, sums in the workspace, a second launch (linear_panel.hip) ----
+// ---- 9..1024 tokens: matrix instructions over units of rows, sums in the workspace, a second launch (linear_panel.hip) ----
 constexpr int kPanelMaxTokens = 1024;
 constexpr size_t kPanelSumsCap = (size_t)32 << 20, kPanelTBytes = (size_t)512 << 10;   // most workspace bytes for the sums of W's and A's rows
 struct PanelMember {
@@ -204,6 +204,7 @@ struct PanelArgs {
   int tbs; int NT; int k_tiles; int KW; int RT; int unit_tiles; int unit_shift; int units; int stages; int rank_tiles; int t_parts; int n_lora;
   // workgroups over the units' stages: every unit in `split` pieces, or (0) `per` stages each, the first `rem` one more
   int n_main; int split; int per; int rem; uint32_t per_inv; uint32_t per1_inv;   // 2^32 / per, 2^32 / (per + 1), rounded up
+  int direct;                                                               // whole units and no adapter: the first launch stores the outputs, there is no second
   float* sums; float* t_sums;                                               // [slot][unit_tiles][NT][1024]; [t_parts][rank_tiles][tbs * NT][1024]
 };
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes);

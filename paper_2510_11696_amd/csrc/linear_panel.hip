@@ -1,20 +1,21 @@
-// NVFP4 + LoRA linear (or a group of linears that read the same x) for 9..128 tokens.
+// NVFP4 + LoRA linear (or a group of linears that read the same x) for 9..128 tokens, and up to 1024 on launches of few rows.
 //
 //   y[m,n] = S32 * sum_k x[m,k] * (s[n,k/16] * e[n,k]) + lora_scale * sum_j t[m,j] * B[n,j],   t = x A^T
 //                                                                    (Eq. 6, Eq. 2)
-// Two launches and no wait between workgroups:
+// Two launches, or without adapters and with whole units one, and no wait between workgroups:
 //
-//   panel_kernel   sums of x against the rows of W and of A.  The weights are cut into units of 128 output rows and
-//                  stages of 256 inputs; the line "unit 0's stages, unit 1's stages, ..." is divided evenly over the
-//                  consumer workgroups (one or two per CU, all resident), so that a launch fills the chip whatever N and K are.
+//   panel_kernel   sums of x against the rows of W and of A.  The weights are cut into units of 64, 128 or 256 output rows and
+//                  stages of 128 or 256 inputs; each unit goes to the consumer workgroups (one or two per CU, all resident) in a whole
+//                  number of pieces where that leaves less than a fifth of them idle, else the line "unit 0's stages, unit 1's stages, ..." is
+//                  divided evenly over them, so that a launch fills most of the chip whatever N and K are.
 //                  Each piece of a unit leaves its fp32 sums in a slot of the workspace.  A's rows are units of
 //                  their own: dense bf16 rows in the same loop, a few K-parts each, by workgroups of the same launch.
 //   panel_finish   adds a unit's slots and t's parts in K order, applies S32, B, lora_scale and bias with one rounding
 //                  (gate / up pairs: SiLU(gate) * up on the rounded values) and stores bf16.
 //
-// A workgroup of eight waves holds 128 rows x all tokens: wave (rgrp, kgrp) owns the two row tiles 2 rgrp, 2 rgrp + 1 and the
-// 64-input slice kgrp of every stage.  Each x fragment read from LDS feeds two matrix instructions (one row tile per
-// wave would need the whole LDS bandwidth at 128 tokens), every weight is dequantised once, and the four slices are
+// A workgroup of eight waves holds a unit's rows x all tokens (of a block of at most 128): wave (rgrp, kgrp) owns one or two row tiles and
+// the 64-input slice kgrp of every stage, of which there are two or four.  Each x fragment read from LDS feeds two matrix instructions (one row tile per
+// wave would need the whole LDS bandwidth at 128 tokens), every weight is dequantised once a token block, and the slices are
 // added through LDS at the end of a piece.  x slabs go from memory to LDS directly (16 bytes per lane, the XOR swizzle
 // applied to the source address), XB - 1 stages ahead; weights into a register ring three stages ahead.  One
 // barrier per stage, which waits for the slab of that stage only: all counts of outstanding loads are exact
@@ -46,7 +47,9 @@ constexpr int kPanelTParts = 8, kPanelTPartsPair = 4;     // most K-parts of t: 
 
 template <int RT> struct PanelWeights { u32x4 c[RT]; uint32_t sc[RT]; };   // one stage of a wave: 64 inputs of its row tiles
 
-template <int NT, int KW, int RT>
+// DIRECT: no adapters, whole units; the outputs are stored here and there is no second launch, nor the sums' way through memory
+// (64 tokens, two launches / one: 512 x 512 10.0 / 6.1 us, 8192 x 1024 12.0 / 7.6, 55296 x 5120 53 / 45).
+template <int NT, int KW, int RT, bool DIRECT>
 __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const PanelArgs a) {
   static_assert(KW == 2 || KW == 4, "a K-slice is one plane of a packed tile");
   constexpr int XB = kPanelSlabs<NT, KW>;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
             f32x4{acc[t][nt][4 * q], acc[t][nt][4 * q + 1], acc[t][nt][4 * q + 2], acc[t][nt][4 * q + 3]};
   };
 
-  if ((int)blockIdx.x < a.n_lora) {
+  if (!DIRECT && (int)blockIdx.x < a.n_lora) {
     // ---- rows of the adapters' A: two rank tiles against every token tile, one K-part in stages of 128 inputs.  Both
     // operands go to LDS row by row (256 bytes of a row per 16 lanes; fetched in operand layout, 32 bytes of 32 rows
     // per request, the same bytes took 3 us a stage); a wave owns one output tile, or with few tokens a share
@@ -313,8 +316,8 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       asm volatile("" ::: "memory");
       load_w(w[(ring + kPanelRing - 1) % kPanelRing], clamp(s + kPanelRing - 1));
       // Each stage is scheduled by itself (four at a time take the compiler minutes).  Boundary here / at the stage's end, us of o and down of the
-      // 7B, 14B and 32B layers together: 128 tokens 185 / 192, 16 tokens 105 / 99.
-      if constexpr (NT == 4) __builtin_amdgcn_sched_barrier(0);
+      // 7B, 14B and 32B layers together: 128 tokens 185 / 192, 16 tokens 105 / 99; ten linears at 64 tokens, end / both 232.6 / 230.3.
+      if constexpr (NT == 2 || NT == 4) __builtin_amdgcn_sched_barrier(0);
       // The conversions of step j + 1 (at the end: of the next stage's first step) and the x fragments of step j + 1
       // stand between the matrix instructions of step j.
       bf16x8 xf[NT];
@@ -381,7 +384,49 @@ __global__ __launch_bounds__(512, NT == 1 ? 4 : 2) void panel_kernel(const Panel
       }
     }
     add_slices();
-    if (kgrp == 0) {
+    if constexpr (DIRECT) {                      // the outputs, as the second launch would round them
+      if (kgrp != 0) return;
+      int col4 = 4 * kg, token = n32;
+      asm volatile("" : "+v"(col4), "+v"(token));   // indexes that depend on the lane alone would be computed before the main loop, and spilled
+      const float S32 = *mem.tensor_scale;
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+        const int64_t n0 = ((int64_t)(ru - mem.unit_begin) * kUnitTiles + rgrp * RT + t) * 32;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[t][nt][i] *= S32;
+        if (mem.bias) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int64_t n = n0 + 8 * (i >> 2) + col4 + (i & 3);
+            const float b = bf16_bits_to_f32(mem.bias[n < mem.N ? n : mem.N - 1]);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[t][nt][i] += b;
+          }
+        }
+        const bool whole = mem.y_vec && n0 + 32 <= mem.N;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          __builtin_amdgcn_sched_barrier(0);     // tile by tile: all addresses at once would be spilled
+          const int tok = (u - ru * a.tbs) * (NT * 32) + nt * 32 + token;
+          if (tok >= a.M) continue;
+          uint16_t* dst = mem.y + (int64_t)tok * mem.ldy + n0 + col4;
+          const int left = (int)(mem.N - n0 - col4 < 32 ? mem.N - n0 - col4 : 32);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const u32x2 w = {pack_bf16x2(acc[t][nt][4 * q], acc[t][nt][4 * q + 1]), pack_bf16x2(acc[t][nt][4 * q + 2], acc[t][nt][4 * q + 3])};
+            if (whole) {
+              *reinterpret_cast<u32x2*>(dst + 8 * q) = w;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (8 * q + e < left) dst[8 * q + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            }
+          }
+        }
+      }
+    } else if (kgrp == 0) {
       float* slot = a.sums + (int64_t)(a.split > 0 ? b : b + u) * (kUnitTiles * NT * 1024);
 #pragma unroll
       for (int t = 0; t < RT; ++t) store(slot + (rgrp * RT + t) * (NT * 1024), t);
@@ -634,9 +679,11 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
   // Units of 256 rows (two K-slices per workgroup, half the sums through LDS) when whole units of that size fill the
   // chip (32B gate + up at 128 tokens 98 us against 111), else of 128 (down 53 against 59); of 64 where few tokens meet few rows,
   // so that half as many pieces of K fill the chip (7B o at 32 tokens 13.1 against 14.8, 14B 15.8 against 18.1; not for a long K
-  // with more than 32 tokens, where twice the slab traffic per weight shows: 32B down at 64 tokens 45 against 40)
+  // with more than 32 tokens, where twice the slab traffic per weight shows: 32B down at 64 tokens 45 against 40).  Of 256 rows too where
+  // that is one round of the chip and units of 128 would be two (40000 x 5120, r = 16, 128 tokens 79 -> 71 us; 50000 x 3584 72 -> 62).
   const int64_t big_units = ceil_div(tiles, 8) * a.tbs;
-  a.KW = (a.NT >= 2 && big_units * 5 >= slots * 4) ? 2 : 4;
+  const bool one_round = a.tbs == 1 && big_units <= slots && ceil_div(tiles, 4) > slots;   // of the large units; of the small ones it would be two
+  a.KW = (a.NT >= 2 && (big_units * 5 >= slots * 4 || one_round)) ? 2 : 4;
   const int64_t one_each = 256 - a.n_lora > 1 ? 256 - a.n_lora : 1;   // consumers at one workgroup per CU
   a.RT = (a.NT <= 2 && a.tbs == 1 && ceil_div(tiles, 4) * 2 <= one_each && (a.NT == 1 || a.k_tiles <= 64)) ? 1 : 2;
   a.unit_shift = a.RT == 1 ? 1 : a.KW == 2 ? 3 : 2;
@@ -668,11 +715,13 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
     int64_t pieces = avail / slot_bytes - a.units + 1;
     pieces = pieces > room ? room : pieces;
     const bool fits = pieces >= 1 && total >= 2 * pieces && total < 65536;
-    if (fits && total / pieces + 2 < ceil_div(a.units, slots) * a.stages) a.n_main = (int)pieces;
+    const int64_t second = 2 + (a.rank_tiles == 0 && !a.pairs ? 6 : 0);   // without adapters whole units need no second launch
+    if (fits && total / pieces + second < ceil_div(a.units, slots) * a.stages) a.n_main = (int)pieces;
     else { a.split = 1; a.n_main = a.units; }
   }
   while (a.split > 1 && a.n_main * slot_bytes > avail) { --a.split; a.n_main = a.units * a.split; }
-  if (a.split == 1 && a.n_main * slot_bytes > avail) return QERL_ERR_SHAPE;
+  a.direct = a.split == 1 && a.rank_tiles == 0 && !a.pairs ? 1 : 0;
+  if (a.split == 1 && (!a.direct || a.tbs > 1) && a.n_main * slot_bytes > avail) return QERL_ERR_SHAPE;   // (beyond 128 tokens: wide enough for the GEMM)
   a.per = (int)(total / a.n_main); a.rem = (int)(total - (int64_t)a.per * a.n_main);
   auto inverse = [](int d) { return d > 1 ? (uint32_t)((((uint64_t)1 << 32) + d - 1) / d) : 0xffffffffu; };
   a.per_inv = inverse(a.per); a.per1_inv = inverse(a.per + 1);
@@ -682,18 +731,23 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
 }
 
 // Time of both launches beyond 128 tokens (blocks of 65 tokens and more): a stage of 256 inputs 1.7 us (three token tiles: 1.4),
-// every slot written and read once at about 4 TB/s, 12 us of fixed chain.  Measured / estimated, us, r = 64: 5120 x 5120, 256 tokens
-// 30 / 32; 5120 x 13824, 256 tokens 52 / 51; 3584 x 18944, 777 tokens (r = 32) 135 / 144; 5120 x 5120, 1000 tokens 92 / 90.
+// every slot written and read once at about 4 TB/s, 12 us of fixed chain, 6 us for each further round of workgroups (A's rows
+// take places of the first: one unit more than the rest holds costs a round).  Measured / estimated, us, r = 64: 5120 x 5120, 256 tokens
+// 30 / 32; 5120 x 13824, 256 tokens 50 / 50; 3584 x 18944, 777 tokens (r = 32) 131 / 144; 18944 x 256, 160 tokens 30 / 28; 4096 x 4096, 1000
+// tokens 73 / 81 (GEMM 67).
 double panel_estimate_us(const PanelArgs& a) {
-  const double per = a.split > 0 ? (double)(ceil_div(a.stages, a.split) * ceil_div(a.n_main, 256)) : (double)(a.per + 2);
+  const int64_t rounds = a.split > 0 ? ceil_div(a.n_main + a.n_lora, 256) : 1;   // (A's rows take their places first)
+  const double per = a.split > 0 ? (double)(ceil_div(a.stages, a.split) * rounds) : (double)(a.per + 2);
   const double stage = (a.NT == 4 ? 1.7 : 1.4) * (a.KW == 2 ? 0.5 : 1.0);
   const double slots = (double)(a.split > 0 ? a.n_main : a.n_main + a.units) * a.unit_tiles * a.NT * 4096.0;
-  return per * stage + 2.0 * slots / 4.0e6 + 12.0;
+  return per * stage + 2.0 * slots / 4.0e6 + 12.0 + 6.0 * (double)(rounds - 1);
 }
 
 template <int NT, int KW, int RT>
 static int launch_panel_t(const PanelArgs& a, hipStream_t st) {
-  panel_kernel<NT, KW, RT><<<dim3((unsigned)(a.n_lora + a.n_main)), dim3(512), (kPanelLds<NT, KW>), st>>>(a);
+  const dim3 grid((unsigned)(a.n_lora + a.n_main));
+  if (a.direct) panel_kernel<NT, KW, RT, true><<<grid, dim3(512), (kPanelLds<NT, KW>), st>>>(a);
+  else panel_kernel<NT, KW, RT, false><<<grid, dim3(512), (kPanelLds<NT, KW>), st>>>(a);
   return launch_status();
 }
 
@@ -705,7 +759,7 @@ int launch_panel(const PanelArgs& a, hipStream_t st) {
       (int64_t)a.k_tiles * kPackTileK < a.K || a.stages * (a.KW / 2) < a.k_tiles || a.units < 1 || a.per < 1 ||
       a.n_main < 1 || (a.split > 0 && (a.n_main != a.units * a.split || a.split > a.stages)) ||
       (int64_t)a.per * a.n_main + a.rem != (int64_t)a.units * a.stages || a.n_lora != ceil_div(a.rank_tiles, 2) * a.t_parts * a.tbs ||
-      a.t_parts > (a.pairs ? kPanelTPartsPair : kPanelTParts) || (a.pairs && (a.n_members != 2 || a.mem[0].N != a.mem[1].N)))
+      (a.direct && (a.split != 1 || a.rank_tiles > 0 || a.pairs)) || a.t_parts > (a.pairs ? kPanelTPartsPair : kPanelTParts) || (a.pairs && (a.n_members != 2 || a.mem[0].N != a.mem[1].N)))
     return QERL_ERR_SHAPE;
   int tiles_max = 0, r_max = 0;
   for (int i = 0; i < a.n_members; ++i) {
@@ -718,7 +772,7 @@ int launch_panel(const PanelArgs& a, hipStream_t st) {
   if (a.RT == 1 && a.KW == 4) rc = a.NT == 1 ? launch_panel_t<1, 4, 1>(a, st) : a.NT == 2 ? launch_panel_t<2, 4, 1>(a, st) : rc;
   else if (a.KW == 4) rc = a.NT == 1 ? launch_panel_t<1, 4, 2>(a, st) : a.NT == 2 ? launch_panel_t<2, 4, 2>(a, st) : a.NT == 3 ? launch_panel_t<3, 4, 2>(a, st) : launch_panel_t<4, 4, 2>(a, st);
   else if (a.RT == 2) rc = a.NT == 2 ? launch_panel_t<2, 2, 2>(a, st) : a.NT == 3 ? launch_panel_t<3, 2, 2>(a, st) : a.NT == 4 ? launch_panel_t<4, 2, 2>(a, st) : rc;
-  if (rc != QERL_OK) return rc;
+  if (rc != QERL_OK || a.direct) return rc;
   const dim3 grid((unsigned)ceil_div(tiles_max, 8), (unsigned)(a.tbs * a.NT), (unsigned)(a.pairs ? 1 : a.n_members));
   const bool wide = r_max > 64;
   if (a.pairs && wide) panel_finish_kernel<true, true><<<grid, dim3(512), 0, st>>>(a);

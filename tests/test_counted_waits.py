@@ -24,8 +24,8 @@ def _panel(nt, kw, rt):
 
 
 # kernel (mangled name) -> {N of the loop's wait: slab requests that may still be under way}
-LOOPS = {f"panel_kernelILi{nt}ELi{kw}ELi{rt}EE": _panel(nt, kw, rt)
-         for nt, kw, rt in [(1, 4, 1), (2, 4, 1), (1, 4, 2), (2, 4, 2), (3, 4, 2), (4, 4, 2), (2, 2, 2), (3, 2, 2), (4, 2, 2)]}
+LOOPS = {f"panel_kernelILi{nt}ELi{kw}ELi{rt}ELb{direct}EE": _panel(nt, kw, rt)
+         for direct in (0, 1) for nt, kw, rt in [(1, 4, 1), (2, 4, 1), (1, 4, 2), (2, 4, 2), (3, 4, 2), (4, 4, 2), (2, 2, 2), (3, 2, 2), (4, 2, 2)]}
 LOOPS["prefill_kernelILi4ELi2ELi4EE"] = {4 + 8: 4}
 LOOPS["mx_gemm_kernel"] = {4 + 8: 4}
 SOURCES = ("linear_panel.hip", "linear_prefill.hip", "mx.hip")

@@ -65,21 +65,53 @@ def test_several_token_blocks(M, K, Ns, rs):
     (30, 24576, 1536, 8),     # the same at two workgroups per CU
     (128, 55296, 384, 8),     # whole units of 256 rows
     (70, 53248, 256, 8),      # the same, three token tiles
-    (128, 70016, 128, 8),     # the sums of all rows do not fit the workspace: several pairs of launches
+    (128, 70016, 128, 8),     # the sums of all rows do not fit the workspace: the GEMM
+    (33, 140032, 128, 8),     # the same up to 64 tokens: several pairs of launches
+    (100, 40000, 768, 8),     # few stages in units of 256 rows: one round of the chip where units of 128 would take two
+    (16, 33024, 512, 8),      # the sums do not fit at 9..16 tokens: the decode kernels
 ])
 def test_wide_launches(M, N, K, r):
+    _wide(M, N, K, r)
+
+
+@pytest.mark.parametrize("M", [9, 16, 17, 33, 65, 128])
+@pytest.mark.parametrize("N,K", [
+    (8200, 512),              # whole units of 128 rows: one launch stores the outputs
+    (1000, 272),              # units of 64 rows up to 64 tokens, a ragged last tile
+    (70016, 384),             # more units than CUs; from 33 tokens on units of 256 rows
+    (4096, 2048),             # units in several pieces: two launches (up to 16 tokens the streaming kernel)
+])
+def test_linears_without_adapters(M, N, K):
+    _wide(M, N, K, 0)
+
+
+def test_outputs_without_adapters_in_one_launch_at_odd_strides():
+    """The first launch stores the outputs of a group: a bias, a leading dimension that allows no 8-byte stores, a ragged member."""
+    for M in (9, 50, 128):
+        K, Ns = 1168, (1000, 33)
+        x = qs.activations(M, K, 50 + M)
+        ms = [_member(N, K, 0, 60 + 3 * i + M, i == 0) for i, N in enumerate(Ns)]
+        wide = torch.full((M, Ns[0] + 3), -5.0, dtype=torch.bfloat16, device="cuda")
+        outs = [wide[:, :Ns[0]], torch.empty((M, Ns[1]), dtype=torch.bfloat16, device="cuda")]
+        qerl.nvfp4_lora_linear_packed_group(x.cuda(), [m["pw"] for m in ms], [None] * 2, [None] * 2, [0.0] * 2, outs=outs, biases=[m["bd"] for m in ms])
+        for i, m in enumerate(ms):
+            check_linear(outs[i], _ref(m, x.float().numpy(), 2.0), ("panel, no adapter", i, M))
+        assert torch.all(wide[:, Ns[0]:] == -5.0)
+
+
+def _wide(M, N, K, r):
     print("panel wide case", M, N, K, r, flush=True)
     gen = torch.Generator().manual_seed(M + N)
     codes = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, generator=gen)
     scales = torch.randint(0x20, 0x50, (N, K // 16), dtype=torch.uint8, generator=gen)
     ts = torch.tensor([0.01], dtype=torch.float32)
-    A, B = qs.lora_pair(N, K, r, 5)
+    A, B = qs.lora_pair(N, K, r, 5) if r else (None, None)
     x = qs.activations(M, K, 6)
     pw = qerl.nvfp4_prepack(codes.cuda(), scales.cuda(), ts.cuda())
-    y = qerl.nvfp4_lora_linear_packed(x.cuda(), pw, A.cuda(), B.cuda(), 2.0)
+    y = qerl.nvfp4_lora_linear_packed(x.cuda(), pw, A.cuda() if r else None, B.cuda() if r else None, 2.0)
     rows = np.unique(np.concatenate([np.arange(0, N, 997), np.arange(0, N, 128), np.arange(127, N, 128), [N - 1]]))
-    ref = oracle.nvfp4_lora_linear(x.float().numpy(), codes.numpy()[rows], scales.numpy()[rows], float(ts), A.float().numpy(),
-                                   B.float().numpy()[rows], 2.0)
+    ref = oracle.nvfp4_lora_linear(x.float().numpy(), codes.numpy()[rows], scales.numpy()[rows], float(ts), A.float().numpy() if r else None,
+                                   B.float().numpy()[rows] if r else None, 2.0)
     check_linear(y[:, torch.from_numpy(rows).cuda()].contiguous(), ref, ("panel wide", M, N, K, r))
 
 
