@@ -23,7 +23,8 @@ static size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // workspace: no call's data region may overlap another call's control words (they must stay zero).
 constexpr size_t kCtrlBytes = kCtrlRegionBytes;
 
-// 17..128 tokens: room for the sums of linear_panel.hip (eight times the outputs in fp32, capped, and a little for t)
+// 17..128 tokens: room for the sums of linear_panel.hip (eight times the outputs in fp32, capped, and a little for t); calls of 9..16 tokens and
+// of more than 128 place them where the other kernels of these counts have their scratch, or do not take those kernels
 static size_t panel_area_bytes(int64_t M, int64_t N) {
   const size_t b = (size_t)8 * (size_t)(M > 0 ? M : 1) * (size_t)(N > 0 ? N : 1) * sizeof(float);
   return align256(b < kPanelSumsCap ? b : kPanelSumsCap) + kPanelTBytes;
@@ -234,10 +235,10 @@ static bool g_use_stream = true;
 // decode kernels' cost follows the tokens in steps of eight, the panel kernels' in steps of 32).
 constexpr int64_t kPanelMinTokens = 9;
 
-// One streaming launch for a group of packed linears sharing x (M <= 16; every r in {0} or 8..64 step 8).
-static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
-                        uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, const uint16_t* x2 = nullptr, int64_t ldx2 = 0) {
-  StreamArgs a{};
+// One streaming launch for a group of packed linears sharing x (M <= 16; every r in {0} or 8..64 step 8): its plan.
+static int stream_plan(StreamArgs& a, size_t* lds, int* MR, const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
+                       const uint16_t* x2 = nullptr, int64_t ldx2 = 0) {
+  a = StreamArgs{};
   a.x = x; a.ldx = ldx; a.M = (int)M; a.K = K; a.k_tiles = (int)ceil_div(K, kPackTileK);
   a.x2 = x2; a.ldx2 = ldx2;
   a.n_members = n;
@@ -268,12 +269,17 @@ static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, co
     int64_t np = ceil_div(2 * (int64_t)a.k_tiles, 8);   // one half K-tile per producer wave and tile pair
     a.n_producers = (int)(np < 1 ? 1 : (np > 16 ? 16 : np));
   }
+  return plan_stream(a, lds, MR);
+}
+static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
+                        uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, const uint16_t* x2 = nullptr, int64_t ldx2 = 0) {
+  StreamArgs a;
   size_t lds = 0;
   int MR = 4;
-  const int prc = plan_stream(a, &lds, &MR);
+  const int prc = stream_plan(a, &lds, &MR, x, M, K, ldx, d, n, x2, ldx2);
   if (prc != QERL_OK) return prc;
   uint32_t* partial = (uint32_t*)(ws + L.partial_off);
-  const size_t part_words = ((size_t)a.Sk * tiles * MR * 64 + 3) & ~(size_t)3;
+  const size_t part_words = ((size_t)a.Sk * a.total_tiles * MR * 64 + 3) & ~(size_t)3;
   a.partial = partial; a.counters = (uint32_t*)ws;
   a.t = (float*)(ws + L.t_off);
   a.lora_ctl = (uint32_t*)ws + L.n_main_ctr + L.n_down_ctr;
@@ -333,8 +339,8 @@ static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, cons
   for (int i = 0; i < n; ++i) n_sum += d[i].N;
   return gemm_with_down(g, dn, tiles, n_sum, ws, L, st, estimate_us);
 }
-// 9..128 tokens, one linear or a group reading the same x, in two launches (linear_panel.hip); where the sums of all rows do
-// not fit the workspace's area, the rows in several parts of two launches each.  act != null: members 0 and 1 are
+// 9..128 tokens, one linear or a group reading the same x, in one or two launches (linear_panel.hip); up to 64 tokens, where the sums
+// of all rows do not fit the workspace's area, the rows in several parts of two launches each.  act != null: members 0 and 1 are
 // gate_proj and up_proj and act = SiLU(gate) (.) up is stored instead of their outputs.
 // Beyond 128 tokens the same kernels take several token blocks, where they are estimated faster than the GEMM: launches of few
 // rows, whose tiles do not fill the chip (5120 x 5120, r = 64, 256 tokens 49 -> 30 us, 3584 x 18944, r = 32, 777 tokens 216 -> 135).
@@ -365,8 +371,32 @@ static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, con
     if (act) gemm_us += 5.0 + 6.0 * (double)M * (double)d[0].N / 5.0e6;   // and the elementwise pass
     return panel_estimate_us(a) < gemm_us ? launch_panel(a, st) : QERL_ERR_SHAPE;
   }
-  int64_t tiles = 0;
-  for (int i = 0; i < n; ++i) tiles += ceil_div(d[i].N, kPackTileRows);
+  int64_t tiles = 0, r_max = 0;
+  bool bias = false;
+  for (int i = 0; i < n; ++i) {
+    tiles += ceil_div(d[i].N, kPackTileRows);
+    r_max = d[i].r > r_max ? d[i].r : r_max;
+    bias = bias || (d[i].bias_bf16 && d[i].r > 64);
+  }
+  // Where the sums do not fit at once, the other kernels of the token count are faster than several pairs of launches: the decode
+  // kernels (r = 32, 9 tokens: 8192 x 512 13.1 us against 17.0), beyond 64 tokens the GEMM (151936 x 3584, r = 16, 100 tokens 165 / 227;
+  // at 64 tokens 155 / 122).  Beyond 64 tokens and K = 512 many rows are the GEMM's as well: writing and reading the sums
+  // takes longer than the product (50000 x 512, r = 16, 100 tokens 22 / 30; 40000 x 1024 30 / 32).
+  const bool one_part = part(0, 1, a) == QERL_OK;
+  if (M > 64 && (!one_part || (K <= 512 && tiles > 1024))) return QERL_ERR_SHAPE;
+  if (M <= 16 && !bias) {   // (the decode kernels take no bias with more than 64 ranks)
+    if (!one_part) return QERL_ERR_SHAPE;
+    if (!act && r_max <= 64) {
+      // The streaming kernel is faster where every CU would have more than one unit and it need not split K (two of 18944 x 3584, r = 32, 9..16
+      // tokens 25 us against 30; 40000 x 5120, r = 16, 9 tokens 31 / 33, but at 12 tokens, K in two ranges, 39 / 34), and
+      // without adapters wherever the panel kernels need their second launch (4096 x 4096, 16 tokens 9.9 / 11.4, 13824 x 5120 in one 17 / 13).
+      StreamArgs sa;
+      size_t lds = 0;
+      int MR = 4;
+      if (a.rank_tiles == 0 && !a.direct) return QERL_ERR_SHAPE;
+      if (a.units > 256 && stream_plan(sa, &lds, &MR, x, M, K, ldx, d, n) == QERL_OK && sa.Sk == 1) return QERL_ERR_SHAPE;
+    }
+  }
   for (int parts = 1; parts <= 64 && parts <= tiles; parts *= 2) {   // (ranks whose sums alone exceed the area fit in no number of parts)
     bool fits = true;
     for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
