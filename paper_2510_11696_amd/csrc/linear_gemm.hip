@@ -669,6 +669,10 @@ constexpr int kCfgTall = 2, kCfgPrefill = 3, kCfgBackward = 4;
 // A workgroup of linear_prefill.hip that has its CU to itself takes 0.58 of the time of a pair (7B gate + up, K = 3584, 777 tokens, 12
 // workgroups beyond two rounds of 512: 214 us, 85 of them a round; 32B down at 4096 tokens, 1.25 rounds: 1020 us, 650 a round)
 constexpr double kPrefillAlone = 0.58;
+// A single round of at most one workgroup per CU takes this much longer than the tiles' arithmetic says, as far as the panel kernels'
+// estimate is concerned (r = 0, us: 3584 + 512 + 512 rows, K = 3584, 777 tokens 59, estimated 34 without; 4096 x 4096, 1000 tokens 57 / 38; 5120 x 5120,
+// 512 tokens 62 / 46; 3584 x 18944, 777 tokens 202 / 155).  Over 348 launches of 160..1000 tokens the choice costs 2.3 % against the faster of both, 6.1 % without.
+constexpr double kGemmAloneEst = 1.4;
 static int g_force_cfg = -1;
 static bool g_split = true;   // whole rounds and remainder as two launches when that is estimated faster
 static int g_force_ksplit = 0;   // tuning: K-parts of the forward launch (0 = automatic, 1 = never)
@@ -923,7 +927,10 @@ int launch_gemm(const GemmArgs& a0, hipStream_t st) {
   }
   if (dry) {
     // the launch's fill, drain and gap, and the down-projections (14 us for one rank tile, 21 for three at 777 tokens)
-    *a.estimate_us = t_final * (double)a.K / 5.6e8 + 6.0 + (a.g_n > 0 ? 11.0 + 3.0 * a.g_tile0[a.g_n] : 0.0);
+    int64_t col_blocks = 0;
+    for (int i = 0; i < a.m_n; ++i) col_blocks += ceil_div(a.m[i].N, (int64_t)kConfigs[best].W * kConfigs[best].NT * 32);
+    const bool alone = t_final == t_single && best != kCfgPrefill && ceil_div(a.M, (int64_t)kConfigs[best].MT * 32) * col_blocks * a.ksplit <= 256;
+    *a.estimate_us = t_final * (double)a.K / 5.6e8 * (alone ? kGemmAloneEst : 1.0) + 6.0 + (a.g_n > 0 ? 11.0 + 3.0 * a.g_tile0[a.g_n] : 0.0);
     return QERL_OK;
   }
   return launch_one(best, a);
