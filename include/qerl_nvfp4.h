@@ -226,9 +226,11 @@ QERL_API int nvfp4_lora_linear_packed_group(const void* x_bf16, int64_t M, int64
  * Section 3.3 "Noise Merging": q, k, v share one such norm, gate and up another),
  * the linears that read it and, in the feed-forward call, SiLU(gate) (.) up and
  * down_proj.  The call sends a few launches that hand their results through the
- * workspace.  Up to 16 tokens a workspace too small for those intermediate results
- * (the size functions returned less in the past) gets ONE persistent launch instead,
- * one workgroup per compute unit, with the same results contract.
+ * workspace.  Up to 16 tokens ONE persistent launch, one workgroup per compute unit
+ * and with the same results contract, serves a group without a norm (up to 8
+ * tokens), a down projection with a bias, and a workspace that holds that launch's
+ * areas but not the intermediate results (the size functions returned less in the
+ * past; up to 8 tokens and K = 8192 the former size holds them).
  *
  * aqn_rmsnorm_nvfp4_lora_linear_group:
  *   xn = aqn_rmsnorm(x, gain, noise, eps) rounded to bf16 (gain == NULL: xn = x),
@@ -243,7 +245,7 @@ QERL_API int nvfp4_lora_linear_packed_group(const void* x_bf16, int64_t M, int64
  * == 0, gain / noise 16-byte aligned; at M <= 16 every adapter needs r % 8 == 0,
  * r <= 64 and 16-byte aligned A and B (QERL_ERR_SHAPE otherwise).
  *   workspace: >= the matching *_workspace_bytes(), 256-byte aligned, prepared once
- *   with qerl_workspace_init(); a linear workspace of that size serves as well (the
+ *   with qerl_workspace_init(); the size for M tokens serves fewer as well; a linear workspace of that size serves as well (the
  *   control words share one layout).  Calls sharing it must be ordered on one stream.
  * Co-residency: the workgroups of these launches (and of the other decode
  * kernels' in-launch hand-overs) wait for each other, which requires that all of

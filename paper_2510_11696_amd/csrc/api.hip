@@ -271,15 +271,20 @@ static int stream_plan(StreamArgs& a, size_t* lds, int* MR, const uint16_t* x, i
   }
   return plan_stream(a, lds, MR);
 }
+// need != null: nothing is launched, *need = the bytes of the workspace that the launch would touch.
 static int stream_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n,
-                        uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, const uint16_t* x2 = nullptr, int64_t ldx2 = 0) {
+                        uint8_t* ws, const WorkspaceLayout& L, hipStream_t st, const uint16_t* x2 = nullptr, int64_t ldx2 = 0, size_t* need = nullptr) {
   StreamArgs a;
   size_t lds = 0;
   int MR = 4;
   const int prc = stream_plan(a, &lds, &MR, x, M, K, ldx, d, n, x2, ldx2);
   if (prc != QERL_OK) return prc;
   uint32_t* partial = (uint32_t*)(ws + L.partial_off);
-  const size_t part_words = ((size_t)a.Sk * a.total_tiles * MR * 64 + 3) & ~(size_t)3;
+  const size_t part_words = a.Sk > 1 ? ((size_t)a.Sk * a.total_tiles * MR * 64 + 3) & ~(size_t)3 : 0;
+  if (need) {
+    *need = align256(L.partial_off + (part_words + (a.r_total > 0 ? kDecodeTpartWords : 0)) * sizeof(uint32_t));
+    return QERL_OK;
+  }
   a.partial = partial; a.counters = (uint32_t*)ws;
   a.t = (float*)(ws + L.t_off);
   a.lora_ctl = (uint32_t*)ws + L.n_main_ctr + L.n_down_ctr;
@@ -345,8 +350,9 @@ static int gemm_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, cons
 // Beyond 128 tokens the same kernels take several token blocks, where they are estimated faster than the GEMM: launches of few
 // rows, whose tiles do not fill the chip (5120 x 5120, r = 64, 256 tokens 49 -> 30 us, 3584 x 18944, r = 32, 777 tokens 216 -> 135).
 // QERL_ERR_SHAPE: not a shape for it (nothing has been launched).
+// need (M <= 128): as in stream_group.
 static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* d, int n, uint8_t* ws,
-                       const WorkspaceLayout& L, uint16_t* act, hipStream_t st) {
+                       const WorkspaceLayout& L, uint16_t* act, hipStream_t st, size_t* need = nullptr) {
   const int64_t k_tiles = ceil_div(K, kPackTileK);
   auto part = [&](int c, int parts, PanelArgs& a) {
     a = PanelArgs{};
@@ -399,8 +405,16 @@ static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, con
   }
   for (int parts = 1; parts <= 64 && parts <= tiles; parts *= 2) {   // (ranks whose sums alone exceed the area fit in no number of parts)
     bool fits = true;
-    for (int c = 0; c < parts && fits; ++c) fits = part(c, parts, a) == QERL_OK;
+    size_t used = 0;
+    for (int c = 0; c < parts && fits; ++c) {
+      fits = part(c, parts, a) == QERL_OK;
+      used = a.used_bytes > used ? a.used_bytes : used;
+    }
     if (!fits) continue;
+    if (need) {
+      *need = align256(L.partial_off + used);
+      return QERL_OK;
+    }
     for (int c = 0; c < parts; ++c) {
       int rc = part(c, parts, a);
       if (rc == QERL_OK) rc = launch_panel(a, st);
@@ -423,8 +437,10 @@ static int packed_single(const void* x, int64_t M, int64_t K, int64_t ldx, const
 
 // act != null: members 0 and 1 are gate_proj and up_proj; act[M, N] = SiLU(gate) (.) up is stored instead of their
 // outputs where the shape has a kernel for it (QERL_OK), else nothing is launched (kNoFusedAct).
+// need != null: nothing is launched, *need = the bytes of the workspace that the call would touch.  exact: up to 16 tokens the workspace may
+// be as small as that (a composed call has sized it), instead of what the public entry point asks for.
 static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* members, int n_members,
-                             void* workspace, size_t workspace_bytes, uint16_t* act, void* stream) {
+                             void* workspace, size_t workspace_bytes, uint16_t* act, void* stream, bool exact = false, size_t* need = nullptr) {
   if (!members) return QERL_ERR_NULL;
   if (n_members < 1 || n_members > kMaxGroup) return QERL_ERR_SHAPE;
   int64_t n_sum = 0, r_sum = 0;
@@ -446,14 +462,17 @@ static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, c
   if (K == 0) return QERL_ERR_SHAPE;
   if (!aligned(x, 16) || ldx % 8 != 0) return QERL_ERR_ALIGN;
   const WorkspaceLayout L = workspace_layout(M, n_sum, K, r_sum);
-  if (!workspace || !aligned(workspace, 256) || workspace_bytes < L.total) return QERL_ERR_WORKSPACE;
+  if (need) *need = L.total;
+  else if (!workspace || !aligned(workspace, 256) || (!(exact && M <= 16) && workspace_bytes < L.total)) return QERL_ERR_WORKSPACE;
+  if (M > 16 && need) return QERL_OK;
   if (lora_ok && M >= kPanelMinTokens && M <= kPanelMaxTokens && (M > 16 || !t_given)) {
-    const int rc = panel_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, act, (hipStream_t)stream);
+    const int rc = panel_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, act, (hipStream_t)stream, need);
     if (rc != QERL_ERR_SHAPE) return rc;
   }
   if (act) return kNoFusedAct;
   if (stream_ok && g_use_stream)
-    return stream_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream);
+    return stream_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream, nullptr, 0, need);
+  if (need) return QERL_OK;
   if (M > 16 && lora_ok && n_members > 1)
     return gemm_group((const uint16_t*)x, M, K, ldx, members, n_members, (uint8_t*)workspace, L, (hipStream_t)stream);
   for (int i = 0; i < n_members; ++i) {   // general case: member by member
@@ -472,8 +491,26 @@ extern "C" int nvfp4_lora_linear_packed_group(const void* x, int64_t M, int64_t 
 }
 
 int qerl::packed_gate_up_act(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* gate_up, void* workspace,
-                             size_t workspace_bytes, uint16_t* act, void* stream) {
-  return packed_group_impl(x, M, K, ldx, gate_up, 2, workspace, workspace_bytes, act, stream);
+                             size_t workspace_bytes, uint16_t* act, void* stream, size_t* need) {
+  return packed_group_impl(x, M, K, ldx, gate_up, 2, workspace, workspace_bytes, act, stream, true, need);
+}
+
+int qerl::packed_group_exact(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* members, int n_members, void* workspace,
+                             size_t workspace_bytes, void* stream, size_t* need) {
+  return packed_group_impl(x, M, K, ldx, members, n_members, workspace, workspace_bytes, nullptr, stream, true, need);
+}
+
+// SiLU(gate) (.) up formed while the streaming kernel stages its input: M <= 16, the adapter as the decode kernels take it
+int qerl::packed_swiglu_exact(const void* gate, const void* up, int64_t M, int64_t K, const qerl_linear_desc* down, void* workspace,
+                              size_t workspace_bytes, void* stream, size_t* need) {
+  LinearCall c{(const uint16_t*)gate, M, K, K, down->tensor_scale, down->N, (const uint16_t*)down->A_bf16, (const uint16_t*)down->B_bf16, down->r,
+               down->lora_scale, (uint16_t*)down->y_bf16, down->ldy, workspace, ~(size_t)0, (hipStream_t)stream};
+  if (!need) {
+    const int vr = validate(c, down->packed, down->packed);
+    if (vr != QERL_OK) return vr > 0 ? QERL_OK : vr;
+  }
+  const WorkspaceLayout L = workspace_layout(M, down->N, K, down->r);
+  return stream_group(c.x, M, K, K, down, 1, (uint8_t*)workspace, L, c.st, (const uint16_t*)up, K, need);
 }
 
 extern "C" size_t nvfp4_prepack_bytes(int64_t N, int64_t K) {

@@ -9,7 +9,8 @@ namespace qerl {
 
 // Up to 16 tokens norm and linears can go out as ONE launch (block_kernel) or as separate ones: the norm with the adapters'
 // down-projections, the grouped linear, the gated down projection (up to 8 tokens), the norm and the panel kernels (from 9 on).
-// The separate launches are the faster ones; the one launch serves workspaces of the size that it needs alone.
+// The separate launches are the faster ones; the one launch serves workspaces of the size that it needs alone where they need more (their
+// areas are counted by the plans that run and shared by gate + up and down: up to 8 tokens that fits the one launch's size).
 // Measured, us in graph replay, one launch / separate: feed-forward block 7B shapes 1 token 55 / 49, 8 tokens 59 / 52, 9 tokens 66 / 62;
 // 14B 65 / 51, 67 / 55; 32B 75 / 73, 79 / 80, 89 / 94; 2048 x 5504 38 / 30, 39 / 34; norm + q + k + v
 // 7B 18 / 14, 19 / 15, 23 / 18; 14B 21 / 17, 22 / 20; 32B 20 / 17, 22 / 20, 28 / 22; 2048 wide 18 / 13, 19 / 13.
@@ -105,24 +106,35 @@ static size_t blk_t_bytes(int64_t M, const qerl_linear_desc* const* d, int n) {
   for (int i = 0; i < n; ++i) b += blk_align256((size_t)QERL_T_PARTS * (size_t)(M > 0 ? M : 1) * (size_t)(d[i]->r > 0 ? d[i]->r : 0) * sizeof(float));
   return b;
 }
-// The norm's launch: xn = aqn_rmsnorm(x), and up to 8 tokens with it t_i = xn A_i^T of the members with an adapter (m[i].t_f32).
+// The size functions: a buffer for M tokens holds every smaller count too (up to 16 tokens each has a plan of its own).  0: not a shape
+// of the call.
+template <class Need>
+static size_t blk_bytes_of_largest(int64_t M, Need need_of) {
+  size_t most = 0;
+  if (need_of(M, &most) != QERL_OK) return 0;
+  for (int64_t m = 1; m < M && m <= 16; ++m) {
+    size_t need = 0;
+    if (need_of(m, &need) == QERL_OK && need > most) most = need;
+  }
+  return most;
+}
+// Whether the norm's launch computes them (rows beyond 8192 it does not take: the linears do)
+static bool blk_norm_with_t(int64_t M, int64_t K, const void* gain) { return gain && M < kBlkPanelTokens && K <= 8192; }
+// The norm's launch: xn = aqn_rmsnorm(x), and with_t: t_i = xn A_i^T of the members with an adapter (m[i].t_f32) too.
 static int blk_norm(const void* x, int64_t M, int64_t K, int64_t ldx, const void* gain, const float* noise, float eps, uint16_t* xn,
-                    qerl_linear_desc* m, int n, uint8_t* t_area, void* stream) {
+                    qerl_linear_desc* m, int n, bool with_t, uint8_t* t_area, void* stream) {
   const void* A[kMaxGroup];
   float* t[kMaxGroup];
   int64_t r[kMaxGroup];
   int na = 0;
-  for (int i = 0; i < n && M < kBlkPanelTokens; ++i)
-    if (m[i].r > 0) {
-      A[na] = m[i].A_bf16; r[na] = m[i].r; t[na] = (float*)t_area; m[i].t_f32 = (float*)t_area;
-      t_area += blk_align256((size_t)QERL_T_PARTS * (size_t)M * (size_t)m[i].r * sizeof(float));
-      ++na;
-    }
-  if (na > 0) {
-    const int rc = aqn_rmsnorm_lora_down(x, M, K, ldx, gain, noise, eps, xn, K, A, r, t, na, stream);
-    if (rc != QERL_ERR_SHAPE) return rc;
-    for (int i = 0; i < n; ++i) m[i].t_f32 = nullptr;   // (rows beyond 8192: the linears compute t themselves)
+  for (int i = 0; i < n; ++i) {
+    m[i].t_f32 = nullptr;
+    if (!with_t || m[i].r == 0) continue;
+    A[na] = m[i].A_bf16; r[na] = m[i].r; t[na] = (float*)t_area; m[i].t_f32 = (float*)t_area;
+    t_area += blk_align256((size_t)QERL_T_PARTS * (size_t)M * (size_t)m[i].r * sizeof(float));
+    ++na;
   }
+  if (na > 0) return aqn_rmsnorm_lora_down(x, M, K, ldx, gain, noise, eps, xn, K, A, r, t, na, stream);
   return aqn_rmsnorm(x, M, K, ldx, gain, noise, eps, xn, K, stream);
 }
 
@@ -138,9 +150,17 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
   int64_t n_sum = 0, r_sum = 0;
   for (int i = 0; i < n; ++i) { d[i] = members + i; n_sum += members[i].N; r_sum += members[i].r; }
   if (M == 0 && launch) return QERL_OK;
-  const size_t lin = launch ? linear_need_bytes(M, n_sum, K, r_sum) : nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
+  // up to 16 tokens what the launches touch, beyond what the linear is checked against; what the size function answers may be more
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)K * sizeof(uint16_t)) : 0;
-  const size_t separate_bytes = lin + xn_bytes + (gain && M < kBlkPanelTokens ? blk_t_bytes(M, d, n) : 0);
+  const bool with_t = blk_norm_with_t(M, K, gain);
+  qerl_linear_desc own[kMaxGroup];
+  for (int i = 0; i < n; ++i) {   // this entry point computes t itself
+    own[i] = members[i];
+    own[i].t_f32 = with_t && own[i].r > 0 ? (const float*)(uintptr_t)256 : nullptr;
+  }
+  size_t lin = launch || M <= 16 ? linear_need_bytes(M, n_sum, K, r_sum) : nvfp4_lora_linear_workspace_bytes(M, n_sum, K, r_sum);
+  if (M > 0 && M <= 16) (void)packed_group_exact((const void*)(uintptr_t)256, M, K, gain ? K : ldx, own, n, (void*)(uintptr_t)256, 0, nullptr, &lin);
+  const size_t separate_bytes = lin + xn_bytes + (with_t ? blk_t_bytes(M, d, n) : 0);
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 1;
@@ -161,15 +181,13 @@ static int group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, const vo
   if (!workspace || !aligned(workspace, 256) || bytes < separate_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
   int64_t ldin = ldx;
-  qerl_linear_desc own[kMaxGroup];
-  for (int i = 0; i < n; ++i) { own[i] = members[i]; own[i].t_f32 = nullptr; }   // this entry point computes t itself
   if (gain) {
     uint16_t* xn = (uint16_t*)((uint8_t*)workspace + lin);
-    const int rc = blk_norm(x, M, K, ldx, gain, noise, eps, xn, own, n, (uint8_t*)workspace + lin + xn_bytes, stream);
+    const int rc = blk_norm(x, M, K, ldx, gain, noise, eps, xn, own, n, with_t, (uint8_t*)workspace + lin + xn_bytes, stream);
     if (rc != QERL_OK) return rc;
     xin = xn; ldin = K;
   }
-  return nvfp4_lora_linear_packed_group(xin, M, K, ldin, own, n, workspace, lin, stream);
+  return packed_group_exact(xin, M, K, ldin, own, n, workspace, lin, stream);
 }
 
 extern "C" size_t aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(int64_t M, int64_t K, const int64_t* Ns, const int64_t* rs, int n) {
@@ -180,9 +198,9 @@ extern "C" size_t aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(int64_t M,
     d[i].A_bf16 = (const void*)(uintptr_t)256; d[i].B_bf16 = (const void*)(uintptr_t)256; d[i].r = rs[i];
     d[i].y_bf16 = (void*)(uintptr_t)256; d[i].ldy = Ns[i];
   }
-  size_t need = 0;
-  const int rc = group_impl(nullptr, M, K, K, (const void*)(uintptr_t)256, nullptr, 0.f, d, n, nullptr, 0, nullptr, false, &need);
-  return rc == QERL_OK ? need : 0;
+  return blk_bytes_of_largest(M, [&](int64_t m, size_t* need) {
+    return group_impl(nullptr, m, K, K, (const void*)(uintptr_t)256, nullptr, 0.f, d, n, nullptr, 0, nullptr, false, need);
+  });
 }
 
 extern "C" int aqn_rmsnorm_nvfp4_lora_linear_group(const void* x, int64_t M, int64_t K, int64_t ldx, const void* gain,
@@ -201,19 +219,34 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   if (M == 0 && launch) return QERL_OK;
   if (launch && (!down->y_bf16 || down->ldy < down->N)) return down->y_bf16 ? QERL_ERR_SHAPE : QERL_ERR_NULL;
   const size_t act_bytes = blk_align256((size_t)(M > 0 ? M : 1) * (size_t)I * sizeof(uint16_t));
-  const size_t lin_gu = launch ? linear_need_bytes(M, 2 * I, H, gate->r + up->r) : nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r);
-  const size_t lin_dn = launch ? linear_need_bytes(M, down->N, I, down->r) + blk_align256((size_t)M * (size_t)I * sizeof(uint16_t))
-                               : nvfp4_lora_linear_swiglu_workspace_bytes(M, down->N, I, down->r);
-  const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
   const size_t xn_bytes = gain ? blk_align256((size_t)M * (size_t)H * sizeof(uint16_t)) : 0;
+  const bool with_t = blk_norm_with_t(M, H, gain);
+  void* const ph = (void*)(uintptr_t)256;            // for plans: checked, never read
+  qerl_linear_desc gu[2] = {*gate, *up};
+  for (qerl_linear_desc& m : gu) { m.y_bf16 = ph; m.ldy = I; m.t_f32 = with_t && m.r > 0 ? (const float*)ph : nullptr; }
+  // gate + up, then down, in the same area: up to 16 tokens what their launches touch, beyond what the linears are checked against
+  // (what the size function answers may be more)
+  const bool answer = !launch && M > 16;
+  size_t lin_gu = answer ? nvfp4_lora_linear_workspace_bytes(M, 2 * I, H, gate->r + up->r) : linear_need_bytes(M, 2 * I, H, gate->r + up->r);
+  size_t lin_dn = (answer ? nvfp4_lora_linear_workspace_bytes(M, down->N, I, down->r) : linear_need_bytes(M, down->N, I, down->r)) + act_bytes;
+  bool fused = false;                                // SiLU(gate) (.) up from one launch: neither gate nor up is stored
+  if (M > 0 && M <= 16) {
+    const int64_t ldin = gain ? H : ldx;
+    fused = packed_gate_up_act(ph, M, H, ldin, gu, ph, 0, (uint16_t*)ph, nullptr, &lin_gu) == QERL_OK;
+    if (!fused) (void)packed_group_exact(ph, M, H, ldin, gu, 2, ph, 0, nullptr, &lin_gu);
+    qerl_linear_desc dn = *down;
+    dn.y_bf16 = ph; dn.ldy = down->N; dn.t_f32 = nullptr;
+    if (fused) (void)packed_group_exact(ph, M, I, I, &dn, 1, ph, 0, nullptr, &lin_dn);
+    else (void)packed_swiglu_exact(ph, ph, M, I, &dn, ph, 0, nullptr, &lin_dn);
+  }
+  const size_t lin = lin_gu > lin_dn ? lin_gu : lin_dn;
   const qerl_linear_desc* gu_d[2] = {gate, up};
-  const size_t separate_bytes = lin + xn_bytes + 2 * act_bytes + (gain && M < kBlkPanelTokens ? blk_t_bytes(M, gu_d, 2) : 0);
+  const size_t separate_bytes = lin + xn_bytes + (fused ? 1 : 2) * act_bytes + (with_t ? blk_t_bytes(M, gu_d, 2) : 0);
   const bool separate = M > 0 && !down->bias_bf16 && (!launch || bytes >= separate_bytes);
   if (M <= 16) {
     BlkArgs a{};
     a.M = (int)(M > 0 ? M : 1); a.n_stages = 2;
-    const qerl_linear_desc* gu[2] = {gate, up};
-    int rc = blk_fill_stage(a.st[0], launch ? x : (const void*)(uintptr_t)256, H, ldx, gain, noise, eps, gu, 2, true);
+    int rc = blk_fill_stage(a.st[0], launch ? x : (const void*)(uintptr_t)256, H, ldx, gain, noise, eps, gu_d, 2, true);
     if (rc != QERL_OK) return rc;
     // the activation's place is known once the plan (size of the partial tiles) is: plan with a placeholder first
     const qerl_linear_desc* dn[1] = {down};
@@ -249,26 +282,29 @@ static int mlp_impl(const void* x, int64_t M, int64_t H, int64_t ldx, const void
   if (!ws || !aligned(ws, 256) || bytes < separate_bytes) return QERL_ERR_WORKSPACE;
   const void* xin = x;
   int64_t ldin = ldx;
-  qerl_linear_desc gu[2] = {*gate, *up};
-  gu[0].y_bf16 = ws + lin + xn_bytes; gu[0].ldy = I; gu[0].t_f32 = nullptr;
-  gu[1].y_bf16 = ws + lin + xn_bytes + act_bytes; gu[1].ldy = I; gu[1].t_f32 = nullptr;
+  gu[0].y_bf16 = ws + lin + xn_bytes;
+  gu[1].y_bf16 = ws + lin + xn_bytes + act_bytes;   // (not written where act comes from one launch)
   if (gain) {
     uint16_t* xn = (uint16_t*)(ws + lin);
-    const int rc = blk_norm(x, M, H, ldx, gain, noise, eps, xn, gu, 2, ws + lin + xn_bytes + 2 * act_bytes, stream);
+    const int rc = blk_norm(x, M, H, ldx, gain, noise, eps, xn, gu, 2, with_t, ws + lin + xn_bytes + 2 * act_bytes, stream);
     if (rc != QERL_OK) return rc;
     xin = xn; ldin = H;
   }
   uint16_t* act = (uint16_t*)(ws + lin + xn_bytes);   // gate's place: the fused form stores no gate
-  int rc = packed_gate_up_act(xin, M, H, ldin, gu, ws, lin, act, stream);
+  qerl_linear_desc dn = *down;
+  dn.t_f32 = nullptr;
+  int rc = M > 16 || fused ? packed_gate_up_act(xin, M, H, ldin, gu, ws, lin, act, stream) : kNoFusedAct;
   if (rc == QERL_OK) {
     if (down->bias_bf16) return QERL_ERR_SHAPE;
+    if (M <= 16) return packed_group_exact(act, M, I, I, &dn, 1, ws, lin, stream);
     return nvfp4_lora_linear_packed(act, M, I, I, down->packed, down->tensor_scale, down->N, down->A_bf16, down->B_bf16, down->r,
                                     down->lora_scale, down->y_bf16, down->ldy, ws, lin, stream);
   }
   if (rc != kNoFusedAct) return rc;
-  rc = nvfp4_lora_linear_packed_group(xin, M, H, ldin, gu, 2, ws, lin, stream);
+  rc = packed_group_exact(xin, M, H, ldin, gu, 2, ws, lin, stream);   // (beyond 16 tokens as nvfp4_lora_linear_packed_group)
   if (rc != QERL_OK) return rc;
   if (down->bias_bf16) return QERL_ERR_SHAPE;   // (the gated entry point takes no bias)
+  if (M <= 16) return packed_swiglu_exact(gu[0].y_bf16, gu[1].y_bf16, M, I, &dn, ws, lin, stream);
   return nvfp4_lora_linear_packed_swiglu(gu[0].y_bf16, gu[1].y_bf16, M, I, I, I, down->packed, down->tensor_scale, down->N,
                                          down->A_bf16, down->B_bf16, down->r, down->lora_scale, down->y_bf16, down->ldy, ws, lin, stream);
 }
@@ -280,9 +316,9 @@ extern "C" size_t aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes(int64_t M, int64_t 
   g.packed = ph; g.tensor_scale = (const float*)ph; g.N = I; g.A_bf16 = ph; g.B_bf16 = ph; g.r = r_gate;
   u = g; u.r = r_up;
   d = g; d.N = N_down; d.r = r_down; d.y_bf16 = (void*)(uintptr_t)256; d.ldy = N_down;
-  size_t need = 0;
-  const int rc = mlp_impl(nullptr, M, H, H, ph, nullptr, 0.f, &g, &u, &d, nullptr, 0, nullptr, false, &need);
-  return rc == QERL_OK ? need : 0;
+  return blk_bytes_of_largest(M, [&](int64_t m, size_t* need) {
+    return mlp_impl(nullptr, m, H, H, ph, nullptr, 0.f, &g, &u, &d, nullptr, 0, nullptr, false, need);
+  });
 }
 
 extern "C" int aqn_rmsnorm_nvfp4_lora_mlp(const void* x, int64_t M, int64_t H, int64_t ldx, const void* gain, const float* noise,

@@ -205,6 +205,7 @@ struct PanelArgs {
   // workgroups over the units' stages: every unit in `split` pieces, or (0) `per` stages each, the first `rem` one more
   int n_main; int split; int per; int rem; uint32_t per_inv; uint32_t per1_inv;   // 2^32 / per, 2^32 / (per + 1), rounded up
   int direct;                                                               // whole units and no adapter: the first launch stores the outputs, there is no second
+  size_t used_bytes;                                                        // of the area, by the sums
   float* sums; float* t_sums;                                               // [slot][unit_tiles][NT][1024]; [t_parts][rank_tiles][tbs * NT][1024]
 };
 int plan_panel(PanelArgs& a, float* area, size_t area_bytes);
@@ -215,8 +216,14 @@ size_t linear_need_bytes(int64_t M, int64_t N, int64_t K, int64_t r);
 // gate_proj and up_proj as nvfp4_lora_linear_packed_group, with act[M, N] = bf16(bf16(SiLU(gate)) * up) in place of their
 // outputs; kNoFusedAct (nothing launched) where the shape has no kernel for it (api.hip)
 constexpr int kNoFusedAct = 1;
+// need != null: nothing is launched, *need = the bytes of workspace that the call would touch (M <= 16; beyond, what it is checked against)
 int packed_gate_up_act(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* gate_up, void* workspace,
-                       size_t workspace_bytes, uint16_t* act, void* stream);
+                       size_t workspace_bytes, uint16_t* act, void* stream, size_t* need = nullptr);
+// nvfp4_lora_linear_packed_group and the gated linear of up to 16 tokens on a workspace of the bytes that `need` answers
+int packed_group_exact(const void* x, int64_t M, int64_t K, int64_t ldx, const qerl_linear_desc* members, int n_members, void* workspace,
+                       size_t workspace_bytes, void* stream, size_t* need = nullptr);
+int packed_swiglu_exact(const void* gate, const void* up, int64_t M, int64_t K, const qerl_linear_desc* down, void* workspace,
+                        size_t workspace_bytes, void* stream, size_t* need = nullptr);
 
 // General fallback (any K % 16 == 0, any alignment of rows the ABI allows).
 int launch_generic_lora_down(const uint16_t* x, int64_t ldx, int64_t M, int64_t K, const uint16_t* A,

@@ -725,6 +725,7 @@ int plan_panel(PanelArgs& a, float* area, size_t area_bytes) {
   a.per = (int)(total / a.n_main); a.rem = (int)(total - (int64_t)a.per * a.n_main);
   auto inverse = [](int d) { return d > 1 ? (uint32_t)((((uint64_t)1 << 32) + d - 1) / d) : 0xffffffffu; };
   a.per_inv = inverse(a.per); a.per1_inv = inverse(a.per + 1);
+  a.used_bytes = (size_t)(t_bytes + (a.direct ? 0 : (a.split > 0 ? a.n_main : a.n_main + a.units - 1) * slot_bytes));
   a.t_sums = area;
   a.sums = area + t_bytes / 4;
   return QERL_OK;

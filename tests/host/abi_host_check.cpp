@@ -104,6 +104,46 @@ int main() {
           }
     printf("host check: %ld calls walked to their launches\n", walks);
   }
+  // The composed calls on a workspace of the size that is asked for, and on the smallest that is accepted: never the one persistent
+  // launch on the first (but a group without a norm up to 8 tokens, and a feed-forward block whose down has a bias), always on the
+  // second where it is the smaller; up to 8 tokens and H = 8192 the size of that launch is enough for the separate ones.
+  {
+    long one_launch = 0, separate = 0;
+    for (int64_t H : {512, 1024, 2048, 3584, 5120, 9216})
+      for (int64_t I : {1024, 5504, 18944, 27648})
+        for (int64_t r : {0, 16, 64})
+          for (int64_t M : {1, 5, 8, 9, 12, 16}) {
+            qerl_linear_desc g{}, d{};
+            g.packed = fake; g.tensor_scale = (const float*)fake; g.N = g.ldy = I; g.y_bf16 = fake; g.A_bf16 = g.B_bf16 = fake; g.r = r;
+            d = g;
+            d.N = d.ldy = H;
+            qerl_linear_desc grp[2] = {g, d};
+            const int64_t Ns[2] = {I, H}, rs[2] = {r, r};
+            for (int what = 0; what < 2; ++what) {
+              auto call = [&](size_t bytes) {
+                launched.clear();
+                return what == 0 ? aqn_rmsnorm_nvfp4_lora_mlp(fake, M, H, H, fake, nullptr, 1e-6f, &g, &g, &d, fake, bytes, nullptr)
+                                 : aqn_rmsnorm_nvfp4_lora_linear_group(fake, M, H, H, fake, nullptr, 1e-6f, grp, 2, fake, bytes, nullptr);
+              };
+              const size_t need = what == 0 ? aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes(M, H, I, H, r, r, r)
+                                            : aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(M, H, Ns, rs, 2);
+              bad += call(need) != QERL_OK || count_launches("block_kernel") != 0;
+              ++separate;
+              size_t lo = 0, hi = need / 256;
+              while (hi - lo > 1) {
+                const size_t mid = (lo + hi) / 2;
+                (call(mid * 256) == QERL_OK ? hi : lo) = mid;
+              }
+              bad += call(hi * 256) != QERL_OK || call(hi * 256 - 256) != QERL_ERR_WORKSPACE;
+              call(hi * 256);
+              const int n = count_launches("block_kernel");
+              bad += n != 0 && (n != 1 || count_launches(nullptr) != 1 || (M <= 8 && H <= 8192));
+              one_launch += n;
+            }
+          }
+    printf("host check: %ld composed calls as separate launches, %ld smallest workspaces with the one launch\n", separate, one_launch);
+    bad += one_launch == 0;
+  }
   printf("host check: %ld sizing calls, %d unexpected results\n", plans, bad);
   return bad != 0;
 }

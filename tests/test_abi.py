@@ -163,6 +163,19 @@ def test_linear_workspace_of_the_largest_call_serves_every_smaller_one(lib):
             assert (s := [f(M, 5120, 5120, r) for r in range(0, 520, 8)]) == sorted(s), M
 
 
+def test_composed_workspaces_hold_what_is_alive(lib):
+    """The composed calls' sizes never fall when the token count grows, and up to 16 tokens they count what the chosen launches touch, once
+    for gate + up and down: a few MB at the largest shapes, not the sum of the separate calls' sizes."""
+    mlp, group = lib.aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes, qerl.aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes
+    tokens = list(range(1, 140)) + [255, 256, 257, 777, 1024, 1025, 4096]
+    for H, I, r in ((5120, 27648, 64), (3584, 18944, 32), (2048, 5504, 16), (512, 1024, 8), (9216, 4096, 0), (1024, 40000, 64)):
+        assert (s := [mlp(M, H, I, H, r, r, r) for M in tokens]) == sorted(s), (H, I, r)
+        assert (s := [group(M, H, [H, I, I], [r] * 3) for M in tokens]) == sorted(s), (H, I, r)
+    assert mlp(1, 5120, 27648, 5120, 64, 64, 64) < 3.2e6 and mlp(8, 5120, 27648, 5120, 64, 64, 64) < 3.6e6
+    assert mlp(1, 3584, 18944, 3584, 32, 32, 32) < 3.0e6 and mlp(16, 3584, 18944, 3584, 32, 32, 32) < 6e6
+    assert mlp(16, 5120, 27648, 5120, 64, 64, 64) < 17e6
+
+
 def _backward_group_bytes(lib, M, K, members):
     from paper_2510_11696_amd.binding import _BackwardDesc
     d = (_BackwardDesc * len(members))()
