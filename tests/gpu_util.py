@@ -53,3 +53,20 @@ def quantize_both(W_f32: np.ndarray):
     torch.cuda.synchronize()
     ref = oracle.nvfp4_quantize(W_f32)
     return (codes, scales, ts), ref
+
+
+def smallest_workspace(call, upper):
+    """The smallest workspace (in steps of 256 bytes) that call(workspace) accepts, found from one of `upper` bytes downwards: a call on a
+    smaller one is refused on the host."""
+    def fits(n):
+        try:
+            call(qerl.Workspace(n * 256))
+            return True
+        except qerl.QerlError as e:
+            assert e.status == -4, e
+            return False
+    lo, hi = 1, -(-upper // 256)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid) else (mid, hi)
+    return qerl.Workspace(hi * 256)

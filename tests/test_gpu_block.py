@@ -1,4 +1,4 @@
-"""GPU parity of the fused decode launches against the oracle's composition of the same operators:
+"""GPU parity of the composed calls against the oracle's composition of the same operators:
     aqn_rmsnorm -> (round to bf16) -> nvfp4_lora_linear for every member                      (norm + group)
     aqn_rmsnorm -> gate, up -> (round to bf16) -> silu_mul -> nvfp4_lora_linear(down)         (feed-forward block)
 The device rounds the intermediate activations from fp32 sums, the oracle from fp64 ones, so a few of them differ by
@@ -63,7 +63,7 @@ def _norm_inputs(M, H, seed, sigma):
     (3584, (1184, 1184), (32, 0), 1e-2, False),             # a member without adapter
     (1040, (72,), (0,), 5e-3, False),                       # K not a multiple of 128, no adapter at all: no producers
 ])
-def test_norm_and_group_in_one_launch(M, H, Ns, rs, sigma, bias):
+def test_norm_and_group_in_one_call(M, H, Ns, rs, sigma, bias):
     print("norm+group case", M, H, Ns, rs, sigma, bias, flush=True)
     xin, gain, Z, xn = _norm_inputs(M, H, 400 + M, sigma)
     mem = [_member(N, H, r, 5000 + 10 * i + M, bias) for i, (N, r) in enumerate(zip(Ns, rs))]
@@ -101,7 +101,7 @@ def test_group_without_norm_in_the_block_kernel(M):
     (2048, 4096, (0, 0, 0), None),           # no adapters, no noise
     (1024, 640, (8, 0, 64), 1e-2),           # mixed ranks
 ])
-def test_feed_forward_block_in_one_launch(M, H, I, rs, sigma):
+def test_feed_forward_block_in_one_call(M, H, I, rs, sigma):
     print("mlp case", M, H, I, rs, sigma, flush=True)
     xin, gain, Z, xn = _norm_inputs(M, H, 800 + M, sigma)
     gate = _member(I, H, rs[0], 6000 + M)

@@ -16,7 +16,7 @@ import paper_2510_11696_amd as qerl
 import qerl_synth as qs
 from oracle import nvfp4_oracle as oracle
 from tests import cases
-from tests.gpu_util import bf16_ulp_distance, check_linear
+from tests.gpu_util import bf16_ulp_distance, check_linear, smallest_workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -143,8 +143,8 @@ def _single_twice(x, m, lora_scale):
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("M", [32, 64, 128])
 def test_7b_mlp_at_a_few_dozen_tokens_as_the_benchmark_launches_it(mlp_7b, M):
-    """gate + up as one group (76 MB streamed: the adapters' down-projections run as the first workgroups of the
-    launch) and down (K = 18944: K-splits and in-launch producers), r = 32, behind the stand-alone RMSNorm."""
+    """gate + up as one group (76 MB streamed; x A^T by the first workgroups of the launch) and down (K = 18944: several
+    pieces per unit), r = 32, behind the stand-alone RMSNorm."""
     print("full-size 7B MLP,", M, "tokens", flush=True)
     g, u, d = mlp_7b["gate"], mlp_7b["up"], mlp_7b["down"]
     y, y_np, _ = _normed_input(M, 3584, 63000 + M, False, [])
@@ -159,9 +159,8 @@ def test_7b_mlp_at_a_few_dozen_tokens_as_the_benchmark_launches_it(mlp_7b, M):
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("M", [1, 16, 128, 300])
 def test_32b_mlp_as_the_benchmark_launches_it(block_32b, M):
-    """32B gate + up (2 x 27648 x 5120: 1728 row tiles) as one group and down (5120 x 27648), r = 64.  From 96 tokens
-    on the GEMM takes over: down's 40 column blocks split K over workgroups (partial sums added by a second launch)
-    and carry the LoRA down-projection as the launch's first workgroups; 300 tokens: three token blocks, the last ragged."""
+    """32B gate + up (2 x 27648 x 5120: 1728 row tiles) as one group and down (5120 x 27648), r = 64.  1 token: the
+    streaming kernel; 16 and 128: the panel kernels; 300: the prefill GEMM for gate + up, three token blocks, the last ragged."""
     print("full-size 32B MLP,", M, "tokens", flush=True)
     g, u, d = block_32b["gate"], block_32b["up"], block_32b["down"]
     y, y_np, ts = _normed_input(M, 5120, 64000 + M, M <= 16, [g.A, u.A])
@@ -209,9 +208,10 @@ def _bf16(a64):
 
 
 def _fused_mlp_case(mem, M, H, seed):
-    """The feed-forward block in ONE launch (norm, gate + up, SiLU-mul, down) on full-size weights, against the
+    """The feed-forward block in one call (norm, gate + up, SiLU-mul, down) on full-size weights, against the
     oracle's composition of the operators: the oracle computes every gate / up output (the down projection reads
-    them all) and the sampled rows of down.  Twice on one workspace, second run bit-identical."""
+    them all) and the sampled rows of down.  Twice on one workspace, second run bit-identical.  From 9 tokens on also on the
+    smallest workspace that is accepted, where the call is one persistent launch."""
     g, u, d = mem["gate"], mem["up"], mem["down"]
     xin = qs.activations(M, H, seed)
     gain = qs.rms_gain(H, seed + 1)
@@ -230,27 +230,38 @@ def _fused_mlp_case(mem, M, H, seed):
     assert torch.equal(y, again), "second run on the same workspace differs"
     # (composed operators: the device rounds the intermediate activations from fp32 sums, the oracle from fp64 ones)
     check_linear(y[:, d.rows_d], ref, ("fused MLP", M, H), slack=4e-3)
+    if M > 8:
+        small = smallest_workspace(lambda w: qerl.aqn_rmsnorm_nvfp4_lora_mlp(
+            xin.cuda(), gain.cuda(), Z.cuda(), 1e-6, g.pw, u.pw, d.pw, (g.Ad, u.Ad, d.Ad), (g.Bd, u.Bd, d.Bd), (2.0, 2.0, 2.0), workspace=w), ws.nbytes)
+        assert small.nbytes < ws.nbytes
+        ws = small
+        y = call().clone()
+        again = call()
+        torch.cuda.synchronize()
+        assert qerl.workspace_status(ws) == 0
+        assert torch.equal(y, again), "second run on the same workspace differs"
+        check_linear(y[:, d.rows_d], ref, ("fused MLP in one launch", M, H), slack=4e-3)
 
 
 @pytest.mark.timeout(900)
 @pytest.mark.parametrize("M", [1, 8, 16])
-def test_32b_feed_forward_block_in_one_launch(block_32b, M):
-    print("full-size 32B feed-forward block in one launch,", M, "tokens", flush=True)
+def test_32b_feed_forward_block_in_one_call(block_32b, M):
+    print("full-size 32B feed-forward block in one call,", M, "tokens", flush=True)
     _fused_mlp_case(block_32b, M, 5120, 67000 + M)
 
 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("M", [8, 16])
-def test_7b_feed_forward_block_in_one_launch(mlp_7b, M):
-    print("full-size 7B feed-forward block in one launch,", M, "tokens", flush=True)
+def test_7b_feed_forward_block_in_one_call(mlp_7b, M):
+    print("full-size 7B feed-forward block in one call,", M, "tokens", flush=True)
     _fused_mlp_case(mlp_7b, M, 3584, 67100 + M)
 
 
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("M", [1, 16])
-def test_32b_norm_and_attention_projections_in_one_launch(block_32b, M):
-    """AQN RMSNorm + q + k + v of the 32B block as one launch of the block kernel."""
-    print("full-size 32B norm + q + k + v in one launch,", M, "tokens", flush=True)
+def test_32b_norm_and_attention_projections_in_one_call(block_32b, M):
+    """AQN RMSNorm + q + k + v of the 32B block in one call."""
+    print("full-size 32B norm + q + k + v in one call,", M, "tokens", flush=True)
     q, k, v = block_32b["q"], block_32b["k"], block_32b["v"]
     H = 5120
     xin = qs.activations(M, H, 68000 + M)

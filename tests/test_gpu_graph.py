@@ -48,8 +48,7 @@ def _replays_match(run, results):
         torch.cuda.synchronize()
 
 
-# 8: the streaming kernel; 40: the mid kernel behind a launch of the LoRA down-projection; 128: the mid kernel with
-# the down-projection's workgroups inside its own launch; 300: the grouped GEMM
+# 8: the streaming kernel; 40, 128: the panel kernels; 300: the grouped GEMM
 @pytest.mark.parametrize("M", [8, 40, 128, 300])
 def test_mlp_block_launches_replay_like_eager(M):
     print("graph case: mlp block, M =", M, flush=True)
@@ -76,11 +75,10 @@ def test_mlp_block_launches_replay_like_eager(M):
     _replays_match(run, lambda: [xn, outs[0], outs[1], y])
 
 
-# the persistent multi-stage kernel: its stage boundary, hand-over words and K-range counters live in the workspace
-# and are re-armed by the launch itself
+# the composed calls: a few launches each that hand their results through the workspace
 @pytest.mark.parametrize("M", [1, 8, 16])
-def test_fused_block_launches_replay_like_eager(M):
-    print("graph case: fused launches, M =", M, flush=True)
+def test_composed_calls_replay_like_eager(M):
+    print("graph case: composed calls, M =", M, flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(70 + M)
     H, I, r = 2048, 2816, 32

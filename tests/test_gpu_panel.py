@@ -1,6 +1,6 @@
 """GPU parity of the 9..128-token kernels (linear_panel.hip) at the sizes where their plan changes: edges of token tiles, row
 tiles, units and stages, each way of cutting the units into pieces, ranks beyond one chunk, rows in several launches, outputs
-without 8-byte stores, and workspaces with room for the one-launch kernels only."""
+and without 8-byte stores."""
 
 import numpy as np
 import pytest
@@ -167,39 +167,3 @@ def test_feed_forward_block_with_the_gated_second_launch(M, H, I, r):
     y = call(ws)
     check_linear(y, ref, ("panel mlp", M, H, I, r), slack=4e-3)
     assert torch.equal(call(ws), y)
-
-
-@pytest.mark.parametrize("M", [1, 8, 9, 16])
-@pytest.mark.parametrize("H,I,r", [(1024, 2048, 16), (2048, 5504, 64)])
-def test_a_workspace_for_the_one_launch_form_is_still_accepted(M, H, I, r):
-    """Up to 16 tokens a buffer that holds the one-launch kernel's areas but not the separate launches' keeps running that
-    kernel: sizes from what the size function asks for downwards, each either refused or right."""
-    print("one-launch workspace", M, H, I, r, flush=True)
-    xin, gain, Z, xn = _norm_inputs(M, H, 21, 1e-2)
-    g, u, d = _member(I, H, r, 22), _member(I, H, r, 25), _member(H, I, r, 28)
-    act = _bf16(oracle.silu_mul(_bf16(_ref(g, xn, 2.0)), _bf16(_ref(u, xn, 2.0))))
-    ref_d, ref_g, ref_u = _ref(d, act, 2.0), _ref(g, xn, 2.0), _ref(u, xn, 2.0)
-    lib = qerl.load_library()
-    dev = [t.cuda() for t in (xin, gain, Z)]
-    outs = {}
-    for which in ("mlp", "group"):
-        need = (lib.aqn_rmsnorm_nvfp4_lora_mlp_workspace_bytes(M, H, I, H, r, r, r) if which == "mlp" else
-                qerl.aqn_rmsnorm_nvfp4_lora_linear_group_workspace_bytes(M, H, [I, I], [r, r]))
-        ran = []
-        for bytes_ in [need] + [need * k // 16 // 256 * 256 for k in range(15, 3, -1)]:
-            ws = qerl.Workspace(bytes_)
-            try:
-                if which == "mlp":
-                    y = [qerl.aqn_rmsnorm_nvfp4_lora_mlp(*dev, 1e-6, g["pw"], u["pw"], d["pw"], [m["Ad"] for m in (g, u, d)],
-                                                         [m["Bd"] for m in (g, u, d)], (2.0,) * 3, workspace=ws)]
-                else:
-                    y = qerl.aqn_rmsnorm_nvfp4_lora_linear_group(*dev, 1e-6, [g["pw"], u["pw"]], [g["Ad"], u["Ad"]], [g["Bd"], u["Bd"]],
-                                                                 [2.0, 2.0], workspace=ws)
-            except (RuntimeError, ValueError):
-                assert bytes_ < need
-                break
-            for got, ref in zip(y, [ref_d] if which == "mlp" else [ref_g, ref_u]):
-                check_linear(got, ref, (which, M, bytes_), slack=4e-3)
-            ran.append(bytes_)
-        outs[which] = ran
-    assert all(outs.values()), outs
