@@ -640,7 +640,7 @@ def run_leg(weights: Weights, M: int, args, steps: int, warmup: int, peaks):
     if peaks:
         ach = peaks["hbm_read_GBps"] if decode else peaks["mfma_bf16_TFLOPs"]
         leg["frac_of_achievable_whole_step"] = round(value / ach, 4)
-        roof["frac_of_achievable"] = round(roof["achieved"] / ach, 4)
+        roof["frac_of_achievable"] = round(roof["achieved"] / (peaks["hbm_read_GBps"] if roof["unit"] == "GB/s" else peaks["mfma_bf16_TFLOPs"]), 4)
     del stack
     torch.cuda.empty_cache()
     return leg
