@@ -198,10 +198,6 @@ struct MxArgs {
   const uint16_t* bias;
 };
 
-// The 8 columns [col, col + 8) of [hi | mid | lo] meet the same 8 columns of B in each of the three parts (r % 8 == 0
-// keeps a run inside one part); the zero padding past 3 r meets column 0.
-__device__ __forceinline__ int lora_b_col(int col, int r) { return col < 3 * r ? col % r : 0; }
-
 // NG: tiles (four 64-input steps each) per wave; MR: accumulator registers with live tokens (4: M <= 8, 16: M <= 32);
 // LC: 16-column chunks of ts the eighth wave has registers for (0: no adapter).  The LoRA up-projection is the eighth
 // wave's: in the first K-range it adds [hi | mid | lo] . [B B B]^T to the sum of the seven partial tiles with bf16
@@ -467,7 +463,7 @@ struct MxGemmArgs {
   const uint8_t* packed; int k_tiles; int n_tiles; int64_t N;
   uint16_t* y; int64_t ldy;
   int n_blocks, nblk_per_xcd;
-  const uint16_t* ts; int64_t ts_ld; int n_chunks; const uint16_t* B; int r;   // as in MxArgs
+  const uint16_t* ts; int64_t ts_ld; const uint16_t* B; int r;   // as in MxArgs
   const uint16_t* bias;
 };
 
@@ -768,7 +764,7 @@ static int mx_linear(const void* x, int64_t M, int64_t K, int64_t ldx, const voi
     MxGemmArgs g{};
     g.xq = xq; g.xs = xsc; g.M = M; g.K = K; g.packed = (const uint8_t*)packed;
     g.k_tiles = (int)ceil_div(K, 256); g.n_tiles = (int)ceil_div(N, 32); g.N = N; g.y = (uint16_t*)y; g.ldy = ldy;
-    g.ts = lo.ts; g.ts_ld = lo.ts_ld; g.n_chunks = lo.n_chunks; g.B = lo.B; g.r = lo.r; g.bias = lo.bias;
+    g.ts = lo.ts; g.ts_ld = lo.ts_ld; g.B = lo.B; g.r = lo.r; g.bias = lo.bias;
     return launch_mx_gemm(g, st);
   }
   const MxWorkspace w = mx_workspace(M, N, K);
