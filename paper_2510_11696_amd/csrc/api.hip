@@ -456,6 +456,7 @@ static int packed_group_impl(const void* x, int64_t M, int64_t K, int64_t ldx, c
     stream_ok = stream_ok && (d.r == 0 || (d.r <= 64 && d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
     lora_ok = lora_ok && (d.r == 0 || (d.r % 8 == 0 && aligned(d.A_bf16, 16) && aligned(d.B_bf16, 16)));
     t_given = t_given || (d.r > 0 && d.t_f32);
+    if (M > 0 && !aligned(d.packed, 16)) return QERL_ERR_ALIGN;
     if (d.r > 0 && d.t_f32 && !aligned(d.t_f32, 32)) return QERL_ERR_ALIGN;
   }
   if (M == 0) return QERL_OK;

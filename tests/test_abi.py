@@ -237,6 +237,10 @@ def test_host_side_validation_of_the_fused_entry_points(lib):
     assert grp(fake, 2, 64, 68, dp, 2, fake, big, None) == -3               # ldx % 8
     assert grp(fake, 2, 64, 64, dp, 2, None, big, None) == -4
     assert grp(fake, 2, 64, 64, dp, 2, fake, 64, None) == -4
+    for M in (2, 12, 100, 500):                                              # packed weights off 16 bytes, as the single linear refuses them
+        d[1].packed = fake + 8
+        assert grp(fake, M, 64, 64, dp, 2, fake, big, None) == -3
+        d[1].packed = fake
     d[1].ldy = 16                                                            # ldy < N
     assert grp(fake, 2, 64, 64, dp, 2, fake, big, None) == -2
     d[1].ldy = 32
