@@ -393,14 +393,15 @@ static int panel_group(const uint16_t* x, int64_t M, int64_t K, int64_t ldx, con
   if (M <= 16 && !bias) {   // (the decode kernels take no bias with more than 64 ranks)
     if (!one_part) return QERL_ERR_SHAPE;
     if (!act && r_max <= 64) {
-      // The streaming kernel is faster where every CU would have more than one unit and it need not split K (two of 18944 x 3584, r = 32, 9..16
-      // tokens 25 us against 30; 40000 x 5120, r = 16, 9 tokens 31 / 33, but at 12 tokens, K in two ranges, 39 / 34), and
+      // The streaming kernel is faster where every CU would have more than one unit of some length and it need not split K (two of 18944 x
+      // 3584, r = 32, 9..16 tokens 25 us against 30; 40000 x 5120, r = 16, 9 tokens 31 / 33, but 40000 x 1024, four stages, 20 / 18, and
+      // at 12 tokens 40000 x 5120, K in two ranges, 39 / 34), and
       // without adapters wherever the panel kernels need their second launch (4096 x 4096, 16 tokens 9.9 / 11.4, 13824 x 5120 in one 17 / 13).
       StreamArgs sa;
       size_t lds = 0;
       int MR = 4;
       if (a.rank_tiles == 0 && !a.direct) return QERL_ERR_SHAPE;
-      if (a.units > 256 && stream_plan(sa, &lds, &MR, x, M, K, ldx, d, n) == QERL_OK && sa.Sk == 1) return QERL_ERR_SHAPE;
+      if (a.units > 256 && (a.rank_tiles == 0 || a.stages >= 8) && stream_plan(sa, &lds, &MR, x, M, K, ldx, d, n) == QERL_OK && sa.Sk == 1) return QERL_ERR_SHAPE;
     }
   }
   for (int parts = 1; parts <= 64 && parts <= tiles; parts *= 2) {   // (ranks whose sums alone exceed the area fit in no number of parts)
