@@ -671,8 +671,10 @@ constexpr int kCfgTall = 2, kCfgPrefill = 3, kCfgBackward = 4;
 constexpr double kPrefillAlone = 0.58;
 // A single round of at most one workgroup per CU takes this much longer than the tiles' arithmetic says, as far as the panel kernels'
 // estimate is concerned (r = 0, us: 3584 + 512 + 512 rows, K = 3584, 777 tokens 59, estimated 34 without; 4096 x 4096, 1000 tokens 57 / 38; 5120 x 5120,
-// 512 tokens 62 / 46; 3584 x 18944, 777 tokens 202 / 155).  Over 348 launches of 160..1000 tokens the choice costs 2.3 % against the faster of both, 6.1 % without.
-constexpr double kGemmAloneEst = 1.4;
+// 512 tokens 62 / 46; 3584 x 18944, 777 tokens 202 / 155).  Over 348 launches of 160..1000 tokens the choice costs 2.1 % against the faster of both
+// (6.1 % without, 2.3 % with 1.4, which sent the 7B shapes' q + k + v, r = 32, 777 tokens to the GEMM: 83 us against 71).  What 1.7 costs:
+// 2048 + 256 + 256 rows, K = 2048, r = 0, 777 tokens 36 us against 32.
+constexpr double kGemmAloneEst = 1.7;
 static int g_force_cfg = -1;
 static bool g_split = true;   // whole rounds and remainder as two launches when that is estimated faster
 static int g_force_ksplit = 0;   // tuning: K-parts of the forward launch (0 = automatic, 1 = never)
