@@ -184,7 +184,8 @@ QERL_API int nvfp4_lora_linear_packed_noalloc(const void* x_bf16, int64_t M, int
 /* ---------------------------------------------------------------------------
  * nvfp4_lora_linear_packed_group -- up to 4 linears that read the same x (the
  * q/k/v or the gate/up projections of a block, which share one noisy RMSNorm
- * output: Section 3.3) in ONE launch.  Each member is the same function of its
+ * output: Section 3.3) in one call: one launch up to 8 tokens, a few launches for
+ * all members beyond.  Each member is the same function of its
  * inputs as in nvfp4_lora_linear_packed; the split of K over workgroups, and
  * with it the fp32 summation order, may differ between the two calls (each is
  * bit-reproducible from call to call).

@@ -25,8 +25,8 @@
 // run beside a matrix instruction), at 128 tokens these and the matrix pipe together (a 128-input stage of 256 rows takes 1.55 us,
 // 0.9 of it matrix instructions); for narrow linears the fixed chain, about 5 us of the first launch and 6 of the second.
 // Measured, whole layers in graph replay, before (one workgroup per CU owning whole rows, down-projections waited for inside the
-// launch, or the prefill GEMM) / now, us: 7B shapes, r = 32, 32 tokens 154 / 97, 64 tokens 184 / 110; 14B, r = 64, 77 tokens 249 / 143;
-// 32B, r = 64, 64 tokens 239 / 151, 128 tokens 272 / 204.
+// launch, or the prefill GEMM) / now, us, the range over several cards: 7B shapes, r = 32, 32 tokens 154 / 97, 64 tokens 184 / 110..115; 14B,
+// r = 64, 77 tokens 249 / 143..146; 32B, r = 64, 64 tokens 239 / 151..156, 128 tokens 272 / 204..212.
 //
 // Operand layouts and the packed tile format are described in linear_decode.hip.
 #include "linear.hpp"
