@@ -970,7 +970,9 @@ static int launch_down64_t(const GemmArgs& a, int n_tiles, int P, dim3 grid, hip
 // r = 16 and 64, the count taken / the chip filled twice over / once, in us: K = 13824: 512 tokens 16.8 (12 parts) / 20.0 / 20.2,
 // 2048 tokens 20.2 (8) / 24.2 / 20.2; K = 18944: 640 tokens 18.7 (15) / 25.6 / 23.1, 4096 tokens 42.1 (8) / 41.9 / 43.4; K = 5120:
 // 5504 tokens 19.4 (5) / 19.3 / 21.9, 8256 tokens 23.8 (3) / 24.0 / 31.6; over all, 0.94 and 0.92 of the time of either aim.
-static int64_t down64_parts(int64_t tbs, int64_t K, int tpw) {
+// A slab that is also quantised counts 1.25 (MX linears, K = 1024, r = 16, 300 and 1000 tokens, one part / two: 29 / 26 and 31 / 28 us; over 70 shapes
+// up to K = 13824 and 4096 tokens 0.99 of the time; with 1.5 0.994).
+static int64_t down64_parts(int64_t tbs, int64_t K, int tpw, bool quantizes) {
   const int64_t p_max = ceil_div(K, 512) < kDownMaxPartsWide ? ceil_div(K, 512) : kDownMaxPartsWide;
   auto filled = [&](int64_t wgs) { const int64_t p = wgs / tbs < p_max ? wgs / tbs : p_max; return p < 1 ? (int64_t)1 : p; };
   if (tpw > 1) return filled(256);
@@ -978,7 +980,7 @@ static int64_t down64_parts(int64_t tbs, int64_t K, int tpw) {
   int64_t best = p_most;
   double t_best = 0;
   for (int64_t p = p_most; p >= 1 && ceil_div(slabs, p) <= longest; --p) {
-    const double t = (double)ceil_div(slabs, p) * (tbs * p <= 256 ? 1.0 : 1.6) + (p > 1 ? 1.7 * (double)p + 6.0 : 0.0);
+    const double t = (double)ceil_div(slabs, p) * (tbs * p <= 256 ? 1.0 : 1.6) * (quantizes ? 1.25 : 1.0) + (p > 1 ? 1.7 * (double)p + 6.0 : 0.0);
     if (p == p_most || t < t_best) { best = p; t_best = t; }
   }
   return best;
@@ -999,7 +1001,7 @@ static int launch_lora_down64(const GemmArgs& a0, hipStream_t st) {
   const int64_t tbs = ceil_div(a.M, 64);
   int64_t P = 1;
   if (a.tpart && a.counters && tbs <= kDownMaxSlots) {
-    P = down64_parts(tbs, a.K, tpw);
+    P = down64_parts(tbs, a.K, tpw, a.xq != nullptr);
     if (g_down64_parts > 0) P = g_down64_parts;
     while (P > 1 && (size_t)(tbs * P) * 4 * tpw * 16 * 64 * sizeof(float) > kDownExchangeBytes) --P;
   }
